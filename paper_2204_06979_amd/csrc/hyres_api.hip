@@ -243,11 +243,18 @@ enum Parts { P_GRAM = 1, P_SMALL = 2, P_IMG = 4, P_SURE = 8 };
 void plan_cube(CubePlan& c, Layout& lay, int parts) {
     c.T = (c.p + 15) / 16;
     c.n = (int64_t)c.H * c.W;
+    bool gpart_in_coef = false;
     if (parts & P_GRAM) {
-        c.gslots = (int)std::max<int64_t>(1, std::min<int64_t>(256, cdiv(c.n, 2048)));
-        const size_t per = c.dtype == HYRES_F64 ? (size_t)c.p * (c.p + 1) / 2 * 8
-                                                : (size_t)c.T * (c.T + 1) / 2 * 256 * 4;
-        c.o_gpart = lay.add(per * c.gslots);
+        if (c.dtype == HYRES_F64) {
+            c.gslots = gram_f64_slots(c.T, c.n);
+            // partials in the coefficient vectors, which a solve fills after its Gram
+            const size_t need = gram_f64_bytes(c.T, c.gslots);
+            gpart_in_coef = (parts & P_IMG) && (size_t)c.r * rup(c.nc, 64) * 8 >= need;
+            if (!gpart_in_coef) c.o_gpart = lay.add(need);
+        } else {
+            c.gslots = (int)std::max<int64_t>(1, std::min<int64_t>(256, cdiv(c.n, 2048)));
+            c.o_gpart = lay.add((size_t)c.T * (c.T + 1) / 2 * 256 * 4 * c.gslots);
+        }
         c.o_G = lay.add((size_t)c.p * c.p * 8);
     }
     if (parts & P_SMALL) {
@@ -274,6 +281,7 @@ void plan_cube(CubePlan& c, Layout& lay, int parts) {
         c.o_Z = lay.add((size_t)c.r * c.nz * es);
         c.ncs = rup(c.nc, 64);
         c.o_coef = lay.add((size_t)c.r * c.ncs * es);
+        if (gpart_in_coef) c.o_gpart = c.o_coef;
         const int64_t a1 = c.L >= 1 ? rup((int64_t)c.lh[1] * c.lw[1], 64) : 0;
         const int64_t a2 = c.L >= 2 ? rup((int64_t)c.lh[2] * c.lw[2], 64) : 0;
         c.tmp_off2 = a1;

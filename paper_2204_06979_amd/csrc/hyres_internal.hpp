@@ -207,6 +207,8 @@ struct AdjDesc {
     int slots, nchunk;
     int* status;
 };
+int gram_f64_slots(int T, int64_t n);
+size_t gram_f64_bytes(int T, int slots);
 hipError_t launch_adj_sweep(const AdjDesc& a, hipStream_t s);
 hipError_t launch_planes_cube(int dtype, const AdjDesc& a, const void* planes, const void* cube, int64_t cp,
                               int64_t crp, double* out, hipStream_t s);
@@ -223,6 +225,12 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ v4f mfma4(float a, float b, v4f c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+// FP64: element v of lane l of the result holds row l / 16 + 4 v, column l mod 16
+typedef double v4d __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ v4d mfma4d(double a, double b, v4d c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
 // index of the cube owning flattened work item `item` (offsets[0..ncubes])

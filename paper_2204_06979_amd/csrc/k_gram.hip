@@ -638,48 +638,6 @@ __global__ __launch_bounds__(256) void k_gram_reduce_f32(const CubeDesc* __restr
     }
 }
 
-// FP64 Gram: grid.x covers upper-triangle entries, grid.y the slots of one cube.
-__global__ void k_gram_f64(const CubeDesc* __restrict__ descs, int cube) {
-    const CubeDesc& d = descs[cube];
-    const int p = d.p;
-    const int ntri = p * (p + 1) / 2;
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    const int slot = blockIdx.y;
-    if (e >= ntri || slot >= d.gslots) return;
-    int a = 0, rem = e;
-    while (rem >= p - a) { rem -= p - a; ++a; }
-    const int b = a + rem;
-    const int64_t per = (d.n + d.gslots - 1) / d.gslots;
-    const int64_t q0 = (int64_t)slot * per;
-    const int64_t q1 = q0 + per < d.n ? q0 + per : d.n;
-    double s = 0.0;
-    int bad = 0;
-    for (int64_t q = q0; q < q1; ++q) {
-        const double* y = pixel_ptr<double>(d, q);
-        const double ya = y[a], yb = y[b];
-        if (a == b) bad |= !__builtin_isfinite(ya);
-        s = fma(ya, yb, s);
-    }
-    if (bad) set_status(d.status, HYRES_DEV_NONFINITE);
-    gmem(static_cast<double*>(d.gpart))[(int64_t)(d.gslot0 + slot) * ntri + e] = s;
-}
-
-__global__ void k_gram_reduce_f64(const CubeDesc* __restrict__ descs, int cube) {
-    const CubeDesc& d = descs[cube];
-    const int p = d.p;
-    const int ntri = p * (p + 1) / 2;
-    const int e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= ntri) return;
-    int a = 0, rem = e;
-    while (rem >= p - a) { rem -= p - a; ++a; }
-    const int b = a + rem;
-    const double* part = gmem(static_cast<const double*>(d.gpart)) + (int64_t)d.gslot0 * ntri + e;
-    double s = 0.0;
-    for (int sl = 0; sl < d.gslots; ++sl) s += part[(int64_t)sl * ntri];
-    d.G[(int64_t)a * p + b] = s;
-    d.G[(int64_t)b * p + a] = s;
-}
-
 // ---------------------------------------------------------------- launchers
 typedef void (*GramF32Kernel)(const CubeDesc*, const int*, int);
 
@@ -770,15 +728,6 @@ hipError_t launch_gram_reduce_f32(int T, const CubeDesc* descs, const int* cubes
     const int NT = T * (T + 1) / 2;
     dim3 grid((NT * 256 + 31) / 32, ncls);
     hipLaunchKernelGGL(k_gram_reduce_f32, grid, dim3(256), 0, s, descs, cubes, ncls);
-    return hipGetLastError();
-}
-
-hipError_t launch_gram_f64(const CubeDesc* descs, int cube, int p, int gslots, hipStream_t s) {
-    const int ntri = p * (p + 1) / 2;
-    hipLaunchKernelGGL(k_gram_f64, dim3((ntri + 255) / 256, gslots), dim3(256), 0, s, descs, cube);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_gram_reduce_f64, dim3((ntri + 255) / 256), dim3(256), 0, s, descs, cube);
     return hipGetLastError();
 }
 
