@@ -39,10 +39,9 @@ hipError_t launch_backproject_f64(const CubeDesc*, int, int64_t, hipStream_t);
 hipError_t launch_dwt_level1_rot(int tx, int ty, const CubeDesc*, const int*, int, int, int, hipStream_t);
 hipError_t launch_dwt_level(int dtype, int tx, int ty, bool inverse, const CubeDesc*, const int*, int, int,
                             int, hipStream_t);
-hipError_t launch_sure_init(int dtype, const CubeDesc*, const int*, int, int, hipStream_t);
-hipError_t launch_sure_round(int dtype, const CubeDesc*, const int*, int, int, hipStream_t);
-int sure_rounds(int dtype);
-int64_t sure_chunk_for(int64_t total_coef, int num_cu);
+hipError_t launch_sure(int dtype, int step, const CubeDesc*, const int*, int, int, hipStream_t);
+int sure_chunks(int64_t N, int64_t total, int num_cu, int64_t room);
+int64_t sure_chunk(int64_t N, int nch);
 hipError_t launch_ritz(const CubeDesc*, const int*, const int*, int, int, int, hipStream_t);
 hipError_t launch_adjoint_pre(const AdjDesc&, int dtype, hipStream_t);
 hipError_t launch_adjoint_thresh(const AdjDesc&, int dtype, hipStream_t);
@@ -211,9 +210,9 @@ struct CubePlan {
     int lh[kMaxLevels + 1] = {0}, lw[kMaxLevels + 1] = {0};
     int64_t loff[kMaxLevels + 1] = {0};
     size_t o_gpart = 0, o_G = 0, o_sigma = 0, o_hv = 0, o_V = 0, o_evals = 0, o_gap = 0, o_P32 = 0, o_Q32 = 0,
-           o_P64 = 0, o_Q64 = 0, o_Z = 0, o_coef = 0, o_tmp = 0, o_hcnt = 0, o_hsum = 0, o_hmin = 0,
-           o_hmax = 0, o_sst = 0, o_lambda = 0, o_sure = 0, o_sbits = 0, o_spre = 0, o_sspre = 0, o_sctr = 0,
-           o_cand = 0, o_rpart = 0, o_rsum = 0, o_rrot = 0;
+           o_P64 = 0, o_Q64 = 0, o_Z = 0, o_coef = 0, o_tmp = 0, o_shist = 0, o_slist = 0,
+           o_ssel = 0, o_sseg = 0, o_lambda = 0, o_sure = 0, o_rpart = 0, o_rsum = 0, o_rrot = 0;
+    int64_t shcs = 0, slcs = 0;   // SURE search: words of count rows, list values per component
     int rgroups = 0;
     bool has_lambda = false;   // thresholds given by the caller: no SURE search
 };
@@ -289,17 +288,24 @@ void plan_cube(CubePlan& c, Layout& lay, int parts) {
         c.o_tmp = lay.add((size_t)std::max<int64_t>(1, c.r * c.tps) * es);
     }
     if (parts & P_SURE) {
-        const size_t nb = (size_t)c.r * kSureBins;
-        c.o_hcnt = lay.add(nb * 4);
-        c.o_hsum = lay.add(nb * 8);
-        c.o_hmin = lay.add(nb * 8);
-        c.o_hmax = lay.add(nb * 8);
-        c.o_sst = lay.add((size_t)c.r * sizeof(SureState));
-        c.o_sbits = lay.add((size_t)c.r * (kSureBins / 32) * 4);
-        c.o_spre = lay.add(nb * 8);
-        c.o_sspre = lay.add(nb * 8);
-        c.o_sctr = lay.add((size_t)c.r * 16);
-        c.o_cand = lay.add((size_t)c.r * kSureCap * 8);
+        if (parts & P_IMG) {
+            // between the transforms the image planes and the approximation
+            // buffers hold nothing: the list and the count rows of the search
+            c.o_slist = c.o_Z;
+            c.slcs = c.nz;
+            c.o_shist = c.o_tmp;
+            c.shcs = c.tps * es / 4;
+        } else {
+            const int nch = sure_chunks(c.nc, (int64_t)c.r * c.nc, 256, kSureMaxChunks);
+            if (nch > 1) {
+                c.shcs = (int64_t)nch * kSureBins;
+                c.slcs = c.nc / 4 + nch;
+            }
+            c.o_shist = lay.add(std::max<size_t>((size_t)c.r * c.shcs * 4, 16));
+            c.o_slist = lay.add(std::max<size_t>((size_t)c.r * c.slcs * es, 16));
+        }
+        c.o_ssel = lay.add((size_t)c.r * sizeof(SureSel));
+        c.o_sseg = lay.add((size_t)c.r * kSureMaxChunks * sizeof(SureSeg));
         c.o_lambda = lay.add((size_t)c.r * 8);
         c.o_sure = lay.add((size_t)c.r * 8);
     }
@@ -356,17 +362,13 @@ CubeDesc make_desc(const CubePlan& c, void* ws) {
         d.coef = at<void>(ws, c.o_coef);
         d.tmp = at<void>(ws, c.o_tmp);
     }
-    if (c.o_hcnt) {
-        d.hcnt = at<uint32_t>(ws, c.o_hcnt);
-        d.hsum = at<double>(ws, c.o_hsum);
-        d.hmin = at<uint64_t>(ws, c.o_hmin);
-        d.hmax = at<uint64_t>(ws, c.o_hmax);
-        d.sst = at<SureState>(ws, c.o_sst);
-        d.sbits = at<uint32_t>(ws, c.o_sbits);
-        d.spre = at<uint64_t>(ws, c.o_spre);
-        d.sspre = at<double>(ws, c.o_sspre);
-        d.sctr = at<uint32_t>(ws, c.o_sctr);
-        d.cand = at<uint64_t>(ws, c.o_cand);
+    if (c.o_sseg) {
+        d.shist = at<uint32_t>(ws, c.o_shist);
+        d.shcs = c.shcs;
+        d.slist = at<void>(ws, c.o_slist);
+        d.slcs = c.slcs;
+        d.ssel = at<SureSel>(ws, c.o_ssel);
+        d.sseg = at<SureSeg>(ws, c.o_sseg);
         d.lambda = at<double>(ws, c.o_lambda);
         d.sure = at<double>(ws, c.o_sure);
     }
@@ -392,7 +394,7 @@ enum { S_GRAM = 1, S_SMALL = 2, S_PROJ = 4, S_DWT = 8, S_SURE = 16, S_IDWT = 32,
 
 enum Kind {
     K_GRAM_F32, K_GRAM_BF16, K_GRAM_RED, K_GRAM_F64, K_SMALL, K_PROJ_F32, K_PROJ_F64, K_DWT, K_IDWT,
-    K_SURE_INIT, K_SURE_ROUND, K_COPY, K_BP_F32, K_BP_F64, K_RITZ, K_BLEND_F32
+    K_SURE, K_COPY, K_BP_F32, K_BP_F64, K_RITZ, K_BLEND_F32
 };
 
 struct Launch {
@@ -660,41 +662,36 @@ void build_group(Exec& x, int stages, int grp) {
     if (stages & S_DWT) add_dwt(x, false, grp, x.precision == HYRES_PREC_MIXED && !f64 && (stages & S_PROJ));
     if (stages & S_SURE) {
         std::vector<int64_t> comp(N, 0), hist(N, 0);
-        // one work-item size for the whole program: about one item per compute unit
         int64_t total_coef = 0;
+        auto values = [](const CubePlan& c) { return c.scope == HYRES_SCOPE_DETAIL ? c.ll_off : c.nc; };
         for (int i = 0; i < N; ++i) {
             const CubePlan& c = x.plan[i];
-            if (in_group(x, i, grp) && !c.has_lambda) total_coef += (int64_t)c.r * (c.scope == HYRES_SCOPE_DETAIL ? c.ll_off : c.nc);
+            if (in_group(x, i, grp) && !c.has_lambda) total_coef += c.r * values(c);
         }
-        const int64_t ch = sure_chunk_for(total_coef, x.h ? x.h->num_cu : 256);
         for (int i = 0; i < N; ++i) {
             const CubePlan& c = x.plan[i];
             if (!in_group(x, i, grp) || c.has_lambda) continue;
-            const int64_t ns = c.scope == HYRES_SCOPE_DETAIL ? c.ll_off : c.nc;
+            CubeDesc& d = x.desc[i];
+            const int64_t ns = values(c);
+            d.snch = sure_chunks(ns, total_coef, x.h ? x.h->num_cu : 256, c.shcs / kSureBins);
+            d.schunk = sure_chunk(ns, d.snch);
+            d.snch = (int)cdiv(ns, d.schunk);
+            d.segcap = c.slcs / d.snch;
             comp[i] = c.r;
-            x.desc[i].schunk = ch;
-            hist[i] = c.r * cdiv(ns, ch);
+            hist[i] = d.snch > 1 ? (int64_t)c.r * d.snch : 0;
         }
         int64_t ncomp, nh;
         const int tc = x.counts(comp, &ncomp);
         const int th = x.counts(hist, &nh);
-        if (ncomp > 0) {
-            Launch I{};
-            I.kind = K_SURE_INIT;
-            I.stage = HYRES_STAGE_SURE;
-            I.a = tc;
-            I.n = N;
-            I.grid = (int)ncomp;
-            x.prog.push_back(I);
-            for (int k = 0; k < sure_rounds(x.dtype); ++k) {
-                Launch R{};
-                R.kind = K_SURE_ROUND;
-                R.stage = HYRES_STAGE_SURE;
-                R.a = th;
-                R.n = N;
-                R.grid = x.grid(nh, 1);
-                x.prog.push_back(R);
-            }
+        for (int step = nh > 0 ? 0 : 2; step < 3 && ncomp > 0; ++step) {
+            Launch R{};
+            R.kind = K_SURE;
+            R.stage = HYRES_STAGE_SURE;
+            R.key = step;
+            R.a = step < 2 ? th : tc;
+            R.n = N;
+            R.grid = (int)(step < 2 ? nh : ncomp);
+            x.prog.push_back(R);
         }
         for (int i = 0; i < N; ++i) {
             if (!in_group(x, i, grp) || !x.plan[i].has_lambda) continue;
@@ -769,9 +766,7 @@ hipError_t launch_one(const Exec& x, const Launch& L, hipStream_t s) {
         case K_IDWT:
             return launch_dwt_level(x.dtype, kTileTX[L.key], kTileTY[L.key], L.kind == K_IDWT, D, x.table(L.a),
                                     L.n, L.level, L.grid, s);
-        case K_SURE_INIT: return launch_sure_init(x.dtype, D, x.table(L.a), L.n, L.grid, s);
-        case K_SURE_ROUND:
-            return launch_sure_round(x.dtype, D, x.table(L.a), L.n, L.grid, s);
+        case K_SURE: return launch_sure(x.dtype, L.key, D, x.table(L.a), L.n, L.grid, s);
         case K_COPY:
             hipLaunchKernelGGL(k_copy_f64, dim3(1), dim3(64), 0, s, L.src, L.dst, L.n);
             return hipGetLastError();

@@ -12,9 +12,10 @@ namespace hyres {
 constexpr int kMaxLevels = 8;
 constexpr int kMaxRank = 16;
 constexpr int kMaxBands = 224;        // FP64 small solver keeps a 224 x 224 matrix in registers
-constexpr int kSureBins = 4096;       // histogram bins per refinement round
-constexpr int kSureRoundsF32 = 5;     // 31-bit keys, >= 12 bits resolved per round when narrow
-constexpr int kSureRoundsF64 = 10;    // 63-bit keys
+constexpr int kSureBins = 4096;       // bins of a threshold-search histogram
+constexpr int kSureMaxChunks = 64;    // chunks per component of the threshold search
+constexpr int64_t kSureDirect = 65536;   // components of up to this many values: one block
+constexpr int64_t kSureRow16 = 65535;    // chunk size up to which its bin counts are stored in 16 bits
 constexpr int kGramThreads = 512;
 constexpr int kSmallThreads = 1024;
 constexpr int kPixTile = 64;          // pixels per projection / back-projection block
@@ -27,24 +28,17 @@ constexpr double kH1 = 0.83651630373780794;
 constexpr double kH2 = 0.22414386804201339;
 constexpr double kH3 = -0.12940952255126037;
 
-// Per-component state of the SURE refinement search.
-struct SureState {
-    uint64_t klo, khi, width;   // current key range [klo, khi) and bin width
-    uint64_t below_cnt;         // number of magnitudes with key < klo
-    double below_sum;           // sum of their squares
-    double best_s;              // smallest SURE value seen at an exact candidate
-    double best_t;              // the candidate attaining it
-    uint64_t pad0;
-    int round;
-    int done;
-    int inexact;
-    int gather;                 // 1: the next pass collects the values of the surviving bins
-    unsigned int nsurv;         // number of values in the surviving bins
-    unsigned int pad;
+// SURE threshold search: the key range [klo, khi) that survives the first
+// histogram, the values below it (exact zeros included) and the exact zeros.
+struct SureSel {
+    uint64_t klo, khi, c0;
+    uint32_t zeros, pad;
 };
-
-constexpr int kSureCap = 8192;        // values finished exactly in one block
-constexpr int kSureBinCap = 1024;     // largest surviving bin the exact finish accepts
+// ... and per chunk: squares of its values below the range, its values inside.
+struct SureSeg {
+    double s0;
+    uint32_t count, pad;
+};
 
 // CubeDesc::mode bits
 constexpr int kModeSigma = 1;      // estimate the noise
@@ -88,14 +82,13 @@ struct CubeDesc {
     void* Z;                                // r x nz component images (also the denoised ones)
     void* coef;                             // r x ncs coefficients
     void* tmp;                              // r x tps approximation buffers
-    uint32_t* hcnt; double* hsum; uint64_t* hmin; uint64_t* hmax;  // r x kSureBins
-    SureState* sst;                         // r
-    uint32_t* sbits;                        // r x kSureBins/32 surviving-bin bitmap
-    uint64_t* spre;                         // r x kSureBins: values below each bin (gather round)
-    double* sspre;                          // r x kSureBins: their sum of squares
-    uint32_t* sctr;                         // r x 4: blocks done in the pass, values gathered, zeros (u64)
-    int64_t schunk;                         // coefficients per SURE work item (a multiple of 1024)
-    uint64_t* cand;                         // r x kSureCap collected magnitudes (keys)
+    // SURE search: rows of bin counts per chunk (component stride shcs words),
+    // segments of surviving values (component stride slcs, segcap each), results
+    uint32_t* shist; int64_t shcs;
+    void* slist; int64_t slcs, segcap;
+    SureSel* ssel;                          // r
+    SureSeg* sseg;                          // r x kSureMaxChunks
+    int64_t schunk; int snch;               // coefficients per chunk, chunks (1: no list)
     double* lambda; double* sure;           // r
     const double* lambda_in;                // optional caller thresholds
     // sliding-window blend in the back-projection (bwy null: plain write).  A

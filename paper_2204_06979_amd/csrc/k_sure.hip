@@ -1,4 +1,4 @@
-// Exact SURE threshold by histogram refinement.
+// Exact SURE threshold by histogram search.
 //
 // For coefficients b_1..b_N of one component the risk estimate of soft
 // thresholding at unit noise is SURE(t) = N - 2 #{|b| <= t} + sum min(b^2, t^2).
@@ -6,129 +6,106 @@
 // minimum is attained on the candidate set.
 //
 // The magnitude |b| is keyed by its IEEE bit pattern (monotone for
-// non-negative numbers).  Each pass histograms the keys inside the current
-// range [klo, khi) into 4096 bins of width 2^shift, recording per bin the
-// count, the sum of squares and the smallest and largest key.  The select
-// step then knows exactly, for every bin:
-//   C = #values below the bin, S = their sum of squares;
-//   SURE at the largest value of the bin, t_max (an exact candidate):
-//     N - 2(C + c) + S + s + (N - C - c) t_max^2;
-//   a lower bound over every candidate t in the bin:
-//     N - 2(C + c) + S + (N - C) t_min^2.
-// Bins whose lower bound exceeds the best exact value seen are discarded.
-// When the surviving bins hold at most kSureCap values, the next pass
-// collects exactly those values and the finish sorts them and evaluates SURE
-// at every one of them: the count and sum of squares of the values not above
-// it are the totals below its bin plus those of its own bin up to it.
-// Otherwise the next pass refines the key range spanned by the surviving bins
-// (bins of width 1 are exact too).  The smallest minimising candidate is
-// returned.
+// non-negative numbers); exact zeros are only counted.  A bin of keys [lo, hi)
+// that holds c of the values, with C values below it whose squares sum to S, has
+//   N - 2 (C + c) + S + (N - C) lo^2                    (L)
+// as a lower bound of SURE over the candidates in it, and with s the sum of
+// squares inside, t the largest number below hi,
+//   N - 2 (C + c) + S + s + (N - C - c) t^2             (U)
+// as an upper bound of the minimum.  A bin whose L exceeds a known U is out.
 //
-// One kernel per pass: blocks of 1024 threads take 16384 coefficients of one
-// component each and merge their histogram into the component's bins; the
-// last block of the component to finish (a counter, with device-scope fences
-// around it) then runs the select, or the finish after a gather pass.
+// 1. k_sure_hist (components of more than kSureDirect values): counts per bin
+//    of each chunk, one LDS atomic per value, into a row of its own.
+// 2. k_sure_gather: every block adds its component's rows, finds the range of
+//    the surviving bins, and copies its chunk's values in that range into its
+//    segment of a list, with the sum of squares of those below.
+// 3. k_sure_finish, one block per component: histograms of counts and sums of
+//    squares over the list, each over the range that survived, until the
+//    surviving bins are small; their values, grouped by bin in LDS, are then
+//    evaluated one by one.  Smaller components do step 1 here, over the
+//    coefficients themselves.
+//
+// The first histogram has 512 bins per octave of [1/16, 8), where thresholds
+// of unit-noise coefficients lie: 16 per octave (one key range for all numbers)
+// put most values of a block into some fifty bins, whose LDS atomics queued,
+// and left most of the values to a second full histogram.  Its sums are not
+// needed: the squares of a bin lie between those of its edges, and a bin is
+// compared with the best one through the bins between the two.
+//
+// Bound by latency and LDS atomics: the three passes over the 21 MB of 349 x 1905
+// and 8 components take 13, 22 and 40 us, against 145 us for six passes with a
+// select in the last block of each; ten components of 145 x 217, one launch,
+// 44 us against 594; four FP64 ones of 64 x 64 25 us against 158.
 #include "hyres_internal.hpp"
 
 namespace hyres {
 
+constexpr int kSureThreads = 1024;
+constexpr int kSureWaves = kSureThreads / 64;
+constexpr int kBinsPer = kSureBins / kSureThreads;    // bins per thread in the selects
+constexpr int kSureLoads = 16;       // values a thread reads at once
+constexpr int kZeroSlot = kSureBins - 1;              // first histogram: exact zeros
+constexpr int kSureLight = 64;      // largest bin evaluated without narrowing the range first
+constexpr int kSureHeavy = 256;     // a larger bin is searched as a range of its own
+constexpr int kSureStack = 256;     // ranges waiting (at most 128 heavy bins of one range)
+
+// Keys, and the bins of the first histogram: `lo_shift`-wide bins below 1/16
+// and from 8 on, 512 bins per octave between.  Word: the part of the key the
+// bins are formed from (its high word for FP64).
 template <typename T> struct KeyTraits;
 template <> struct KeyTraits<float> {
     typedef uint32_t K;
-    static constexpr uint64_t kEnd = 0x80000000ull;
-    static constexpr int kRounds = kSureRoundsF32;
+    static constexpr int kCap = 16384;       // values evaluated at once (LDS)
+    static constexpr int kWordShift = 0;
+    static constexpr uint32_t kC0 = 0x3D800000u, kC1 = 0x41000000u;
+    static constexpr int kMid = 14;          // bits below 512 bins per octave
+    static constexpr int kLow = 246, kHigh = kLow + 3584;
     __device__ static K key(float v) { return __float_as_uint(v) & 0x7fffffffu; }
     __device__ static double val(uint64_t k) { return (double)__uint_as_float((uint32_t)k); }
 };
 template <> struct KeyTraits<double> {
     typedef unsigned long long K;
-    static constexpr uint64_t kEnd = 0x8000000000000000ull;
-    static constexpr int kRounds = kSureRoundsF64;
+    static constexpr int kCap = 8192;
+    static constexpr int kWordShift = 32;
+    static constexpr uint32_t kC0 = 0x3FB00000u, kC1 = 0x40200000u;
+    static constexpr int kMid = 11;
+    static constexpr int kLow = 255, kHigh = kLow + 3584;
     __device__ static K key(double v) {
         return (unsigned long long)__double_as_longlong(v) & 0x7fffffffffffffffull;
     }
     __device__ static double val(uint64_t k) { return __longlong_as_double((long long)k); }
 };
+constexpr int kSureOuter = 22;               // bits of an outer bin
+template <typename T>
+__device__ __forceinline__ int first_bin(typename KeyTraits<T>::K k) {
+    typedef KeyTraits<T> KT;
+    const uint32_t w = (uint32_t)((uint64_t)k >> KT::kWordShift);
+    if (w < KT::kC0) return (int)(w >> kSureOuter);
+    if (w < KT::kC1) return KT::kLow + (int)((w - KT::kC0) >> KT::kMid);
+    return KT::kHigh + (int)((w - KT::kC1) >> kSureOuter);
+}
+// Smallest key of bin b (the end of the keys beyond the last bin).
+template <typename T>
+__device__ __forceinline__ uint64_t first_edge(int b) {
+    typedef KeyTraits<T> KT;
+    uint64_t w;
+    if (b < KT::kLow) w = (uint64_t)b << kSureOuter;
+    else if (b < KT::kHigh) w = KT::kC0 + ((uint64_t)(b - KT::kLow) << KT::kMid);
+    else w = KT::kC1 + ((uint64_t)(b - KT::kHigh) << kSureOuter);
+    if (w > 0x80000000ull) w = 0x80000000ull;
+    if (b < KT::kLow && w > KT::kC0) w = KT::kC0;
+    return w << KT::kWordShift;
+}
 
-constexpr int kSureThreads = 1024;                    // threads of a pass block
-constexpr int kSureWaves = kSureThreads / 64;
-constexpr int kSureChunk = 16 * kSureThreads;         // smallest work item (coefficients)
-constexpr int kGatherPer = 16;                        // gathered coefficients per thread and step
-constexpr int kBinsPer = kSureBins / kSureThreads;    // bins per thread in the select
-constexpr int kSureGroup = 4;   // chunks per block after the first pass (fewer partial merges)
-constexpr int64_t kSureGroupSpan = 65536;   // ... while a block's range stays within this many values
-
-__host__ __device__ inline int sure_shift_for(uint64_t span) {
-    int s = 0;
-    while (((span + ((1ull << s) - 1)) >> s) > (uint64_t)kSureBins) ++s;
-    return s;
+// Smallest shift that leaves at most kSureBins bins of a span > 0.
+__device__ __forceinline__ int shift_for(uint64_t span) {
+    static_assert(kSureBins == 1 << 12, "12 bits of bins");
+    const int len = span > 1 ? 64 - __clzll((long long)(span - 1)) : 0;
+    return len > 12 ? len - 12 : 0;
 }
 
 __device__ __forceinline__ int64_t sure_count(const CubeDesc& d) {
     return d.scope == HYRES_SCOPE_DETAIL ? d.ll_off : d.nc;
-}
-
-// counters of component comp: [0] blocks done in this pass, [1] values gathered, [2..3] exact zeros
-__device__ __forceinline__ unsigned long long* sure_zeros(const CubeDesc& d, int comp) {
-    return reinterpret_cast<unsigned long long*>(d.sctr + 4 * comp + 2);
-}
-
-// Field-by-field store of a search state (a struct copy from LDS to global
-// memory would go through a private temporary, which the compiler places in
-// LDS indexed by the flat thread id, read from the dispatch packet).
-__device__ __forceinline__ void put_state(SureState* dst, const SureState& s) {
-    dst->klo = s.klo;
-    dst->khi = s.khi;
-    dst->width = s.width;
-    dst->below_cnt = s.below_cnt;
-    dst->below_sum = s.below_sum;
-    dst->best_s = s.best_s;
-    dst->best_t = s.best_t;
-    dst->pad0 = s.pad0;
-    dst->round = s.round;
-    dst->done = s.done;
-    dst->inexact = s.inexact;
-    dst->gather = s.gather;
-    dst->nsurv = s.nsurv;
-    dst->pad = s.pad;
-}
-
-// Reset the search state, the counters and the global bins of every component.
-template <typename T>
-__global__ void k_sure_init(const CubeDesc* __restrict__ descs, const int* __restrict__ items, int ncubes) {
-    typedef KeyTraits<T> KT;
-    const int total = items[ncubes];
-    for (int item = blockIdx.x; item < total; item += gridDim.x) {
-        const int c = find_cube(items, ncubes, item);
-        const CubeDesc& d = descs[c];
-        const int comp = item - items[c];
-        const int64_t base = (int64_t)comp * kSureBins;
-        for (int b = threadIdx.x; b < kSureBins; b += blockDim.x) {
-            gmem(d.hcnt)[base + b] = 0;
-            gmem(d.hsum)[base + b] = 0.0;
-            gmem(d.hmin)[base + b] = ~0ull;
-            gmem(d.hmax)[base + b] = 0;
-        }
-        if (threadIdx.x < 4) gmem(d.sctr)[4 * comp + threadIdx.x] = 0u;
-        if (threadIdx.x == 0) {
-            SureState st;
-            st.klo = 0;
-            st.khi = KT::kEnd;
-            st.width = sure_shift_for(KT::kEnd);
-            st.below_cnt = 0;
-            st.below_sum = 0.0;
-            st.best_s = __builtin_inf();
-            st.best_t = 0.0;
-            st.pad0 = 0;
-            st.round = 0;
-            st.done = 0;
-            st.inexact = 0;
-            st.gather = 0;
-            st.nsurv = 0;
-            st.pad = 0;
-            d.sst[comp] = st;
-        }
-    }
 }
 
 // ---- wave primitives (whole wave active) ----
@@ -199,541 +176,719 @@ __device__ __forceinline__ int wave_minmax_i32(int v) {
     return r;
 }
 
-// LDS of a pass block: the histogram of its chunk, or the keys of the finish.
-template <typename T> struct SureLds {
-    typedef typename KeyTraits<T>::K K;
-    static constexpr size_t kHist = (size_t)kSureBins * (4 + 8 + 2 * sizeof(K));
-    static constexpr size_t kFinish = (size_t)kSureBins * 8 + 16 + (size_t)kSureCap * 8;
-    static constexpr size_t kBytes = kHist > kFinish ? kHist : kFinish;
-};
 
 // Small per-block state.
 struct SureShared {
-    SureState st;
-    uint32_t wc[kSureWaves], wm[kSureWaves];
-    double ws[kSureWaves], bs[kSureWaves], bt[kSureWaves];
+    uint32_t wc[kSureWaves], wn[kSureWaves];
+    double ws[kSureWaves], wt[kSureWaves], bs[kSureWaves], bt[kSureWaves];
     int wf[kSureWaves], wl[kSureWaves], wx[kSureWaves];
-    uint32_t bits[kSureBins / 32];
-    unsigned long long zeros;
-    uint32_t base;
-    int last;
+    uint32_t zeros, count;
+    double ref[4];                 // first select: the reference bin
+    uint64_t c0;
+    int first, last;
 };
 
-// Histogram of the coefficients e0..e1-1 inside [klo, khi), merged into the
-// component's bins.
+// Combining one value per wave (in LDS, kSureWaves = 16 of them) in a DPP row:
+// every wave does it for itself, one LDS read and four steps.
+static_assert(kSureWaves == 16, "one DPP row");
+// sum of the waves before this one; the sum of all in *total
+__device__ __forceinline__ uint32_t waves_before(const uint32_t* w, int wave, uint32_t* total) {
+    uint32_t v = w[threadIdx.x & 15];
+    v += dpp_u32<0x111>(v);
+    v += dpp_u32<0x112>(v);
+    v += dpp_u32<0x114>(v);
+    v += dpp_u32<0x118>(v);
+    *total = readlane_u32(v, 15);
+    return wave ? readlane_u32(v, wave - 1) : 0u;
+}
+__device__ __forceinline__ double waves_before(const double* w, int wave, double* total) {
+    double v = w[threadIdx.x & 15];
+    v += dpp_shift_f64<0x111>(v);
+    v += dpp_shift_f64<0x112>(v);
+    v += dpp_shift_f64<0x114>(v);
+    v += dpp_shift_f64<0x118>(v);
+    *total = readlane_f64(v, 15);
+    return wave ? readlane_f64(v, wave - 1) : 0.0;
+}
+template <bool MAX>
+__device__ __forceinline__ int waves_minmax(const int* w) {
+    return wave_minmax_i32<MAX>(w[threadIdx.x & 15]);
+}
+
+// First histogram of values e0..e1-1 into lc (kSureBins counts, zeroed by the
+// caller).  Each thread keeps its zeros; returns them.
 template <typename T>
-__device__ void sure_hist_range(const CubeDesc& d, int comp, int64_t e0, int64_t e1, const SureState& st,
-                                unsigned char* lds, SureShared& sh) {
+__device__ __forceinline__ uint32_t first_histogram(const HYRES_GLOBAL T* cf, int64_t e0, int64_t e1, uint32_t* lc) {
     typedef KeyTraits<T> KT;
-    typedef typename KT::K K;
-    uint32_t* lc = reinterpret_cast<uint32_t*>(lds);
-    double* ls = reinterpret_cast<double*>(lds + kSureBins * 4);
-    K* lmin = reinterpret_cast<K*>(lds + kSureBins * 12);
-    K* lmax = lmin + kSureBins;
-    const int tid = threadIdx.x;
-    for (int b = tid; b < kSureBins; b += kSureThreads) {
-        lc[b] = 0;
-        ls[b] = 0.0;
-        lmin[b] = (K)~0ull;
-        lmax[b] = 0;
-    }
-    if (tid == 0) sh.zeros = 0;
-    __syncthreads();
-    const T* cf = gmem(static_cast<const T*>(d.coef)) + (int64_t)comp * d.ncs;
-    const uint64_t klo = st.klo, khi = st.khi;
-    const int shf = (int)st.width;
-    unsigned long long nz = 0;
-    constexpr int U = 8;
-    for (int64_t e = e0 + tid; e < e1; e += U * kSureThreads) {
+    constexpr int U = kSureLoads;
+    uint32_t nz = 0;
+    for (int64_t e = e0 + threadIdx.x; e < e1; e += U * kSureThreads) {
         T v[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int64_t idx = e + (int64_t)u * kSureThreads;
-            v[u] = idx < e1 ? cf[idx] : (T)0;
+            const int64_t i = e + (int64_t)u * kSureThreads;
+            v[u] = i < e1 ? cf[i] : (T)0;
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            if (e + (int64_t)u * kSureThreads < e1) {
-                const K k = KT::key(v[u]);
-                if (st.round == 0 && k == 0) ++nz;
-                if ((uint64_t)k >= klo && (uint64_t)k < khi) {
-                    const int b = (int)(((uint64_t)k - klo) >> shf);
-                    atomicAdd(&lc[b], 1u);
-                    atomicAdd(&ls[b], (double)v[u] * (double)v[u]);
-                    atomicMin(&lmin[b], k);
-                    atomicMax(&lmax[b], k);
-                }
-            }
+            const auto k = KT::key(v[u]);
+            if (k != 0) atomicAdd(&lc[first_bin<T>(k)], 1u);
+            else if (e + (int64_t)u * kSureThreads < e1) ++nz;
         }
     }
-    if (nz) atomicAdd(&sh.zeros, nz);
-    __syncthreads();
-    const int64_t base = (int64_t)comp * kSureBins;
-    for (int b = tid; b < kSureBins; b += kSureThreads) {
-        if (lc[b]) {
-            atomicAdd(&gmem(d.hcnt)[base + b], lc[b]);
-            atomicAdd(&gmem(d.hsum)[base + b], ls[b]);
-            atomicMin(&gmem(d.hmin)[base + b], (unsigned long long)lmin[b]);
-            atomicMax(&gmem(d.hmax)[base + b], (unsigned long long)lmax[b]);
-        }
-    }
-    if (tid == 0 && sh.zeros) atomicAdd(sure_zeros(d, comp), sh.zeros);
+    return nz;
 }
 
-// The magnitudes among e0..e1-1 (at most kGatherPer per thread) that fall in surviving
-// bins (bitmap in sh.bits), appended to the component's list: one reservation
-// per block, then plain stores.
+// Select on the first histogram: c[j] holds bin 4 tid + j (the zero slot's
+// count in `zeros`).  Returns the first and last surviving bin (-1: none) and the
+// number of values below the first.  Sums of squares are known to the edges of
+// the bins only: relative to a reference bin J with upper bound U, L - U needs
+// the sum over the bins between, bounded by their edges.
 template <typename T>
-__device__ void sure_gather_chunk(const CubeDesc& d, int comp, int64_t e0, int64_t e1, const SureState& st,
-                                  SureShared& sh) {
+__device__ __forceinline__ void first_select(const uint32_t (&c)[kBinsPer], uint32_t zeros, double N, SureShared& sh,
+                                             int* first, int* last, uint64_t* c0) {
     typedef KeyTraits<T> KT;
-    typedef typename KT::K K;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const T* cf = gmem(static_cast<const T*>(d.coef)) + (int64_t)comp * d.ncs;
-    const uint64_t klo = st.klo, khi = st.khi;
-    const int shf = (int)st.width;
-    K kv[kGatherPer];
-    uint32_t m = 0;
+    double a[kBinsPer], b[kBinsPer];
+    uint32_t tc = 0;
+    double tl = 0.0, th = 0.0;
 #pragma unroll
-    for (int j = 0; j < kGatherPer; ++j) {
-        const int64_t e = e0 + tid + (int64_t)j * kSureThreads;
-        kv[j] = 0;
-        if (e < e1) {
-            const K k = KT::key(cf[e]);
-            if ((uint64_t)k >= klo && (uint64_t)k < khi) {
-                const int b = (int)(((uint64_t)k - klo) >> shf);
-                if ((sh.bits[b >> 5] >> (b & 31)) & 1u) {
-                    kv[j] = k;
-                    m |= 1u << j;
-                }
-            }
-        }
-    }
-    const uint32_t cnt = (uint32_t)__builtin_popcount(m);
-    const uint32_t inc = wave_incl_u32(cnt);
-    if (lane == 63) sh.wc[wave] = inc;
-    __syncthreads();
-    uint32_t off = inc - cnt, tot = 0;
-    for (int w = 0; w < kSureWaves; ++w) {
-        if (w < wave) off += sh.wc[w];
-        tot += sh.wc[w];
-    }
-    if (tid == 0) sh.base = tot ? atomicAdd(&gmem(d.sctr)[4 * comp + 1], tot) : 0u;
-    __syncthreads();
-    uint64_t* out = gmem(d.cand) + (int64_t)comp * kSureCap;
-    uint32_t pos = sh.base + off;
-#pragma unroll
-    for (int j = 0; j < kGatherPer; ++j) {
-        if ((m >> j) & 1u) {
-            if (pos < (uint32_t)kSureCap) out[pos] = (uint64_t)kv[j];
-            ++pos;
-        }
-    }
-}
-
-// Exact finish from the gathered values: grouped by bin (counting sort in
-// LDS), then SURE at each value: the count and sum of squares of its bin's
-// values not above it, added to the totals below the bin.
-template <typename T>
-__device__ void sure_finish(const CubeDesc& d, int comp, double N, unsigned char* lds, SureShared& sh) {
-    typedef KeyTraits<T> KT;
-    uint32_t* bcnt = reinterpret_cast<uint32_t*>(lds);              // kSureBins
-    uint32_t* boff = bcnt + kSureBins;                               // kSureBins + 1
-    uint64_t* keys = reinterpret_cast<uint64_t*>(lds + (size_t)kSureBins * 8 + 16);   // kSureCap
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const SureState st = sh.st;
-    // the gather re-reads the values the last histogram counted, so the
-    // surviving bins hold exactly nsurv (<= kSureCap) values
-    const uint32_t got = gmem(d.sctr)[4 * comp + 1];
-    const int nc = (int)(got < (uint32_t)kSureCap ? got : (uint32_t)kSureCap);
-    const uint64_t klo = st.klo;
-    const int shf = (int)st.width;
-    const uint64_t* src = gmem(d.cand) + (int64_t)comp * kSureCap;
-    for (int b = tid; b < kSureBins; b += kSureThreads) bcnt[b] = 0u;
-    __syncthreads();
-    for (int i = tid; i < nc; i += kSureThreads) atomicAdd(&bcnt[(int)((src[i] - klo) >> shf)], 1u);
-    __syncthreads();
-    // segment offsets: exclusive prefix of the bin counts
-    {
-        uint32_t c[kBinsPer], tc = 0;
-#pragma unroll
-        for (int j = 0; j < kBinsPer; ++j) {
-            c[j] = bcnt[tid * kBinsPer + j];
+    for (int j = 0; j < kBinsPer; ++j) {
+        const int bin = kBinsPer * tid + j;
+        const double lo = KT::val(first_edge<T>(bin)), hi = KT::val(first_edge<T>(bin + 1) - 1);
+        a[j] = lo * lo;
+        b[j] = hi * hi;
+        if (c[j]) {
             tc += c[j];
-        }
-        const uint32_t inc = wave_incl_u32(tc);
-        if (lane == 63) sh.wc[wave] = inc;
-        __syncthreads();
-        uint32_t o = inc - tc;
-        for (int w = 0; w < wave; ++w) o += sh.wc[w];
-#pragma unroll
-        for (int j = 0; j < kBinsPer; ++j) {
-            boff[tid * kBinsPer + j] = o;
-            bcnt[tid * kBinsPer + j] = 0u;
-            o += c[j];
-        }
-        if (tid == kSureThreads - 1) boff[kSureBins] = o;
-    }
-    __syncthreads();
-    for (int i = tid; i < nc; i += kSureThreads) {
-        const uint64_t key = src[i];
-        const int b = (int)((key - klo) >> shf);
-        keys[boff[b] + atomicAdd(&bcnt[b], 1u)] = key;
-    }
-    __syncthreads();
-    double bs = __builtin_inf(), bt = 0.0;
-    for (int i = tid; i < nc; i += kSureThreads) {
-        const uint64_t key = keys[i];
-        const int b = (int)((key - klo) >> shf);
-        const int s0 = (int)boff[b], s1 = (int)boff[b + 1];
-        double cw = 0.0, sw = 0.0;
-        int j = s0;
-        for (; j + 4 <= s1; j += 4) {             // four reads in flight, added in order
-            uint64_t kq[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) kq[u] = keys[j + u];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                if (kq[u] <= key) {
-                    const double vj = KT::val(kq[u]);
-                    cw += 1.0;
-                    sw = fma(vj, vj, sw);
-                }
-            }
-        }
-        for (; j < s1; ++j) {
-            const uint64_t kj = keys[j];
-            if (kj <= key) {
-                const double vj = KT::val(kj);
-                cw += 1.0;
-                sw = fma(vj, vj, sw);
-            }
-        }
-        const int64_t bi = (int64_t)comp * kSureBins + b;
-        const double c = (double)d.spre[bi] + cw;
-        const double S = d.sspre[bi] + sw;
-        const double v = KT::val(key);
-        const double sv = N - 2.0 * c + S + (N - c) * v * v;
-        if (sv < bs || (sv == bs && v < bt)) {
-            bs = sv;
-            bt = v;
+            tl = fma((double)c[j], a[j], tl);
+            th = fma((double)c[j], b[j], th);
         }
     }
-    wave_argmin(bs, bt);
-    if (lane == 0) {
-        sh.bs[wave] = bs;
-        sh.bt[wave] = bt;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        SureState ns = st;
-        double b_s = st.best_s, b_t = st.best_t;
-        for (int w = 0; w < kSureWaves; ++w) {
-            if (sh.bs[w] < b_s || (sh.bs[w] == b_s && sh.bt[w] < b_t)) {
-                b_s = sh.bs[w];
-                b_t = sh.bt[w];
-            }
-        }
-        ns.best_s = b_s;
-        ns.best_t = b_t;
-        ns.done = 1;
-        ns.round = st.round + 1;
-        if (got != st.nsurv) ns.inexact = 1;
-        d.lambda[comp] = b_t;
-        if (d.sure) d.sure[comp] = b_s;
-        if (ns.inexact) set_status(d.status, HYRES_DEV_SURE_INEXACT);
-        put_state(&d.sst[comp], ns);
-    }
-}
-
-// Select step of a component after its histogram pass: exact prefix sums,
-// bounds, survivors, then either the next range or a gather of the surviving
-// values.
-template <typename T>
-__device__ void sure_select(const CubeDesc& d, int comp, double N, SureShared& sh) {
-    typedef KeyTraits<T> KT;
-    constexpr int PER = kBinsPer;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t base = (int64_t)comp * kSureBins;
-    const SureState st = sh.st;
-    uint32_t cnt[PER];
-    double sum[PER];
-    uint64_t kmin[PER], kmax[PER];
-    uint32_t tc = 0;                  // counts stay below 2^32 (at most 2^31 pixels)
-    double ts = 0.0;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const int b = tid * PER + j;
-        cnt[j] = gmem(d.hcnt)[base + b];
-        sum[j] = gmem(d.hsum)[base + b];
-        kmin[j] = gmem(d.hmin)[base + b];
-        kmax[j] = gmem(d.hmax)[base + b];
-        tc += cnt[j];
-        ts += sum[j];
-    }
-    // exclusive prefix over threads of the counts and sums: waves by DPP and
-    // readlane, then the totals of the waves before (fixed order)
     const uint32_t ic = wave_incl_u32(tc);
-    const double is = wave_incl_f64(ts);
-    const double is_prev = __shfl_up(is, 1, 64);
+    const double il = wave_incl_f64(tl), ih = wave_incl_f64(th);
+    const double pl = __shfl_up(il, 1, 64), ph = __shfl_up(ih, 1, 64);
     if (lane == 63) {
         sh.wc[wave] = ic;
-        sh.ws[wave] = is;
+        sh.ws[wave] = il;
+        sh.wt[wave] = ih;
     }
-    for (int w = tid; w < kSureBins / 32; w += kSureThreads) sh.bits[w] = 0u;
     __syncthreads();
-    uint32_t oc = 0;
-    double os = 0.0;
-    for (int w = 0; w < wave; ++w) {
-        oc += sh.wc[w];
-        os += sh.ws[w];
-    }
-    unsigned long long pc = (unsigned long long)(oc + ic - tc);
-    double ps = lane == 0 ? os : os + is_prev;
-    double bs = __builtin_inf(), bt = 0.0;
-    if (st.round == 0 && tid == 0) {
-        bs = N - 2.0 * (double)*sure_zeros(d, comp);   // candidate t = 0
-        bt = 0.0;
-    }
-    double lbv[PER];
-    unsigned long long pcs[PER];
-    double pss[PER];
+    uint32_t all;
+    double allf;
+    const uint32_t oc = waves_before(sh.wc, wave, &all);
+    const double ol = waves_before(sh.ws, wave, &allf), oh = waves_before(sh.wt, wave, &allf);
+    // values below this thread's bins, and the bounds of their sum of squares
+    const double C0 = (double)zeros + (double)(oc + ic - tc);
+    const double L0 = lane ? ol + pl : ol, H0 = lane ? oh + ph : oh;
+    double best = __builtin_inf(), bj = 0.0;
+    {
+        double C = C0, Sl = L0, Sh = H0;
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        pcs[j] = pc;
-        pss[j] = ps;
-        lbv[j] = __builtin_inf();
-        if (cnt[j]) {
-            const double C = (double)(st.below_cnt + pc);
-            const double S = st.below_sum + ps;
-            const double cc = (double)cnt[j];
-            const double tmax = KT::val(kmax[j]), tmin = KT::val(kmin[j]);
-            const double smax = N - 2.0 * (C + cc) + (S + sum[j]) + (N - C - cc) * tmax * tmax;
-            lbv[j] = N - 2.0 * (C + cc) + S + (N - C) * tmin * tmin;
-            if (smax < bs || (smax == bs && tmax < bt)) {
-                bs = smax;
-                bt = tmax;
+        for (int j = 0; j < kBinsPer; ++j) {
+            if (!c[j]) continue;
+            C += c[j];
+            Sl = fma((double)c[j], a[j], Sl);
+            Sh = fma((double)c[j], b[j], Sh);
+            const double e = N - 2.0 * C + 0.5 * (Sl + Sh) + (N - C) * b[j];
+            if (e < best) {
+                best = e;
+                bj = (double)(kBinsPer * tid + j);
             }
         }
-        pc += cnt[j];
-        ps += sum[j];
     }
-    wave_argmin(bs, bt);
+    wave_argmin(best, bj);
     if (lane == 0) {
-        sh.bs[wave] = bs;
-        sh.bt[wave] = bt;
+        sh.bs[wave] = best;
+        sh.bt[wave] = bj;
     }
     __syncthreads();
-    double best_s = sh.bs[0], best_t = sh.bt[0];
-    for (int w = 1; w < kSureWaves; ++w) {
-        if (sh.bs[w] < best_s || (sh.bs[w] == best_s && sh.bt[w] < best_t)) {
-            best_s = sh.bs[w];
-            best_t = sh.bt[w];
-        }
-    }
-    if (st.best_s < best_s || (st.best_s == best_s && st.best_t < best_t)) {
-        best_s = st.best_s;
-        best_t = st.best_t;
-    }
-    const double U = best_s + 1e-12 * (fabs(best_s) + N);
-    int f = 0x7fffffff, l = -1;
-    uint32_t m = 0, mx = 0;
-    bool surv[PER];
+    best = sh.bs[lane & 15];
+    bj = sh.bt[lane & 15];
+    wave_argmin(best, bj);
+    const int J = (int)bj;
+    if (tid == J / kBinsPer) {
+        double C = C0, Sl = L0, Sh = H0, bb = 0.0;
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        surv[j] = cnt[j] && lbv[j] <= U;
-        if (surv[j]) {
-            const int b = tid * PER + j;
-            f = b < f ? b : f;
-            l = b > l ? b : l;
-            m += cnt[j];
-            mx = cnt[j] > mx ? cnt[j] : mx;
+        for (int j = 0; j < kBinsPer; ++j)
+            if (kBinsPer * tid + j <= J && c[j]) {
+                C += c[j];
+                Sl = fma((double)c[j], a[j], Sl);
+                Sh = fma((double)c[j], b[j], Sh);
+                bb = b[j];
+            }
+        sh.ref[0] = C;
+        sh.ref[1] = Sl;
+        sh.ref[2] = Sh;
+        sh.ref[3] = bb;
+    }
+    __syncthreads();
+    const double CJ = sh.ref[0], SlJ = sh.ref[1], ShJ = sh.ref[2], rise = (N - CJ) * sh.ref[3];
+    const bool have = best < __builtin_inf();
+    const double tol = 1e-10 * (N + ShJ + rise);
+    int f = 0x7fffffff, l = -1;
+    double cf = 0.0;
+    {
+        double C = C0, Sl = L0, Sh = H0;
+#pragma unroll
+        for (int j = 0; j < kBinsPer; ++j) {
+            const int bin = kBinsPer * tid + j;
+            if (!c[j]) continue;
+            const double cc = (double)c[j], low = (N - C) * a[j];
+            const double between = bin > J ? Sl - SlJ : Sh - ShJ;
+            const double over = -2.0 * (C + cc - CJ) + between + low - rise;        // L - U at the reference
+            const double over0 = -2.0 * (C + cc - (double)zeros) + Sl + low;        // L - SURE(0)
+            if (have && over <= tol && over0 <= tol) {     // NaN: not a candidate
+                if (bin < f) {
+                    f = bin;
+                    cf = C;
+                }
+                l = bin;
+            }
+            C += cc;
+            Sl = fma(cc, a[j], Sl);
+            Sh = fma(cc, b[j], Sh);
         }
     }
-    // first and last surviving bin, largest surviving bin, surviving values
     const int wf = wave_minmax_i32<false>(f), wl = wave_minmax_i32<true>(l);
-    const int wmx = wave_minmax_i32<true>((int)mx);
-    const uint32_t im = wave_incl_u32(m);
-    if (lane == 63) sh.wm[wave] = im;
     if (lane == 0) {
         sh.wf[wave] = wf;
         sh.wl[wave] = wl;
-        sh.wx[wave] = wmx;
     }
     __syncthreads();
-    int fb = sh.wf[0], lb = sh.wl[0];
-    unsigned int mxv = (unsigned int)sh.wx[0];
-    uint32_t msum = 0;
-    for (int w = 0; w < kSureWaves; ++w) {
-        msum += sh.wm[w];
-        if (w > 0) {
-            fb = sh.wf[w] < fb ? sh.wf[w] : fb;
-            lb = sh.wl[w] > lb ? sh.wl[w] : lb;
-            mxv = (unsigned int)sh.wx[w] > mxv ? (unsigned int)sh.wx[w] : mxv;
-        }
-    }
-    const unsigned long long msurv = msum;
-    const bool gather = lb >= 0 && st.width > 0 && msurv <= (unsigned long long)kSureCap &&
-                        mxv <= (unsigned)kSureBinCap;
-    if (gather) {
-        // bitmap of the surviving bins and the counts and sums below each
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            if (surv[j]) {
-                const int b = tid * PER + j;
-                atomicOr(&sh.bits[b >> 5], 1u << (b & 31));
-                d.spre[base + b] = st.below_cnt + pcs[j];
-                d.sspre[base + b] = st.below_sum + pss[j];
-            }
-        }
-        __syncthreads();
-        for (int w = tid; w < kSureBins / 32; w += kSureThreads)
-            d.sbits[(int64_t)comp * (kSureBins / 32) + w] = sh.bits[w];
-    }
-    // the prefix before the first surviving bin
-    if (!gather && tid == fb / PER && fb != 0x7fffffff) {
-        const int j = fb - tid * PER;
-        unsigned long long c0 = 0;
-        double s0 = 0.0;
-#pragma unroll
-        for (int jj = 0; jj < PER; ++jj)
-            if (jj == j) {
-                c0 = pcs[jj];
-                s0 = pss[jj];
-            }
-        sh.st.below_cnt = st.below_cnt + c0;
-        sh.st.below_sum = st.below_sum + s0;
-    }
+    const int ff = waves_minmax<false>(sh.wf), ll = waves_minmax<true>(sh.wl);
+    if (l >= 0 && f == ff) sh.c0 = (uint64_t)cf;
     __syncthreads();
-    if (tid == 0) {
-        SureState ns = sh.st;
-        ns.best_s = best_s;
-        ns.best_t = best_t;
-        ns.round = st.round + 1;
-        if (st.width == 0 || lb < 0) {
-            ns.done = 1;
-        } else if (gather) {
-            ns.gather = 1;
-            ns.nsurv = (unsigned int)msurv;
-        } else {
-            ns.klo = st.klo + ((uint64_t)fb << st.width);
-            const uint64_t hi = st.klo + ((uint64_t)(lb + 1) << st.width);
-            ns.khi = hi < st.khi ? hi : st.khi;
-            ns.width = sure_shift_for(ns.khi - ns.klo);
-            if (ns.round >= KT::kRounds) {
-                ns.done = 1;
-                ns.inexact = 1;
-            }
-        }
-        if (ns.done) {
-            d.lambda[comp] = ns.best_t;
-            if (d.sure) d.sure[comp] = ns.best_s;
-            if (ns.inexact) set_status(d.status, HYRES_DEV_SURE_INEXACT);
-        }
-        put_state(&d.sst[comp], ns);
-        gmem(d.sctr)[4 * comp] = 0u;        // block counter of the next pass
-        gmem(d.sctr)[4 * comp + 1] = 0u;    // gathered values
-    }
-    // clear the bins for the next pass
-    for (int b = tid; b < kSureBins; b += kSureThreads) {
-        gmem(d.hcnt)[base + b] = 0;
-        gmem(d.hsum)[base + b] = 0.0;
-        gmem(d.hmin)[base + b] = ~0ull;
-        gmem(d.hmax)[base + b] = 0;
+    *first = ll >= 0 ? ff : -1;
+    *last = ll;
+    *c0 = sh.c0;
+}
+
+// Keys of the bins first..last, zeros left out.
+template <typename T>
+__device__ __forceinline__ void first_range(int first, int last, uint64_t* klo, uint64_t* khi) {
+    const uint64_t k = first_edge<T>(first);
+    *klo = k ? k : 1;
+    *khi = first_edge<T>(last + 1);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kSureThreads) void k_sure_hist(const CubeDesc* __restrict__ descs,
+                                                            const int* __restrict__ items, int ncubes) {
+    __shared__ __align__(16) uint32_t lc[kSureBins];
+    const int c = find_cube(items, ncubes, blockIdx.x);
+    const CubeDesc& d = descs[c];
+    const int nch = d.snch, local = blockIdx.x - items[c], comp = local / nch, chunk = local - comp * nch;
+    const int tid = threadIdx.x;
+    for (int b = tid; b < kSureBins; b += kSureThreads) lc[b] = 0;
+    __syncthreads();
+    const int64_t N = sure_count(d), e0 = (int64_t)chunk * d.schunk, e1 = min(e0 + d.schunk, N);
+    const uint32_t nz =
+        first_histogram<T>(gmem(static_cast<const T*>(d.coef)) + (int64_t)comp * d.ncs, e0, e1, lc);
+    if (nz) atomicAdd(&lc[kZeroSlot], nz);
+    __syncthreads();
+    HYRES_GLOBAL uint32_t* row = gmem(d.shist) + comp * d.shcs;
+    if (d.schunk <= kSureRow16) {             // counts of a chunk fit 16 bits: two per word
+        row += (int64_t)chunk * (kSureBins / 2);
+        for (int b = tid; b < kSureBins / 2; b += kSureThreads) row[b] = lc[2 * b] | lc[2 * b + 1] << 16;
+    } else {
+        row += (int64_t)chunk * kSureBins;
+        for (int b = tid; b < kSureBins; b += kSureThreads) row[b] = lc[b];
     }
 }
 
-// One pass over every component still searching: histogram or gather of each
-// chunk; the last block of a component runs its select or finish.
 template <typename T>
-__global__ __launch_bounds__(kSureThreads) void k_sure_round(const CubeDesc* __restrict__ descs,
-                                                             const int* __restrict__ items, int ncubes) {
-    __shared__ __align__(16) unsigned char lds[SureLds<T>::kBytes];
+__global__ __launch_bounds__(kSureThreads) void k_sure_gather(const CubeDesc* __restrict__ descs,
+                                                              const int* __restrict__ items, int ncubes) {
+    typedef KeyTraits<T> KT;
     __shared__ SureShared sh;
-    const int total = items[ncubes];
-    const int tid = threadIdx.x;
-    for (int item = blockIdx.x; item < total; item += gridDim.x) {
-        const int c = find_cube(items, ncubes, item);
-        const CubeDesc& d = descs[c];
-        const int64_t N = sure_count(d);
-        const int64_t ch = d.schunk;
-        const int nch = (int)((N + ch - 1) / ch);
-        const int local = item - items[c];
-        const int comp = local / nch;
-        const int chunk = local - comp * nch;
+    const int cu = find_cube(items, ncubes, blockIdx.x);
+    const CubeDesc& d = descs[cu];
+    const int nch = d.snch, local = blockIdx.x - items[cu], comp = local / nch, chunk = local - comp * nch;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t N = sure_count(d);
+    uint32_t c[kBinsPer] = {0, 0, 0, 0};
+    static_assert(kBinsPer == 4, "rows are read four bins at a time");
+    const HYRES_GLOBAL uint32_t* rows = gmem(d.shist) + comp * d.shcs;
+    if (d.schunk <= kSureRow16) {
+        const HYRES_GLOBAL uint2* r = (const HYRES_GLOBAL uint2*)rows + tid;
+#pragma unroll 8
+        for (int k = 0; k < nch; ++k) {
+            const uint32_t x = r[(int64_t)k * kSureThreads].x, y = r[(int64_t)k * kSureThreads].y;
+            c[0] += x & 0xffffu;
+            c[1] += x >> 16;
+            c[2] += y & 0xffffu;
+            c[3] += y >> 16;
+        }
+    } else {
+#pragma unroll 4
+        for (int k = 0; k < nch; ++k)
+#pragma unroll
+            for (int j = 0; j < kBinsPer; ++j) c[j] += rows[(int64_t)k * kSureBins + kBinsPer * tid + j];
+    }
+    if (tid == kSureThreads - 1) {
+        sh.zeros = c[kBinsPer - 1];
+        c[kBinsPer - 1] = 0;
+        sh.count = 0;
+    }
+    __syncthreads();
+    const uint32_t zeros = sh.zeros;
+    int first, last;
+    uint64_t c0;
+    first_select<T>(c, zeros, (double)N, sh, &first, &last, &c0);
+    uint64_t klo = 1, khi = 1;
+    if (first >= 0) first_range<T>(first, last, &klo, &khi);
+    if (chunk == 0 && tid == 0) {
+        SureSel* s = d.ssel + comp;
+        s->klo = klo;
+        s->khi = khi;
+        s->c0 = c0;
+        s->zeros = zeros;
+    }
+    if (first < 0) return;
+    const int64_t e0 = (int64_t)chunk * d.schunk, e1 = min(e0 + d.schunk, N);
+    const HYRES_GLOBAL T* cf = gmem(static_cast<const T*>(d.coef)) + (int64_t)comp * d.ncs;
+    HYRES_GLOBAL T* seg = gmem(static_cast<T*>(d.slist)) + comp * d.slcs + (int64_t)chunk * d.segcap;
+    const uint32_t cap = (uint32_t)d.segcap;
+    constexpr int U = kSureLoads;
+    double s0 = 0.0;
+    for (int64_t e = e0 + tid - lane; e < e1; e += U * kSureThreads) {   // whole waves
+        T v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = e + lane + (int64_t)u * kSureThreads;
+            v[u] = i < e1 ? cf[i] : (T)0;
+        }
+        bool in[U];
+        uint32_t n = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint64_t k = KT::key(v[u]);
+            in[u] = k >= klo && k < khi;
+            n += (uint32_t)__popcll(__ballot(in[u]));
+            if (k < klo) s0 = fma((double)v[u], (double)v[u], s0);
+        }
+        uint32_t at = 0;
+        if (lane == 0 && n) at = atomicAdd(&sh.count, n);
+        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const unsigned long long m = __ballot(in[u]);
+            const uint32_t pos = at + (uint32_t)__popcll(m & ((1ull << lane) - 1));
+            if (in[u] && pos < cap) seg[pos] = v[u];
+            at += (uint32_t)__popcll(m);
+        }
+    }
+    s0 = wave_sum(s0);
+    if (lane == 0) sh.ws[wave] = s0;
+    __syncthreads();
+    if (tid == 0) {
+        double s = 0.0;
+        for (int w = 0; w < kSureWaves; ++w) s += sh.ws[w];
+        SureSeg* o = d.sseg + (int64_t)comp * kSureMaxChunks + chunk;
+        o->s0 = s;
+        o->count = sh.count;
+    }
+}
+
+// A range of keys to search: values and squares below it, a lower bound.
+struct SureRange {
+    uint64_t klo, khi, c0;
+    double s0, lb;
+};
+
+template <typename T>
+__global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __restrict__ descs,
+                                                              const int* __restrict__ items, int ncubes) {
+    typedef KeyTraits<T> KT;
+    typedef typename KT::K K;
+    constexpr int PER = kBinsPer, CAP = KT::kCap;
+    __shared__ uint32_t cnt[kSureBins];       // values per bin
+    __shared__ uint32_t pre[kSureBins];       // ... below the bin
+    __shared__ uint32_t off[kSureBins];       // end of the bin's values in `keys`
+    __shared__ double sum[kSureBins];         // squares per bin, then below the bin
+    __shared__ K keys[CAP];
+    __shared__ uint32_t bits[kSureBins / 32];
+    __shared__ SureRange stack[kSureStack];
+    __shared__ SureShared sh;
+    __shared__ int s_sp, s_lo, s_hi, s_inexact;
+    __shared__ uint32_t s_count[kSureMaxChunks];
+    const int cu = find_cube(items, ncubes, blockIdx.x);
+    const CubeDesc& d = descs[cu];
+    const int comp = blockIdx.x - items[cu];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t Ni = sure_count(d);
+    const double N = (double)Ni;
+    const int nch = d.snch;
+    const HYRES_GLOBAL T* coef = gmem(static_cast<const T*>(d.coef)) + (int64_t)comp * d.ncs;
+    const HYRES_GLOBAL T* list = gmem(static_cast<const T*>(d.slist)) + comp * d.slcs;
+    // f(value) for each of the values: the coefficients, taken by the whole block;
+    // or the chunks' segments (the chunk itself where its segment overflowed), in
+    // parts that the waves take in turn.
+    const int parts = (kSureWaves + nch - 1) / nch;
+    auto run = [&](const HYRES_GLOBAL T* p, int64_t a, int64_t b, int stride, auto f) {
+        constexpr int U = kSureLoads;
+        for (int64_t i = a; i < b; i += (int64_t)stride * U) {
+            T v[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) {
+                const int64_t e = i + (int64_t)stride * k;
+                v[k] = e < b ? p[e] : (T)0;
+            }
+#pragma unroll
+            for (int k = 0; k < U; ++k) f(v[k]);          // zeros are in no range
+        }
+    };
+    auto for_each = [&](auto f) {
+        if (nch == 1) {
+            run(coef, tid, Ni, kSureThreads, f);
+            return;
+        }
+        for (int u = wave; u < nch * parts; u += kSureWaves) {
+            const int s = u / parts, part = u - s * parts;
+            const bool fits = s_count[s] <= (uint32_t)d.segcap;
+            const int64_t m = fits ? (int64_t)s_count[s] : min(d.schunk, Ni - (int64_t)s * d.schunk);
+            const int64_t step = (m + parts - 1) / parts, a = part * step, b = min(a + step, m);
+            run(fits ? list + (int64_t)s * d.segcap : coef + (int64_t)s * d.schunk, a + lane, b, 64, f);
+        }
+    };
+
+    uint32_t zeros = 0;
+    uint64_t klo = 1, khi = 1, c0 = 0;
+    double s0 = 0.0;
+    bool need_s0 = false;
+    if (nch == 1) {
+        for (int b = tid; b < kSureBins; b += kSureThreads) cnt[b] = 0;
         __syncthreads();
-        if (tid == 0) sh.st = d.sst[comp];
+        const uint32_t nz = first_histogram<T>(coef, 0, Ni, cnt);
+        if (nz) atomicAdd(&cnt[kZeroSlot], nz);
         __syncthreads();
-        if (sh.st.done) continue;   // uniform across the block
-        const SureState st = sh.st;
-        // in refinement passes few values are in range: a block takes up to
-        // kSureGroup small chunks (the others of the group only count themselves)
-        const int64_t gmax = kSureGroupSpan / ch;
-        const int grp = st.round == 0 || st.gather ? 1 : (int)(gmax < 1 ? 1 : (gmax > kSureGroup ? kSureGroup : gmax));
-        if (chunk % grp == 0) {
-            const int64_t e0 = (int64_t)chunk * ch;
-            const int64_t eg = e0 + (int64_t)grp * ch;
-            const int64_t e1 = eg < N ? eg : N;
-            if (st.gather) {
-                for (int w = tid; w < kSureBins / 32; w += kSureThreads)
-                    sh.bits[w] = d.sbits[(int64_t)comp * (kSureBins / 32) + w];
-                constexpr int64_t span = (int64_t)kGatherPer * kSureThreads;
-                for (int64_t a = e0; a < e1; a += span) {
-                    __syncthreads();
-                    sure_gather_chunk<T>(d, comp, a, a + span < e1 ? a + span : e1, st, sh);
+        uint32_t c[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) c[j] = cnt[PER * tid + j];
+        zeros = cnt[kZeroSlot];
+        if (tid == kSureThreads - 1) c[PER - 1] = 0;
+        int first, last;
+        first_select<T>(c, zeros, N, sh, &first, &last, &c0);
+        if (first >= 0) first_range<T>(first, last, &klo, &khi);
+        need_s0 = true;
+    } else {
+        const SureSel s = d.ssel[comp];
+        klo = s.klo;
+        khi = s.khi;
+        c0 = s.c0;
+        zeros = s.zeros;
+        const SureSeg* sg = d.sseg + (int64_t)comp * kSureMaxChunks;
+        if (khi > klo) {
+            for (int k = tid; k < nch; k += kSureThreads) s_count[k] = sg[k].count;
+            for (int k = 0; k < nch; ++k) s0 += sg[k].s0;
+        }
+    }
+    // candidate 0 and the smallest upper bound so far
+    double best_s = N - 2.0 * (double)zeros, best_t = 0.0, U = best_s;
+    if (tid == 0) {
+        s_sp = 0;
+        s_inexact = 0;
+        if (khi > klo) {
+            stack[0].klo = klo;
+            stack[0].khi = khi;
+            stack[0].c0 = c0;
+            stack[0].s0 = s0;
+            stack[0].lb = -__builtin_inf();
+            s_sp = 1;
+        }
+    }
+    __syncthreads();
+    // block-wide argmin of each thread's (s, t), smaller t on ties
+    auto block_argmin = [&](double& s, double& t) {
+        wave_argmin(s, t);
+        __syncthreads();
+        if (lane == 0) {
+            sh.bs[wave] = s;
+            sh.bt[wave] = t;
+        }
+        __syncthreads();
+        s = sh.bs[lane & 15];
+        t = sh.bt[lane & 15];
+        wave_argmin(s, t);
+    };
+    while (true) {
+        __syncthreads();
+        const int sp = s_sp;
+        if (sp == 0) break;
+        klo = stack[sp - 1].klo;
+        khi = stack[sp - 1].khi;
+        c0 = stack[sp - 1].c0;
+        s0 = stack[sp - 1].s0;
+        const double tol = 1e-12 * (fabs(U) + N);
+        const bool skip = !(stack[sp - 1].lb <= U + tol);
+        __syncthreads();
+        if (tid == 0) s_sp = sp - 1;
+        if (skip) continue;
+        const int shf = shift_for(khi - klo);
+        for (int b = tid; b < kSureBins; b += kSureThreads) {
+            cnt[b] = 0;
+            sum[b] = 0.0;
+        }
+        __syncthreads();
+        double below = 0.0;
+        for_each([&](T v) {
+            const uint64_t k = KT::key(v);
+            if (k >= klo && k < khi) {
+                const int b = (int)((k - klo) >> shf);
+                atomicAdd(&cnt[b], 1u);
+                atomicAdd(&sum[b], (double)v * (double)v);
+            } else if (need_s0 && k < klo) {
+                below = fma((double)v, (double)v, below);
+            }
+        });
+        if (need_s0) {
+            below = wave_sum(below);
+            if (lane == 0) sh.ws[wave] = below;
+        }
+        __syncthreads();
+        if (need_s0) {
+            (void)waves_before(sh.ws, wave, &s0);
+            need_s0 = false;
+            __syncthreads();
+        }
+        // exclusive prefixes of the counts and sums
+        uint32_t c[PER], tc = 0;
+        double q[PER], tq = 0.0;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            c[j] = cnt[PER * tid + j];
+            q[j] = sum[PER * tid + j];
+            tc += c[j];
+            tq += q[j];
+        }
+        const uint32_t ic = wave_incl_u32(tc);
+        const double iq = wave_incl_f64(tq), pq = __shfl_up(iq, 1, 64);
+        if (lane == 63) {
+            sh.wc[wave] = ic;
+            sh.ws[wave] = iq;
+        }
+        __syncthreads();
+        uint32_t total;
+        double all;
+        uint32_t pc = waves_before(sh.wc, wave, &total) + ic - tc;
+        double ps = waves_before(sh.ws, wave, &all);
+        if (lane) ps += pq;
+        double lb[PER], us = __builtin_inf(), ut = 0.0;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int b = PER * tid + j;
+            pre[b] = pc;
+            sum[b] = ps;
+            lb[j] = __builtin_inf();
+            if (c[j]) {
+                const double C = (double)(c0 + pc), S = s0 + ps, cc = (double)c[j];
+                const uint64_t end = klo + ((uint64_t)(b + 1) << shf);
+                const double t0 = KT::val(klo + ((uint64_t)b << shf)), t1 = KT::val((end < khi ? end : khi) - 1);
+                lb[j] = N - 2.0 * (C + cc) + S + (N - C) * t0 * t0;
+                const double up = N - 2.0 * (C + cc) + (S + q[j]) + (N - C - cc) * t1 * t1;
+                if (up < us || (up == us && t1 < ut)) {
+                    us = up;
+                    ut = t1;
+                }
+            }
+            pc += c[j];
+            ps += q[j];
+        }
+        block_argmin(us, ut);
+        if (us < U) U = us;
+        if (shf == 0) {                       // one value per bin: the bounds are exact
+            if (us < best_s || (us == best_s && ut < best_t)) {
+                best_s = us;
+                best_t = ut;
+            }
+            continue;
+        }
+        const double lim = U + 1e-12 * (fabs(U) + N);
+        int f = 0x7fffffff, l = -1, mx = 0, nh = 0;
+        uint32_t m = 0;
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (lb[j] <= lim) {
+                const int b = PER * tid + j, n = c[j] < 0x7fffffffu ? (int)c[j] : 0x7fffffff;
+                f = b < f ? b : f;
+                l = b;
+                mx = n > mx ? n : mx;
+                nh += n > kSureHeavy ? 1 : 0;
+                m += c[j];
+            }
+        const int wf = wave_minmax_i32<false>(f), wl = wave_minmax_i32<true>(l), wx = wave_minmax_i32<true>(mx);
+        const uint32_t wm = wave_incl_u32(m), wh = wave_incl_u32((uint32_t)nh);
+        __syncthreads();
+        if (lane == 63) {
+            sh.wf[wave] = wf;
+            sh.wl[wave] = wl;
+            sh.wx[wave] = wx;
+            sh.wc[wave] = wm;
+            sh.wn[wave] = wh;
+        }
+        __syncthreads();
+        f = waves_minmax<false>(sh.wf);
+        l = waves_minmax<true>(sh.wl);
+        mx = waves_minmax<true>(sh.wx);
+        uint32_t heavies;
+        (void)waves_before(sh.wc, wave, &total);
+        (void)waves_before(sh.wn, wave, &heavies);
+        if (l < 0) continue;
+        if ((total > (uint32_t)CAP || mx > kSureLight) && (l - f + 1) * 2 <= kSureBins) {
+            // the surviving bins span at most half the range: search that
+            if (tid == 0) {
+                const uint64_t hi = klo + ((uint64_t)(l + 1) << shf);
+                SureRange& r = stack[s_sp];
+                r.klo = klo + ((uint64_t)f << shf);
+                r.khi = hi < khi ? hi : khi;
+                r.c0 = c0 + pre[f];
+                r.s0 = s0 + sum[f];
+                r.lb = -__builtin_inf();
+                s_sp = s_sp + 1;
+            }
+            continue;
+        }
+        // bins too large to evaluate value by value become ranges of their own
+        const uint32_t heavy = heavies <= 128 ? (uint32_t)kSureHeavy : (uint32_t)(CAP / 2);
+        uint32_t g[PER], tg = 0;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int b = PER * tid + j;
+            g[j] = 0;
+            if (!(lb[j] <= lim)) continue;
+            if (c[j] > heavy) {
+                const int at = atomicAdd(&s_sp, 1);
+                if (at < kSureStack) {
+                    const uint64_t hi = klo + ((uint64_t)(b + 1) << shf);
+                    SureRange& r = stack[at];
+                    r.klo = klo + ((uint64_t)b << shf);
+                    r.khi = hi < khi ? hi : khi;
+                    r.c0 = c0 + pre[b];
+                    r.s0 = s0 + sum[b];
+                    r.lb = lb[j];
+                } else {
+                    s_inexact = 1;
                 }
             } else {
-                sure_hist_range<T>(d, comp, e0, e1, st, lds, sh);
+                g[j] = c[j];
+                tg += c[j];
             }
         }
-        // Every wave waits for its global atomics and stores to be acknowledged;
-        // then one release fence (device scope) for the block before it is
-        // counted, and one acquire fence in the last block before its reads.
-        // The L1 and L2 the fences act on are shared by the waves of the block.
-        __builtin_amdgcn_s_waitcnt(0);
+        const uint32_t ig = wave_incl_u32(tg);
         __syncthreads();
-        if (tid == 0) {
-            __threadfence();
-            const bool last = atomicAdd(&gmem(d.sctr)[4 * comp], 1u) == (unsigned)(nch - 1);
-            if (last) __threadfence();
-            sh.last = last;
+        if (lane == 63) sh.wc[wave] = ig;
+        if (tid == 0 && s_sp > kSureStack) s_sp = kSureStack;
+        __syncthreads();
+        uint32_t light;
+        const uint32_t og = waves_before(sh.wc, wave, &light) + ig - tg;
+        // groups of consecutive bins whose values fit in LDS (mostly one)
+        const uint32_t gc = light <= (uint32_t)CAP ? (uint32_t)CAP : (uint32_t)(CAP / 2);
+        for (uint32_t base = 0; base < light; base += gc) {
+            if (tid < kSureBins / 32) bits[tid] = 0;
+            if (tid == 0) {
+                s_lo = CAP;
+                s_hi = 0;
+            }
+            __syncthreads();
+            uint32_t o = og;
+            uint32_t mine = 0;
+            int lo = CAP, hi = 0;
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                if (g[j] && o >= base && o - base < gc) {
+                    off[PER * tid + j] = o - base;
+                    mine |= 1u << j;
+                    lo = min(lo, (int)(o - base));
+                    hi = max(hi, (int)(o - base + g[j]));
+                }
+                o += g[j];
+            }
+            if (mine) {
+                atomicOr(&bits[tid >> 3], mine << (4 * (tid & 7)));
+                atomicMin(&s_lo, lo);
+                atomicMax(&s_hi, hi);
+            }
+            __syncthreads();
+            for_each([&](T v) {
+                const uint64_t k = KT::key(v);
+                if (k >= klo && k < khi) {
+                    const int b = (int)((k - klo) >> shf);
+                    if ((bits[b >> 5] >> (b & 31)) & 1u) keys[atomicAdd(&off[b], 1u)] = (K)k;
+                }
+            });
+            __syncthreads();
+            double es = __builtin_inf(), et = 0.0;
+            for (int i = s_lo + tid; i < s_hi; i += kSureThreads) {
+                const uint64_t key = keys[i];
+                const int b = (int)((key - klo) >> shf);
+                const int n = (int)cnt[b], j1 = (int)off[b];
+                int in = 0;
+                double sq = 0.0;
+                for (int j = j1 - n; j < j1; j += 4) {      // four reads in flight, added in order
+                    uint64_t kj[4];
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) kj[w] = keys[j + w < j1 ? j + w : j1 - 1];
+#pragma unroll
+                    for (int w = 0; w < 4; ++w)
+                        if (j + w < j1 && kj[w] <= key) {
+                            const double vj = KT::val(kj[w]);
+                            ++in;
+                            sq = fma(vj, vj, sq);
+                        }
+                }
+                const double cc = (double)(c0 + pre[b]) + (double)in, S = s0 + sum[b] + sq, v = KT::val(key);
+                const double sv = N - 2.0 * cc + S + (N - cc) * v * v;
+                if (sv < es || (sv == es && v < et)) {
+                    es = sv;
+                    et = v;
+                }
+            }
+            block_argmin(es, et);
+            if (es < best_s || (es == best_s && et < best_t)) {
+                best_s = es;
+                best_t = et;
+            }
+            if (best_s < U) U = best_s;
+            __syncthreads();
         }
-        __syncthreads();
-        if (!sh.last) continue;
-        if (st.gather) sure_finish<T>(d, comp, (double)N, lds, sh);
-        else sure_select<T>(d, comp, (double)N, sh);
+    }
+    if (tid == 0) {
+        d.lambda[comp] = best_t;
+        if (d.sure) d.sure[comp] = best_s;
+        if (s_inexact) set_status(d.status, HYRES_DEV_SURE_INEXACT);
     }
 }
 
 // ---------------------------------------------------------------- launchers
-hipError_t launch_sure_init(int dtype, const CubeDesc* descs, const int* items, int ncubes, int grid,
-                            hipStream_t s) {
-    if (dtype == HYRES_F64)
-        hipLaunchKernelGGL(k_sure_init<double>, dim3(grid), dim3(256), 0, s, descs, items, ncubes);
-    else
-        hipLaunchKernelGGL(k_sure_init<float>, dim3(grid), dim3(256), 0, s, descs, items, ncubes);
+hipError_t launch_sure(int dtype, int step, const CubeDesc* descs, const int* items, int ncubes, int grid,
+                       hipStream_t s) {
+#define HYRES_S(K)                                                                                                \
+    if (dtype == HYRES_F64) hipLaunchKernelGGL(K<double>, dim3(grid), dim3(kSureThreads), 0, s, descs, items, ncubes); \
+    else hipLaunchKernelGGL(K<float>, dim3(grid), dim3(kSureThreads), 0, s, descs, items, ncubes)
+    if (step == 0) HYRES_S(k_sure_hist);
+    else if (step == 1) HYRES_S(k_sure_gather);
+    else HYRES_S(k_sure_finish);
+#undef HYRES_S
     return hipGetLastError();
 }
 
-hipError_t launch_sure_round(int dtype, const CubeDesc* descs, const int* items, int ncubes, int grid,
-                             hipStream_t s) {
-    if (dtype == HYRES_F64)
-        hipLaunchKernelGGL(k_sure_round<double>, dim3(grid), dim3(kSureThreads), 0, s, descs, items, ncubes);
-    else
-        hipLaunchKernelGGL(k_sure_round<float>, dim3(grid), dim3(kSureThreads), 0, s, descs, items, ncubes);
-    return hipGetLastError();
+// Chunks of one component of N values in a program of `total` values: one per
+// compute unit over all components, of at least 16384 values, at most `room`
+// (rows that fit) and kSureMaxChunks.  Components of up to kSureDirect values
+// take one block for the whole search (two launches fewer; a block reads 65536
+// values in 2 us).  Up to 64 chunks of 16-bit counts before longer ones.
+int sure_chunks(int64_t N, int64_t total, int num_cu, int64_t room) {
+    if (N <= kSureDirect) return 1;
+    int64_t ch = (total + num_cu - 1) / num_cu;
+    if (ch < 16384) ch = 16384;
+    int64_t nch = (N + ch - 1) / ch;
+    if (N <= 64 * kSureRow16 && (N + nch - 1) / nch > kSureRow16 - 1024) nch = (N + kSureRow16 - 1025) / (kSureRow16 - 1024);
+    if (nch > 64) nch = 64;
+    if (nch > room) nch = room;
+    return nch < 1 ? 1 : (int)nch;
 }
-
-// One more pass than refinement rounds, so a gather decided in the last
-// refinement round is still finished.
-int sure_rounds(int dtype) { return (dtype == HYRES_F64 ? kSureRoundsF64 : kSureRoundsF32) + 1; }
-// Coefficients per work item: about one item per compute unit over all the
-// components of a program (each block then streams its item once per pass),
-// at least kSureChunk, a multiple of the block size.
-int64_t sure_chunk_for(int64_t total_coef, int num_cu) {
-    int64_t ch = (total_coef + num_cu - 1) / (num_cu > 0 ? num_cu : 1);
-    ch = (ch + kSureThreads - 1) / kSureThreads * kSureThreads;
-    return ch > kSureChunk ? ch : kSureChunk;
+int64_t sure_chunk(int64_t N, int nch) {
+    return ((N + nch - 1) / nch + kSureThreads - 1) / kSureThreads * kSureThreads;
 }
 
 }  // namespace hyres

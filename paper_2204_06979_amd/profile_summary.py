@@ -14,7 +14,7 @@ the ratio of the bytes a plain copy of known size moves to what the same
 counter reports for that copy.  Per-step figures divide a kernel's total over
 the run by the number of steps in it: one step is one run of the whole path
 (one solve, one batch, or one sliding-window solve), and every step starts
-the threshold search once (one k_sure_init dispatch per step).
+the threshold search once (one k_sure_finish dispatch per step).
 """
 from __future__ import annotations
 
@@ -91,7 +91,7 @@ def summarize(a) -> int:
     cw = copy_factor(a.cal_write, "WRITE_SIZE") if a.cal_write else None
     def steps_of(counts):
         # one threshold-search start per cube group and solve
-        s = sum(c for n, c in counts if "k_sure_init" in n)
+        s = sum(c for n, c in counts if "k_sure_finish" in n)
         s = s or sum(c for n, c in counts if "k_small" in n) or 1
         return max(1, s // max(1, a.groups))
     solves_t = steps_of([(n, c) for n, c, *_ in stats])
