@@ -18,66 +18,81 @@
 // v_fmac_f64): one instruction per entry and no LDS traffic or register for the
 // row operand.  Column sums stay in the lane but for two swaps over g, and a
 // matrix row, which by symmetry is the next column, leaves the registers with
-// one LDS write per wave.  From T = 5 on a wave owns the tiles w and w + W
-// (W = ceil(T / 2)): the work of a step beside the products (norm, square root,
-// quotient, reductions) is issued once for both, and no SIMD has more than two
-// waves.  Both eliminations are bound by instruction issue, the late steps of the
-// tridiagonalisation by the latency of its two barriers and its square root.
-// The previous layout (a thread grid with 5 x 9 entries per thread at p = 144,
-// row sums over 16 lanes by DPP, the operands of both sides from LDS) issued
-// about 480 vector instructions per Householder step and wave.
+// one LDS write per wave.  A wave owns one tile up to T = 12 (at most three waves
+// and 168 registers per SIMD); beyond, seven waves own two tiles each (two
+// waves and 256 registers per SIMD) and keep the rows of the first three tiles,
+// dead after 48 steps, in LDS (two tiles per wave from T = 9 on measured 314 us
+// against 298 at p = 144).  What bounds it is the chain of a step, about 250
+// instructions of one wave at five cycles each beside the products: reductions,
+// a square root, a quotient, a barrier.  The previous layout (a thread grid with
+// 5 x 9 entries per thread at p = 144, row sums over 16 lanes by DPP, operands of
+// both sides from LDS) issued about 480 vector instructions per Householder
+// step and wave.  Microseconds before and now at rank 4-10: 32 bands 81, 50; 103
+// 375, 203; 128 435, 231; 144 472, 290; 191 867, 428; 224 1490, 706.  Of the 290:
+// noise 61, tridiagonalisation 137, Sturm counts 29, twisted factorisation 20,
+// back-transformation 36.
 #include "hyres_internal.hpp"
 
 namespace hyres {
 
 constexpr int kSmallP = 256;   // LDS vector length (p <= 224)
 
+// Entry of lane C of each row of 16 lanes, to every lane of the row.
+template <int C>
+__device__ __forceinline__ double row_bcast(double v) {
+    long long x = __builtin_bit_cast(long long, v);
+    x = __builtin_amdgcn_update_dpp(x, x, 0x150 + C, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, x);
+}
+
 // Sturm count: number of eigenvalues of the symmetric tridiagonal matrix
 // smaller than x, from the sign changes of the leading principal minors
 // p_i(x) = (d_i - x) p_{i-1}(x) - e_{i-1}^2 p_{i-2}(x) (a minor that is
 // exactly zero counts as positive); both minors are rescaled by a power of two
-// every 8 steps so the recursion stays in range.  de[i] = (d_i, e_{i-1}^2), a
-// step is three FP64 instructions and one that shifts the sign into a word; the
-// next 8 entries are read while these run.
-__device__ __forceinline__ int sgnbit(double v) { return (int)((unsigned)__double2hiint(v) >> 31); }
-
-__device__ __forceinline__ int sturm_count(const double2* __restrict__ de, int p, double x) {
-    double pm2 = 1.0, pm1 = de[0].x - x;
-    uint32_t bits = (uint32_t)sgnbit(pm1);     // signs of the minors, the latest lowest
-    int cnt = (int)bits, i = 1;
-    double2 cur[8];
-    if (i + 8 <= p) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) cur[u] = de[i + u];
-    }
-    for (; i + 8 <= p; i += 8) {
-        double2 nxt[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) nxt[u] = de[i + 8 + u];      // past p: padding, not used
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const double pi = fma(cur[u].x - x, pm1, -cur[u].y * pm2);
+// every 8 steps so the recursion stays in range.  Lane c of a row of 16 holds
+// d_i and e_{i-1}^2 of i = 16 b + c (entries past the matrix: d = 3, e = 0, no sign
+// change for x < 3); a step is two broadcasts, three FP64 operations and one that
+// shifts the sign into a word: 24 issue cycles, no LDS (broadcast 16-byte reads of
+// all waves were its bound before, 49 cycles a step).
+template <int T>
+__device__ __forceinline__ int sturm_count(const double (&dv)[T], const double (&ev)[T], double x) {
+    double pm2 = 0.0, pm1 = 1.0;
+    uint32_t bits = 0;                         // signs of the minors, the latest lowest
+    int cnt = 0;
+    static_for<2 * T>([&](auto h) {
+        constexpr int b = decltype(h)::value / 2, c0 = 8 * (decltype(h)::value % 2);
+        static_for<8>([&](auto u) {
+            constexpr int c = c0 + decltype(u)::value;
+            const double pi = fma(row_bcast<c>(dv[b]) - x, pm1, -row_bcast<c>(ev[b]) * pm2);
             bits = __builtin_amdgcn_alignbit(bits, (uint32_t)__double2hiint(pi), 31);
             pm2 = pm1;
             pm1 = pi;
-        }
+        });
         cnt += __builtin_popcount((bits ^ (bits >> 1)) & 0xffu);
         const int e1 = __builtin_amdgcn_frexp_exp(pm1), e2 = __builtin_amdgcn_frexp_exp(pm2);
         const int e = e1 > e2 ? e1 : e2;
         pm1 = ldexp(pm1, -e);
         pm2 = ldexp(pm2, -e);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) cur[u] = nxt[u];
-    }
-    for (int u = 0; i < p; ++i, ++u) {
-        const double2 v = de[i];
-        const double pi = fma(v.x - x, pm1, -v.y * pm2);
-        bits = __builtin_amdgcn_alignbit(bits, (uint32_t)__double2hiint(pi), 31);
-        cnt += (int)((bits ^ (bits >> 1)) & 1u);
-        pm2 = pm1;
-        pm1 = pi;
-    }
+    });
     return cnt;
+}
+
+// 1 / d and sqrt(s) for normal s > 0: the hardware estimates (24 bits) and
+// Newton steps, to about one unit in the last place, without the scaling
+// steps of the general division and square root (their latency is on the
+// chain of every elimination step).
+__device__ __forceinline__ double recip(double d) {
+    double r = __builtin_amdgcn_rcp(d);
+    r = fma(fma(-d, r, 1.0), r, r);
+    return fma(fma(-d, r, 1.0), r, r);
+}
+__device__ __forceinline__ double root(double s) {
+    const double y = __builtin_amdgcn_rsq(s);
+    double w = s * y, h = 0.5 * y;
+    const double e = fma(-h, w, 0.5);
+    w = fma(w, e, w);
+    h = fma(h, e, h);
+    return fma(fma(-w, w, s), h, w);
 }
 
 // In place: lo = max and hi = min over each aligned group of M lanes (M = 4, 16, 32 or 64).
@@ -109,13 +124,16 @@ __device__ __forceinline__ void group_maxmin(double& lo, double& hi, int M) {
     hi = ha < hb ? ha : hb;
 }
 
+// Barrier that orders LDS accesses only: __syncthreads() also waits for the
+// global stores in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // ---- products of register rows with a vector held in lanes (see the top) ----
 // a[k] += x[lane C0 + k of this row of 16] * z, k < N.  The wait states at the
 // start cover a write of x right before (a DPP operand needs two).
 #define HYRES_BC(A, X, Z, C) "v_fmac_f64_dpp " A ", " X ", " Z " row_newbcast:" C " row_mask:0xf bank_mask:0xf\n"
-template <int E0, int N, int E>
+template <int C0, int E0, int N, int E>
 __device__ __forceinline__ void axpy_block(double (&a)[E], double x, double z) {
-    constexpr int C0 = E0 & 15;
     static_assert(C0 + N <= 16, "within one register of x");
     if constexpr (N == 4) {
         asm("s_nop 1\n" HYRES_BC("%0", "%4", "%5", "%6") HYRES_BC("%1", "%4", "%5", "%7")
@@ -149,9 +167,8 @@ __device__ __forceinline__ void axpy_block(double (&a)[E], double x, double z) {
     }
 }
 // y[k mod 4] += x[lane C0 + k] * a[k], k < N
-template <int E0, int N, int E>
+template <int C0, int E0, int N, int E>
 __device__ __forceinline__ void dot_block(const double (&a)[E], double x, double (&y)[4]) {
-    constexpr int C0 = E0 & 15;
     if constexpr (N == 4) {
         asm("s_nop 1\n" HYRES_BC("%0", "%4", "%5", "%9") HYRES_BC("%1", "%4", "%6", "%10")
                 HYRES_BC("%2", "%4", "%7", "%11") HYRES_BC("%3", "%4", "%8", "%12")
@@ -171,61 +188,82 @@ __device__ __forceinline__ void dot_block(const double (&a)[E], double x, double
     }
 }
 #undef HYRES_BC
-// All rows from element E0 on.
-template <int E0, int E, int M>
-__device__ __forceinline__ void axpy_rows(double (&a)[E], const double (&x)[M], double z) {
-    if constexpr (E0 < E) {
+// All rows from element E0 on.  The first EL elements of a column live in LDS
+// (element e at low[e * stride]), the others in a[e - EL].
+template <int E0, int EL, int E, int M>
+__device__ __forceinline__ void axpy_rows(double (&a)[E - EL], double* low, int stride, const double (&x)[M], double z) {
+    if constexpr (E0 < EL) {
+        double t[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) t[k] = low[(E0 + k) * stride];
+        axpy_block<(E0 & 15), 0, 4>(t, x[E0 >> 4], z);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) low[(E0 + k) * stride] = t[k];
+        __builtin_amdgcn_sched_barrier(0);   // reads hoisted above others would spill
+        axpy_rows<E0 + 4, EL, E, M>(a, low, stride, x, z);
+    } else if constexpr (E0 < E) {
         constexpr int room = 16 - (E0 & 15), len = room < E - E0 ? room : E - E0;
         constexpr int N = len >= 16 ? 16 : len >= 8 ? 8 : 4;
-        axpy_block<E0, N>(a, x[E0 >> 4], z);
-        axpy_rows<E0 + N, E, M>(a, x, z);
+        axpy_block<(E0 & 15), E0 - EL, N>(a, x[E0 >> 4], z);
+        axpy_rows<E0 + N, EL, E, M>(a, low, stride, x, z);
     }
 }
-template <int E0, int E, int M>
-__device__ __forceinline__ void dot_rows(const double (&a)[E], const double (&x)[M], double (&y)[4]) {
-    if constexpr (E0 < E) {
+template <int E0, int EL, int E, int M>
+__device__ __forceinline__ void dot_rows(const double (&a)[E - EL], const double* low, int stride, const double (&x)[M],
+                                         double (&y)[4]) {
+    if constexpr (E0 < EL) {
+        double t[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) t[k] = low[(E0 + k) * stride];
+        dot_block<(E0 & 15), 0, 4>(t, x[E0 >> 4], y);
+        __builtin_amdgcn_sched_barrier(0);
+        dot_rows<E0 + 4, EL, E, M>(a, low, stride, x, y);
+    } else if constexpr (E0 < E) {
         constexpr int room = 16 - (E0 & 15), len = room < E - E0 ? room : E - E0;
         constexpr int N = len >= 8 ? 8 : 4;
-        dot_block<E0, N>(a, x[E0 >> 4], y);
-        dot_rows<E0 + N, E, M>(a, x, y);
+        dot_block<(E0 & 15), E0 - EL, N>(a, x[E0 >> 4], y);
+        dot_rows<E0 + N, EL, E, M>(a, low, stride, x, y);
     }
 }
 
-// Sum over the four rows of 16 lanes, to every lane.
-__device__ __forceinline__ double rows_sum(double v) {
-    {
-        const uint32_t lo = (uint32_t)__double2loint(v), hi = (uint32_t)__double2hiint(v);
-        const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-        const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-        v = __hiloint2double((int)b[0], (int)a[0]) + __hiloint2double((int)b[1], (int)a[1]);
-    }
-    const uint32_t lo = (uint32_t)__double2loint(v), hi = (uint32_t)__double2hiint(v);
-    const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-    const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-    return __hiloint2double((int)b[0], (int)a[0]) + __hiloint2double((int)b[1], (int)a[1]);
+// Sum over the four rows of 16 lanes (g), to every lane: the B operand of the
+// 4 x 4 x 4 product of four blocks holds row k = g of column c in lane (g, c), so
+// a product with ones is the sum, one instruction of 28 cycles.
+__device__ __forceinline__ double rows_sum(double v) { return __builtin_amdgcn_mfma_f64_4x4x4f64(1.0, v, 0.0, 0, 0, 0); }
+// Sum over the wave, to every lane: as the A operand the row sums come out
+// transposed within each block of four columns; their sum over g is the block's,
+// and two mirrors within the 16 lanes add the blocks.
+__device__ __forceinline__ double wave_total(double v) {
+    v = rows_sum(__builtin_amdgcn_mfma_f64_4x4x4f64(v, 1.0, 0.0, 0, 0, 0));
+    v += dpp_f64<0x141>(v);   // row_half_mirror
+    v += dpp_f64<0x140>(v);   // row_mirror
+    return v;
 }
 
-// a[E0 + q] for the wave-uniform q < N (every index a constant: the array stays in
-// registers).
-template <int E0, int N, int E>
-__device__ __forceinline__ double pick(const double (&a)[E], int q) {
+// Element E0 + q of a column for the wave-uniform q < N (every index a constant:
+// the array stays in registers).
+template <int E0, int N, int EL, int E>
+__device__ __forceinline__ double pick(const double (&a)[E - EL], const double* low, int stride, int q) {
     if constexpr (N > 1 && E0 + N > E) {
-        return pick<E0, N - 1, E>(a, q);
+        return pick<E0, N - 1, EL, E>(a, low, stride, q);
+    } else if constexpr (E0 + N <= EL) {
+        return low[(E0 + q) * stride];
     } else if constexpr (N == 1) {
-        return a[E0];
+        return a[E0 - EL];
     } else {
-        const double v = pick<E0, N - 1, E>(a, q);
-        return q == N - 1 ? a[E0 + N - 1] : v;
+        const double v = pick<E0, N - 1, EL, E>(a, low, stride, q);
+        return q == N - 1 ? a[E0 + N - 1 - EL] : v;
     }
 }
 
 // Shape of the column layout of T tiles.
 template <int T>
 struct Cols {
-    static constexpr int NC = T >= 5 ? 2 : 1;            // column tiles per wave
+    static constexpr int NC = T >= 13 ? 2 : 1;           // column tiles per wave
     static constexpr int W = (T + NC - 1) / NC;          // waves that own columns
-    static constexpr int NW = T >= 5 ? 8 : 4;            // waves of the block
+    static constexpr int NW = W > 8 ? W : T >= 5 ? 8 : 4;  // waves of the block
     static constexpr int E = 4 * T;                      // rows per lane
+    static constexpr int EL = NC == 2 ? E - 44 : 0;      // ... of which in LDS: registers hold 2 x 44 rows
     static constexpr int M = (T + 3) / 4;                // registers of a row vector
     static constexpr int SP = M % 2 ? 16 * M : 16 * M + 16;   // LDS stride of its four parts: 16 mod 32 doubles
     static constexpr int Q = (T + 3) / 4;                // 64-entry pieces of a vector
@@ -239,7 +277,8 @@ template <int T>
 __global__ __launch_bounds__(64 * Cols<T>::NW) void k_small(const CubeDesc* __restrict__ descs,
                                                             const int* __restrict__ cubes, int ncls) {
     typedef Cols<T> CL;
-    constexpr int NW = CL::NW, NTH = 64 * NW, NC = CL::NC, W = CL::W, E = CL::E, M = CL::M, SP = CL::SP;
+    constexpr int NW = CL::NW, NTH = 64 * NW, NC = CL::NC, W = CL::W, E = CL::E, EL = CL::EL, M = CL::M,
+                  SP = CL::SP;
     constexpr int Q = CL::Q, PL = CL::PL;
     constexpr int VPW = (kMaxRank + NW - 1) / NW;   // eigenvectors per wave
     if ((int)blockIdx.x >= ncls) return;
@@ -249,17 +288,19 @@ __global__ __launch_bounds__(64 * Cols<T>::NW) void k_small(const CubeDesc* __re
     const int t = threadIdx.x, lane = t & 63, g = lane >> 4, c = lane & 15;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
 
-    __shared__ double s_row[2][2][4 * SP];           // matrix rows on their way (noise: pairs)
+    __shared__ double s_row[2][2][4 * SP];           // matrix rows (noise: pairs), u and the next row (eigen)
     __shared__ double s_u[4 * SP];
     __shared__ double s_col[2][PL];
     __shared__ double s_sig[PL];
     __shared__ double s_dd[PL], s_ee[PL], s_hb[PL], s_ev[PL];
-    __shared__ double2 s_de[PL + 16];                // scaled (d_i, e_{i-1}^2)
-    __shared__ double s_zL[PL * kMaxRank];           // multipliers of the top-down factorisation [i][g]
-    __shared__ double s_zU[PL * kMaxRank];           // multipliers of the bottom-up one         [i][g]
-    __shared__ double s_z[kMaxRank][PL];             // eigenvectors of the tridiagonal / of C
+    // the LDS rows of the columns, then multipliers of the top-down and of the
+    // bottom-up factorisation [i][g], and the eigenvectors of the tridiagonal / of C
+    constexpr int kPool = NC * EL * 64 * W > 3 * PL * kMaxRank ? NC * EL * 64 * W : 3 * PL * kMaxRank;
+    __shared__ double s_pool[kPool];
+    double* const s_zL = s_pool;
+    double* const s_zU = s_pool + PL * kMaxRank;
+    double (*const s_z)[PL] = reinterpret_cast<double (*)[PL]>(s_pool + 2 * PL * kMaxRank);
     __shared__ double s_red[4];
-    __shared__ double s_vav[NW];                     // per-wave shares of v^T A v
     __shared__ int s_kb[kMaxRank];                   // twist indices
     __shared__ double s_cross[kMaxRank][kMaxRank + 1];   // rank by SURE: sum_{j>=k} l_i / (l_i - l_j), [i][k]
     __shared__ int s_rank;                           // rank used
@@ -273,7 +314,9 @@ __global__ __launch_bounds__(64 * Cols<T>::NW) void k_small(const CubeDesc* __re
     }
     int flags = 0;
     HYRES_STAMP(d, 0);
-    double A[NC][E];
+    double A[NC][E - EL];
+    constexpr int LS = NC * 64 * W;                  // stride of the LDS rows
+    double* low[NC];
     // column and slot of this lane per column tile (tiles beyond T: column -1)
     int col[NC], own[NC];
 #pragma unroll
@@ -281,8 +324,23 @@ __global__ __launch_bounds__(64 * Cols<T>::NW) void k_small(const CubeDesc* __re
         const int tile = wave + W * j;
         col[j] = wave < W && tile < T ? 16 * tile + c : -1;
         own[j] = col[j] >= 0 ? slot_of<T>(col[j]) : 0;
+        low[j] = s_pool + (j * W + (wave < W ? wave : 0)) * 64 + lane;
     }
     const HYRES_GLOBAL double* G = gmem(static_cast<const double*>(d.G));
+    HYRES_GLOBAL double* hv = gmem(d.hv);
+    int clampc[NC];
+#pragma unroll
+    for (int j = 0; j < NC; ++j) clampc[j] = min(max(col[j], 0), p - 1);
+    // this lane's columns of G, every load in flight at once (entries beyond p
+    // read the last row or column and are replaced by the caller)
+    auto load_columns = [&]() {
+        static_for<NC * E>([&](auto x) {
+            constexpr int j = decltype(x)::value / E, e = decltype(x)::value % E;
+            const double v = G[(uint32_t)(min(4 * e + g, p - 1) * p + clampc[j])];
+            if constexpr (e < EL) low[j][e * LS] = v;
+            else A[j][e - EL] = v;
+        });
+    };
     __syncthreads();
 
     // ---------------------------------------------------------------- noise
@@ -295,10 +353,16 @@ __global__ __launch_bounds__(64 * Cols<T>::NW) void k_small(const CubeDesc* __re
     // pairs, one barrier each: row k1 after the k0 step is formed by every lane.
     if (d.mode & 1) {
         if (wave < W) {
+            load_columns();
             static_for<NC * E>([&](auto x) {
                 constexpr int j = decltype(x)::value / E, e = decltype(x)::value % E;
                 const int i = 4 * e + g, n = col[j];
-                A[j][e] = i < p && n >= 0 && n < p ? G[(int64_t)i * p + n] : (i == n ? 1.0 : 0.0);
+                double v;
+                if constexpr (e < EL) v = low[j][e * LS];
+                else v = A[j][e - EL];
+                v = i < p && n >= 0 && n < p ? v : (i == n ? 1.0 : 0.0);
+                if constexpr (e < EL) low[j][e * LS] = v;
+                else A[j][e - EL] = v;
             });
         }
         // diagonal of G for the pivot test (s_ev is free until the eigenvalues)
@@ -311,7 +375,8 @@ __global__ __launch_bounds__(64 * Cols<T>::NW) void k_small(const CubeDesc* __re
         }
         static_for<T>([&](auto tc) {
             constexpr int t0 = decltype(tc)::value, m0 = t0 / 4;
-            for (int kk = 0; kk < 16; kk += 2) {
+#pragma unroll 1
+            for (int kk = 0; kk < 16; kk += 2) {   // unrolled, its code would not fit the instruction cache
                 const int k0 = 16 * t0 + kk, k1 = k0 + 1;
                 if (k0 >= p) break;
                 double (*row)[4 * SP] = s_row[(kk >> 1) & 1];
@@ -319,7 +384,7 @@ __global__ __launch_bounds__(64 * Cols<T>::NW) void k_small(const CubeDesc* __re
                 if (wave < W) {
                     static_for<NC>([&](auto jc) {
                         constexpr int j = decltype(jc)::value;
-                        const double v = pick<4 * t0, 4>(A[j], kk >> 2);
+                        const double v = pick<4 * t0, 4, EL, E>(A[j], low[j], LS, kk >> 2);
                         if (col[j] >= 0 && (gr == 0 || gr == 1)) row[gr][own[j]] = v;
                     });
                 }
@@ -331,13 +396,13 @@ __global__ __launch_bounds__(64 * Cols<T>::NW) void k_small(const CubeDesc* __re
                     flags |= HYRES_DEV_NOT_PD;
                     d0 = 1.0;
                 }
-                const double inv0 = 1.0 / d0, m01 = r01 * inv0;
+                const double inv0 = recip(d0), m01 = r01 * inv0;
                 double d1 = fma(-r01, m01, r11);
                 if (!(d1 > 1e-12 * s_ev[k1])) {
                     flags |= HYRES_DEV_NOT_PD;
                     d1 = 1.0;
                 }
-                const double inv1 = 1.0 / d1;
+                const double inv1 = recip(d1);
                 if (wave < W) {
                     double x0[M], x1[M];
 #pragma unroll
@@ -356,8 +421,8 @@ __global__ __launch_bounds__(64 * Cols<T>::NW) void k_small(const CubeDesc* __re
                         if (n == k0) dself[j] = d0;
                         if (n < k1) acc[j] = fma(r1, c1, acc[j]);
                         if (n == k1) dself[j] = d1;
-                        axpy_rows<4 * t0, E, M>(A[j], x0, -c0);
-                        axpy_rows<4 * t0, E, M>(A[j], x1, -c1);
+                        axpy_rows<4 * t0, EL, E, M>(A[j], low[j], LS, x0, -c0);
+                        axpy_rows<4 * t0, EL, E, M>(A[j], low[j], LS, x1, -c1);
                     });
                 }
             }
@@ -385,129 +450,161 @@ __global__ __launch_bounds__(64 * Cols<T>::NW) void k_small(const CubeDesc* __re
     if (d.mode & 2) {
         // ------------------------------------------------------- whitened Gram
         if (wave < W) {
+            double sn[NC];
+#pragma unroll
+            for (int j = 0; j < NC; ++j) sn[j] = s_sig[clampc[j]];
+            load_columns();
             static_for<NC * E>([&](auto x) {
                 constexpr int j = decltype(x)::value / E, e = decltype(x)::value % E;
                 const int i = 4 * e + g, n = col[j];
-                A[j][e] = i < p && n >= 0 && n < p ? G[(int64_t)i * p + n] / (s_sig[i] * s_sig[n]) : 0.0;
+                double v;
+                if constexpr (e < EL) v = low[j][e * LS];
+                else v = A[j][e - EL];
+                v = i < p && n >= 0 && n < p ? v / (s_sig[i] * sn[j]) : 0.0;
+                if constexpr (e < EL) low[j][e * LS] = v;
+                else A[j][e - EL] = v;
             });
         }
-        for (int i = t; i < 4 * SP; i += NTH) s_row[0][0][i] = s_row[1][0][i] = 0.0;
         __syncthreads();
 
         // ------------------------------------------------ tridiagonalisation
         // Step k, x the entries of row k beyond the diagonal: v = x - alpha e_{k+1},
         // u = beta A v, A <- A - v w^T - w v^T with w = u - K v, K = (beta / 2) u^T v, that
         // is A_in -= v_i (u_n - 2 K v_n) + u_i v_n.  A v = A x - alpha A e_{k+1}: the
-        // products with x do not wait for the norm that gives alpha.
+        // products with x do not wait for the norm that gives alpha.  One barrier a
+        // step: the waves publish A v and row k + 1 before the update, and every wave
+        // forms the next x from them (in row layout, and for its own columns).
+        double xr[M], xo[NC];
+        static_for<NC>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
+            const double v = pick<0, 1, EL, E>(A[j], low[j], LS, 0);
+            if (col[j] >= 0 && g == 0) {
+                s_u[own[j]] = col[j] > 0 ? v : 0.0;
+                if (col[j] == 0) s_dd[0] = v;
+            }
+        });
+        __syncthreads();
+#pragma unroll
+        for (int m = 0; m < M; ++m) xr[m] = s_u[g * SP + 16 * m + c];
+#pragma unroll
+        for (int j = 0; j < NC; ++j) xo[j] = s_u[own[j]];
         static_for<T>([&](auto tc) {
-            constexpr int t0 = decltype(tc)::value, m0 = t0 / 4;
+            constexpr int t0 = decltype(tc)::value, m0 = t0 / 4, mn = (t0 + 1) / 4 < M ? (t0 + 1) / 4 : m0;
+#pragma unroll 1
             for (int kk = 0; kk < 16; ++kk) {
                 const int k = 16 * t0 + kk;
                 if (k >= p - 2) break;
-                double* xs = s_row[k & 1][0];
+                double* su = s_row[k & 1][0];
+                double* sa = s_row[k & 1][1];
                 bool act[NC], any = false;
-                static_for<NC>([&](auto jc) {
-                    constexpr int j = decltype(jc)::value;
+#pragma unroll
+                for (int j = 0; j < NC; ++j) {
                     const int tile = wave + W * j;
-                    const bool has = wave < W && tile < T;
-                    act[j] = has && tile >= t0;
+                    act[j] = wave < W && tile < T && tile >= t0;
                     any |= act[j];
-                    // row k; zeros up to the diagonal (the tile before t0 clears its last entry)
-                    if (has && tile >= t0 - 1) {
-                        const double v = pick<4 * t0, 4>(A[j], kk >> 2);
-                        if (g == (kk & 3)) {
-                            xs[own[j]] = col[j] > k ? v : 0.0;
-                            if (col[j] == k) s_dd[k] = v;
-                        }
-                    }
-                });
-                __syncthreads();
-                double xr[M], u[NC], v[NC], alpha = 0.0, beta = 0.0;
+                }
+                double y[NC], v[NC], v1 = 0.0, alpha = 0.0, beta = 0.0;
                 if (any) {
                     double ss = 0.0;
 #pragma unroll
-                    for (int m = m0; m < M; ++m) {
-                        xr[m] = xs[g * SP + 16 * m + c];
-                        ss = fma(xr[m], xr[m], ss);
-                    }
-                    const double x1 = xs[slot_of<T>(k + 1)];
-                    double y[NC];
+                    for (int m = m0; m < M; ++m) ss = fma(xr[m], xr[m], ss);
+                    ss = wave_total(ss);
+                    // entry k + 1 of x, in the lane and register of its row
+                    const int l1 = ((k + 1) & 3) * 16 + (((k + 1) >> 2) & 15);
+                    const double x1 = readlane_f64(kk == 15 ? xr[mn] : xr[m0], l1);
+                    double a1[NC];
                     static_for<NC>([&](auto jc) {
                         constexpr int j = decltype(jc)::value;
-                        y[j] = 0.0;
+                        y[j] = a1[j] = 0.0;
                         if (act[j]) {
+                            a1[j] = pick<4 * t0, 5, EL, E>(A[j], low[j], LS, (kk + 1) >> 2);
                             double q[4] = {0.0, 0.0, 0.0, 0.0};
-                            dot_rows<4 * t0, E, M>(A[j], xr, q);
+                            dot_rows<4 * t0, EL, E, M>(A[j], low[j], LS, xr, q);
                             y[j] = (q[0] + q[1]) + (q[2] + q[3]);
                         }
                     });
-                    ss = rows_sum(row16_sum(ss));
-                    const double nrm = sqrt(ss);
+                    const bool some = ss > 1e-200;       // else the row is taken as tridiagonal already
+                    const double nr = root(fmax(ss, 1e-200)), nrm = some ? nr : 0.0;
                     alpha = x1 >= 0.0 ? -nrm : nrm;
-                    const double vtv = 2.0 * alpha * (alpha - x1);
-                    beta = vtv > 0.0 ? 2.0 / vtv : 0.0;
-                    const double v1 = x1 - alpha;
-                    // v in place of x: the lane that holds entry k + 1
-                    {
-                        const bool mine = lane == ((k + 1) & 3) * 16 + (((k + 1) >> 2) & 15);
-                        if ((t0 & 3) == 3 && t0 + 1 < T && kk == 15) {
-                            constexpr int m1 = m0 + 1 < M ? m0 + 1 : m0;
-                            xr[m1] = mine ? v1 : xr[m1];
-                        } else {
-                            xr[m0] = mine ? v1 : xr[m0];
-                        }
-                    }
+                    const double b = recip(nr * (nr + fabs(x1)));     // 2 / v^T v
+                    beta = some ? b : 0.0;
+                    v1 = x1 - alpha;
                     const bool row1 = g == ((kk + 1) & 3);
-                    double q = 0.0;
                     static_for<NC>([&](auto jc) {
                         constexpr int j = decltype(jc)::value;
-                        u[j] = v[j] = 0.0;
+                        v[j] = 0.0;
                         if (act[j]) {
-                            const double a1 = pick<4 * t0, 5>(A[j], (kk + 1) >> 2);
-                            y[j] = rows_sum(row1 ? fma(-alpha, a1, y[j]) : y[j]);
-                            v[j] = col[j] == k + 1 ? v1 : xs[own[j]];
-                            q = fma(v[j], y[j], q);
-                            u[j] = beta * y[j];
-                            if (g == 0) s_u[own[j]] = u[j];
-                            if (g == 1 && col[j] > k && col[j] < p) d.hv[(int64_t)k * p + col[j]] = v[j];
+                            y[j] = rows_sum(row1 ? fma(-alpha, a1[j], y[j]) : y[j]);
+                            v[j] = col[j] == k + 1 ? v1 : xo[j];
+                            if (row1) {
+                                su[own[j]] = y[j];
+                                sa[own[j]] = a1[j];
+                            }
                         }
                     });
-                    q = row16_sum(q);
-                    if (lane == 0) s_vav[wave] = q;
-                    if (col[0] == 16 * t0 + c || (NC == 2 && col[NC - 1] == 16 * t0 + c)) {   // the wave of tile t0
-                        if (lane == 0) {
-                            s_ee[k] = alpha;
-                            s_hb[k] = beta;
-                        }
-                    }
+                    if (kk == 15) xr[mn] = lane == l1 ? v1 : xr[mn];      // v in place of x
+                    else xr[m0] = lane == l1 ? v1 : xr[m0];
                 }
-                __syncthreads();
+                lds_barrier();
                 if (any) {
-                    double vav = 0.0;
+                    double yr[M], xn[M], q = 0.0;        // A v and row k + 1 in row layout
+                    const double y1 = su[slot_of<T>(k + 1)];
 #pragma unroll
-                    for (int w = 0; w < W; ++w)
-                        if (w >= t0 || (NC == 2 && w + W < T && w + W >= t0)) vav += s_vav[w];
-                    const double K2 = beta * (beta * vav);
-                    double ur[M];
+                    for (int m = m0; m < M; ++m) {
+                        yr[m] = su[g * SP + 16 * m + c];
+                        xn[m] = sa[g * SP + 16 * m + c];
+                    }
 #pragma unroll
-                    for (int m = m0; m < M; ++m) ur[m] = s_u[g * SP + 16 * m + c];
+                    for (int m = m0; m < M; ++m) {
+                        // rows up to k hold what their waves left there
+                        yr[m] = beta * yr[m];
+                        q = fma(xr[m], yr[m], q);
+                    }
+                    q = wave_total(q);                   // beta v^T A v
+                    const double u1 = beta * y1;
+                    double u[NC];
                     static_for<NC>([&](auto jc) {
                         constexpr int j = decltype(jc)::value;
                         if (act[j]) {
-                            axpy_rows<4 * t0, E, M>(A[j], xr, fma(K2, v[j], -u[j]));
-                            axpy_rows<4 * t0, E, M>(A[j], ur, -v[j]);
+                            u[j] = beta * y[j];
+                            if (g == 1 && col[j] < p) hv[(uint32_t)(k * p + col[j])] = v[j];
+                            axpy_rows<4 * t0, EL, E, M>(A[j], low[j], LS, yr, -v[j]);
                         }
                     });
+                    if (lane == 0) {
+                        s_ee[k] = alpha;                 // the same value from every wave
+                        s_hb[k] = beta;
+                    }
+                    const double K2 = beta * q;
+                    // row k + 1 after the update
+#pragma unroll
+                    for (int m = m0; m < M; ++m) {
+                        const int i = 4 * (16 * m + c) + g;
+                        const double nx = fma(-u1, xr[m], fma(-v1, fma(-K2, xr[m], yr[m]), xn[m]));
+                        xn[m] = i > k + 1 ? nx : 0.0;
+                    }
+                    static_for<NC>([&](auto jc) {
+                        constexpr int j = decltype(jc)::value;
+                        if (act[j]) {
+                            const double z = fma(-K2, v[j], u[j]);
+                            const double nx = fma(-u1, v[j], fma(-v1, z, sa[own[j]]));
+                            if (col[j] == k + 1) s_dd[k + 1] = nx;
+                            xo[j] = col[j] > k + 1 ? nx : 0.0;
+                            axpy_rows<4 * t0, EL, E, M>(A[j], low[j], LS, xr, -z);
+                        }
+                    });
+#pragma unroll
+                    for (int m = m0; m < M; ++m) xr[m] = xn[m];
                 }
             }
         });
         __syncthreads();
-        constexpr int EL = E > 8 ? 8 : E;                // rows of the last two tiles
-        static_for<NC * EL>([&](auto x) {
-            constexpr int j = decltype(x)::value / EL, e = E - EL + decltype(x)::value % EL;
+        constexpr int EE = E > 8 ? 8 : E;                // rows of the last two tiles
+        static_for<NC * EE>([&](auto x) {
+            constexpr int j = decltype(x)::value / EE, e = E - EE + decltype(x)::value % EE;
             const int i = 4 * e + g, n = col[j];
-            if (i == n && i >= p - 2 && i < p) s_dd[i] = A[j][e];
-            if (i == p - 1 && n == p - 2) s_ee[p - 2] = A[j][e];
+            if (i == n && i >= p - 2 && i < p) s_dd[i] = A[j][e - EL];
+            if (i == p - 1 && n == p - 2) s_ee[p - 2] = A[j][e - EL];
         });
         __syncthreads();
 
@@ -531,18 +628,22 @@ __global__ __launch_bounds__(64 * Cols<T>::NW) void k_small(const CubeDesc* __re
         __syncthreads();
         const double gmax = s_red[0];
         const double sc = 1.0 / gmax;
-        for (int i = t; i < PL + 16; i += NTH) {
+        double dv[T], ev2[T];                            // scaled d_i and e_{i-1}^2 of i = 16 b + c
+#pragma unroll
+        for (int b = 0; b < T; ++b) {
+            const int i = 16 * b + c;
             const double es = i > 0 && i < p ? s_ee[i - 1] * sc : 0.0;
-            s_de[i] = make_double2(i < p ? s_dd[i] * sc : 0.0, es * es);
+            dv[b] = i < p ? s_dd[i] * sc : 3.0;
+            ev2[b] = es * es;
         }
-        __syncthreads();
         // Multisection: M lanes per eigenvalue evaluate the Sturm count at M
         // interior points, shrinking the bracket M+1 times per iteration.
         // Only the top r+1 eigenvalues are needed by the solve; all p are
         // computed when requested.
         {
             const int nev = (d.mode & 16) ? p : (r + 1 < p ? r + 1 : p);
-            const int M = nev * 64 <= NTH ? 64 : (nev * 16 <= 2 * NTH ? 16 : 4);
+            // one wave per SIMD counts as fast as one wave alone
+            const int M = nev * 64 <= 256 ? 64 : (nev * 16 <= 2 * NTH ? 16 : 4);
             const int iters = M == 64 ? 9 : (M == 16 ? 14 : 24);
             const double inv_m1 = 1.0 / (double)(M + 1);
             const int m = t % M;
@@ -554,7 +655,7 @@ __global__ __launch_bounds__(64 * Cols<T>::NW) void k_small(const CubeDesc* __re
                     double lo = -1.0 - 1e-12, hi = 1.0 + 1e-12;
                     for (int it = 0; it < iters; ++it) {
                         const double x = lo + (hi - lo) * ((double)(m + 1) * inv_m1);
-                        const int cnt = sturm_count(s_de, p, x);
+                        const int cnt = sturm_count<T>(dv, ev2, x);
                         const bool below = cnt <= midx;   // x <= lambda
                         double lo_c = below ? x : lo;
                         double hi_c = below ? hi : x;
@@ -764,54 +865,123 @@ __global__ __launch_bounds__(64 * Cols<T>::NW) void k_small(const CubeDesc* __re
 
         HYRES_STAMP(d, 5);
         // -------------------------- back-transformation v = H_0 ... H_{p-3} z
-        // Reflectors are staged from global memory into LDS eight at a time by
-        // the whole block (coalesced), then applied by the waves owning vectors.
+        // On the FP64 matrix cores, sixteen reflectors at a time: a wave holds the
+        // rows of one or two tiles of the vectors as accumulators (16 rows x 16
+        // vectors, which is also the B operand of a product over those rows).
+        // With S = H z and the products H H^T of the sixteen (summed over the
+        // waves through LDS), the j-th of them multiplies its reflector by
+        // t_j = hb_j (S_j - sum_{i<j} (h_j^T h_i) t_i), a substitution that every wave
+        // does for itself, and z -= H^T t.  One at a time, a wave sum on the chain of
+        // each reflector, it took 31 us at p = 144.
         {
-            constexpr int RB = 8;
-            constexpr int SPT = (RB * PL + NTH - 1) / NTH;   // staged entries per thread
-            double* stage = s_zL;                       // free now: RB x PL doubles
-            // the next group's reflectors are read into registers while the
-            // current group is applied
-            double nxt[SPT];
-            auto fetch = [&](int k1) {
-                const int k0 = k1 - RB + 1 < 0 ? 0 : k1 - RB + 1;
+            constexpr int TPW = (T + NW - 1) / NW;
+            constexpr int NP = T < NW ? T : NW;          // waves that hold tiles
+            double* part = s_pool;                       // [wave][S, H H^T][element][lane]
+            static_assert(NP * 512 <= 2 * PL * kMaxRank, "below the vectors");
 #pragma unroll
-                for (int j = 0; j < SPT; ++j) {
-                    const int e = t + j * NTH;
-                    const int kk = k1 - e / PL, i = e % PL;
-                    nxt[j] = (e < RB * PL && kk >= k0 && i > kk && i < p) ? d.hv[(int64_t)kk * p + i] : 0.0;
+            for (int v = 0; v < VPW; ++v) {
+                const int gv = wave + NW * v;
+                if (gv < r) {
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) s_z[gv][lane + 64 * q] = zr[v][q];
                 }
-            };
-            if (p - 3 >= 0) fetch(p - 3);
-            for (int k1 = p - 3; k1 >= 0; k1 -= RB) {
-                const int k0 = k1 - RB + 1 < 0 ? 0 : k1 - RB + 1;
-                __syncthreads();
+            }
+            __syncthreads();
+            v4d Z[TPW];
+            double ha[TPW][4], ht[TPW][4], na[TPW][4], nt[TPW][4];
 #pragma unroll
-                for (int j = 0; j < SPT; ++j) {
-                    const int e = t + j * NTH;
-                    if (e < RB * PL) stage[e] = nxt[j];
+            for (int q = 0; q < TPW; ++q)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int i = 16 * (wave + NW * q) + g + 4 * v;
+                    Z[q][v] = c < r && i < p ? s_z[c < r ? c : 0][i < p ? i : 0] : 0.0;
                 }
-                __syncthreads();
-                if (k1 - RB >= 0) fetch(k1 - RB);
-                if (wave < r) {
-                    for (int k = k1; k >= k0; --k) {
-                        const double* hk = stage + (k1 - k) * PL;
-                        double h[Q];
+            // reflectors k1, k1 - 1, ... k1 - 15 on this wave's rows, by (reflector
+            // lane, row) and by (row lane, reflector); entries outside the reflector
+            // are read at 0 and cleared at their use, a group later
+            auto inside = [&](int k, int i) { return k >= 0 && i > k && i < p; };
+            auto entry = [&](int k, int i) { return hv[inside(k, i) ? (uint32_t)(k * p + i) : 0u]; };
+            auto fetch = [&](int k1, double (&a)[TPW][4], double (&h)[TPW][4]) {
 #pragma unroll
-                        for (int q = 0; q < Q; ++q) h[q] = hk[lane + 64 * q];
-                        const double hb = s_hb[k];
+                for (int q = 0; q < TPW; ++q)
 #pragma unroll
-                        for (int v = 0; v < VPW; ++v) {
-                            if (wave + NW * v < r) {
-                                double sdot = 0.0;
-#pragma unroll
-                                for (int q = 0; q < Q; ++q) sdot = fma(h[q], zr[v][q], sdot);
-                                sdot = wave_sum(sdot) * hb;
-#pragma unroll
-                                for (int q = 0; q < Q; ++q) zr[v][q] = fma(-sdot, h[q], zr[v][q]);
-                            }
-                        }
+                    for (int e = 0; e < 4; ++e) {
+                        const int i0 = 16 * (wave + NW * q);
+                        a[q][e] = entry(k1 - c, i0 + 4 * e + g);
+                        h[q][e] = entry(k1 - 4 * e - g, i0 + c);
                     }
+            };
+            if (p >= 3) fetch(p - 3, ha, ht);
+#pragma unroll 1
+            for (int k1 = p - 3; k1 >= 0; k1 -= 16) {
+                if (k1 >= 16) fetch(k1 - 16, na, nt);
+                v4d S = {0.0, 0.0, 0.0, 0.0}, R = S;
+#pragma unroll
+                for (int q = 0; q < TPW; ++q)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const double h = inside(k1 - c, 16 * (wave + NW * q) + 4 * e + g) ? ha[q][e] : 0.0;
+                        S = mfma4d(h, Z[q][e], S);
+                        R = mfma4d(h, h, R);
+                    }
+                if (wave < NP) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        part[wave * 512 + e * 64 + lane] = S[e];
+                        part[wave * 512 + 256 + e * 64 + lane] = R[e];
+                    }
+                }
+                lds_barrier();
+                for (int e = t; e < 512; e += NTH) {
+                    double x = 0.0;
+#pragma unroll
+                    for (int w = 0; w < NP; ++w) x += part[w * 512 + e];
+                    part[e] = x;
+                }
+                lds_barrier();
+                double acc[16], tb[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int j = 0; j < 16; ++j) acc[j] = part[16 * j + c];
+                static_for<16>([&](auto ic) {
+                    constexpr int i = decltype(ic)::value, b0 = (i + 1) / 4 * 4;
+                    const double hb = k1 - i >= 0 ? s_hb[k1 - i < 0 ? 0 : k1 - i] : 0.0;
+                    const double ti = -hb * acc[i];
+                    const double row = part[256 + 16 * i + c];
+                    if constexpr (16 - b0 == 16) axpy_block<0, 0, 16>(acc, row, ti);
+                    if constexpr (16 - b0 == 12) axpy_block<4, 4, 4>(acc, row, ti);
+                    if constexpr (16 - b0 == 12 || 16 - b0 == 8) axpy_block<8, 8, 8>(acc, row, ti);
+                    if constexpr (16 - b0 == 4) axpy_block<12, 12, 4>(acc, row, ti);
+                    tb[i / 4] = g == i % 4 ? ti : tb[i / 4];
+                });
+#pragma unroll
+                for (int q = 0; q < TPW; ++q)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const bool in = inside(k1 - 4 * e - g, 16 * (wave + NW * q) + c);
+                        Z[q] = mfma4d(in ? ht[q][e] : 0.0, tb[e], Z[q]);
+                        ha[q][e] = na[q][e];
+                    }
+#pragma unroll
+                for (int q = 0; q < TPW; ++q)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) ht[q][e] = nt[q][e];
+                lds_barrier();
+            }
+#pragma unroll
+            for (int q = 0; q < TPW; ++q)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int i = 16 * (wave + NW * q) + g + 4 * v;
+                    if (c < r && i < p) s_z[c][i] = Z[q][v];
+                }
+            __syncthreads();
+#pragma unroll
+            for (int v = 0; v < VPW; ++v) {
+                const int gv = wave + NW * v;
+#pragma unroll
+                for (int q = 0; q < Q; ++q) {
+                    const int i = lane + 64 * q;
+                    zr[v][q] = gv < r && i < p ? s_z[gv][i] : 0.0;
                 }
             }
         }
