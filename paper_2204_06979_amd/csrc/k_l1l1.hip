@@ -56,8 +56,8 @@ __global__ __launch_bounds__(64) void k_l1l1(L1Args a, int64_t groups) {
     constexpr int PPB = 64 / S;                 // pixels per block
     constexpr int NI = 2 * (S - 1);             // interface unknowns
     __shared__ T s_h[M][64];                    // h, band-major (lane-private columns)
-    __shared__ T s_inv[S][M], s_f[S][M];        // block Thomas: 1 / beta_i and -e / beta_i = mu2 / beta_i
-    __shared__ T s_wr[S][M], s_wl[S][M];        // spikes of the last / first row coupling
+    __shared__ __align__(16) T s_f[S][M];       // block Thomas: -e / beta_i = mu2 / beta_i (0 beyond the cube)
+    __shared__ __align__(16) T s_wr[S][M], s_wl[S][M];   // spikes of the last / first row coupling
     __shared__ T s_r[NI > 0 ? NI : 1][NI > 0 ? NI : 1];   // inverse of the interface system
     __shared__ double s_tip[S][2][2];           // spike values at the ends of each block [s][wr/wl][first/last]
     __shared__ double s_beta[S][M], s_w[S][M];  // FP64 pivots and a spike being formed
@@ -69,7 +69,8 @@ __global__ __launch_bounds__(64) void k_l1l1(L1Args a, int64_t groups) {
         const int l = p - seg * M;
         return l < 0 ? 0 : (l > M ? M : l);
     }();
-    const double mu1 = a.mu1, mu2 = a.mu2;
+    // (a mu1 / mu2 beyond 1e30 changes no result: x = a then)
+    const double mu2 = a.mu2, mu1 = a.mu1 < 1e30 * mu2 ? a.mu1 : 1e30 * mu2;
 
     // ---------------------------------------------------------- block tables
     // Factors of each diagonal block of M = mu1 I + mu2 D^T D and its spikes
@@ -86,9 +87,7 @@ __global__ __launch_bounds__(64) void k_l1l1(L1Args a, int64_t groups) {
             s_beta[s][i] = i == 0 ? dg : dg - e * e / s_beta[s][i - 1];
         }
         for (int i = 0; i < M; ++i) {
-            s_inv[s][i] = i < L ? (T)(1.0 / s_beta[s][i]) : (T)0;
-            // the last row of a block does not couple forward inside the block
-            s_f[s][i] = i < L - 1 ? (T)(mu2 / s_beta[s][i]) : (T)0;
+            s_f[s][i] = i < L ? (T)(mu2 / s_beta[s][i]) : (T)0;
             s_wr[s][i] = (T)0;
             s_wl[s][i] = (T)0;
         }
@@ -144,8 +143,8 @@ __global__ __launch_bounds__(64) void k_l1l1(L1Args a, int64_t groups) {
         __syncthreads();
     }
 
-    const T t1 = (T)(1.0 / mu1), t2 = (T)(a.lam / mu2);
-    const T m1 = (T)mu1, m2 = (T)mu2;
+    const T t1 = (T)(1.0 / a.mu1), t2 = (T)(a.lam / mu2);
+    const T rho = (T)(mu1 / mu2);
     // rows of D this lane owns: every band but the cube's last; the last band
     // of a block before a boundary uses the next block's first x
     const int vlen = seg < S - 1 ? M : lenS - 1;
@@ -178,10 +177,10 @@ __global__ __launch_bounds__(64) void k_l1l1(L1Args a, int64_t groups) {
             constexpr bool FIRST = decltype(first_c)::value;
             const int z0 = opaque_zero();
             const T* hcol = &s_h[0][lane + z0];
-            const T* tinv = &s_inv[seg][z0];
-            const T* tf = &s_f[seg][z0];
-            const T* twr = &s_wr[seg][z0];
-            const T* twl = &s_wl[seg][z0];
+            // (rows of a multiple of four entries: four to a read)
+            const T* tf = static_cast<const T*>(__builtin_assume_aligned(&s_f[seg][z0], 16));
+            const T* twr = static_cast<const T*>(__builtin_assume_aligned(&s_wr[seg][z0], 16));
+            const T* twl = static_cast<const T*>(__builtin_assume_aligned(&s_wl[seg][z0], 16));
             T xn = (T)0, cprev = (T)0;
             if constexpr (S > 1 && !FIRST) {
                 // x across the boundaries: the next block's first, the previous block's last
@@ -195,7 +194,7 @@ __global__ __launch_bounds__(64) void k_l1l1(L1Args a, int64_t groups) {
                     cprev = fma((T)-2, nb, v);
                 }
             }
-            T zprev = (T)0;
+            T w = cprev;                         // z + c of the band before
 #pragma unroll
             for (int i = 0; i < M; ++i) {
                 const T hi = hcol[i * 64];
@@ -204,22 +203,22 @@ __global__ __launch_bounds__(64) void k_l1l1(L1Args a, int64_t groups) {
                     a1 = hi;
                     c = (T)0;
                 } else {
-                    const T t = (hi - x[i]) + b1[i];
-                    const T nb1 = clip(t, t1);
-                    a1 = fma((T)2, nb1, hi - t);
+                    const T d = x[i] - b1[i];
+                    const T nb1 = clip(hi - d, t1);
+                    a1 = fma((T)2, nb1, d);
                     b1[i] = nb1;
                     const T xnext = i + 1 < M ? x[i + 1] : xn;
                     const T v = (xnext - x[i]) + b2[i];
                     const T nb2 = clip(v, t2);
-                    const bool has = i < vlen;
-                    c = has ? fma((T)-2, nb2, v) : (T)0;
-                    b2[i] = has ? nb2 : (T)0;
+                    b2[i] = nb2;
+                    c = fma((T)-2, nb2, v);
+                    // rows of D end within the last 4 S bands of a segment (M is
+                    // p / S rounded up to a multiple of four)
+                    if (i >= M - 4 * S) c = i < vlen ? c : (T)0;
                 }
-                const T rhs = fma(m1, a1, m2 * (cprev - c));
-                const T z = fma(m2, zprev, rhs) * tinv[i];
+                const T z = (fma(rho, a1, w) - c) * tf[i];
                 x[i] = z;
-                zprev = z;
-                cprev = c;
+                w = z + c;
             }
 #pragma unroll
             for (int i = M - 2; i >= 0; --i) x[i] = fma(tf[i], x[i + 1], x[i]);
@@ -242,8 +241,15 @@ __global__ __launch_bounds__(64) void k_l1l1(L1Args a, int64_t groups) {
                 }
                 xr = seg < S - 1 ? xr : (T)0;
                 xl = seg > 0 ? xl : (T)0;
+                if constexpr (S == 2) {          // one boundary per block
+                    const T xs = seg ? xl : xr;
+                    const T* tw = seg ? twl : twr;
 #pragma unroll
-                for (int i = 0; i < M; ++i) x[i] = fma(-xr, twr[i], fma(-xl, twl[i], x[i]));
+                    for (int i = 0; i < M; ++i) x[i] = fma(-xs, tw[i], x[i]);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < M; ++i) x[i] = fma(-xr, twr[i], fma(-xl, twl[i], x[i]));
+                }
             }
         };
         sweep(std::integral_constant<bool, true>{});
@@ -259,9 +265,9 @@ __global__ __launch_bounds__(64) void k_l1l1(L1Args a, int64_t groups) {
 }
 
 // Lanes per pixel and segment length for p bands: segments of at most 64
-// (FP32) or 32/48/56 (FP64) bands in registers, every segment non-empty.
+// (FP32) or 32/48/56 (FP64) bands in registers, a multiple of four (the
+// segments' padding is work), every segment non-empty.
 bool l1l1_shape(int p, int dtype, int* S, int* M) {
-    auto up8 = [](int v) { return (v + 7) / 8 * 8; };
     int s, m;
     if (dtype == HYRES_F32) {
         if (p <= 64) s = 1;
@@ -272,11 +278,24 @@ bool l1l1_shape(int p, int dtype, int* S, int* M) {
         else if (p <= 96) s = 2;
         else s = 4;
     }
-    m = up8((p + s - 1) / s);
+    m = ((p + s - 1) / s + 3) / 4 * 4;
     if (p < 1 || p > kMaxBands || m > kL1MaxSeg || (s - 1) * m >= p) return false;
     *S = s;
     *M = m;
     return true;
+}
+
+// k_l1l1<T, M, S> for the M of l1l1_shape, LO..HI in steps of four.
+template <typename T, int S, int LO, int HI>
+static hipError_t launch_l1l1_m(int M, const L1Args& a, int grid, int64_t groups, hipStream_t st) {
+    if constexpr (LO <= HI) {
+        if (M == LO) {
+            hipLaunchKernelGGL((k_l1l1<T, LO, S>), dim3(grid), dim3(64), 0, st, a, groups);
+            return hipGetLastError();
+        }
+        return launch_l1l1_m<T, S, LO + 4, HI>(M, a, grid, groups, st);
+    }
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_l1l1(const L1Args& a, int num_cu, hipStream_t st) {
@@ -287,23 +306,14 @@ hipError_t launch_l1l1(const L1Args& a, int num_cu, hipStream_t st) {
     const int64_t cap = (int64_t)num_cu * 16;
     const int grid = (int)(groups < cap ? groups : cap);
     if (grid < 1) return hipSuccess;
-#define HYRES_L1(T, MM, SS) \
-    if (M == MM && S == SS) { \
-        hipLaunchKernelGGL((k_l1l1<T, MM, SS>), dim3(grid), dim3(64), 0, st, a, groups); \
-        return hipGetLastError(); \
-    }
     if (a.dtype == HYRES_F32) {
-        HYRES_L1(float, 8, 1) HYRES_L1(float, 16, 1) HYRES_L1(float, 24, 1) HYRES_L1(float, 32, 1)
-        HYRES_L1(float, 40, 1) HYRES_L1(float, 48, 1) HYRES_L1(float, 56, 1) HYRES_L1(float, 64, 1)
-        HYRES_L1(float, 40, 2) HYRES_L1(float, 48, 2) HYRES_L1(float, 56, 2) HYRES_L1(float, 64, 2)
-        HYRES_L1(float, 40, 4) HYRES_L1(float, 48, 4) HYRES_L1(float, 56, 4)
-    } else {
-        HYRES_L1(double, 8, 1) HYRES_L1(double, 16, 1) HYRES_L1(double, 24, 1) HYRES_L1(double, 32, 1)
-        HYRES_L1(double, 24, 2) HYRES_L1(double, 32, 2) HYRES_L1(double, 40, 2) HYRES_L1(double, 48, 2)
-        HYRES_L1(double, 32, 4) HYRES_L1(double, 40, 4) HYRES_L1(double, 48, 4) HYRES_L1(double, 56, 4)
+        if (S == 1) return launch_l1l1_m<float, 1, 4, 64>(M, a, grid, groups, st);
+        if (S == 2) return launch_l1l1_m<float, 2, 36, 64>(M, a, grid, groups, st);
+        return launch_l1l1_m<float, 4, 36, 56>(M, a, grid, groups, st);
     }
-#undef HYRES_L1
-    return hipErrorInvalidValue;
+    if (S == 1) return launch_l1l1_m<double, 1, 4, 32>(M, a, grid, groups, st);
+    if (S == 2) return launch_l1l1_m<double, 2, 20, 48>(M, a, grid, groups, st);
+    return launch_l1l1_m<double, 4, 28, 56>(M, a, grid, groups, st);
 }
 
 }  // namespace hyres
