@@ -206,6 +206,7 @@ inline int64_t rup(int64_t a, int64_t b) { return cdiv(a, b) * b; }
 // Geometry and workspace layout of one cube.
 struct CubePlan {
     int H = 0, W = 0, p = 0, r = 0, L = 0, dtype = 0, scope = 0, T = 0, gslots = 1, precision = 0;
+    int64_t gper = 2048;                 // pixels of an FP32 Gram slot, at least
     int64_t n = 0, nz = 0, nc = 0, ncs = 0, tps = 0, tmp_off2 = 0, ll_off = 0;
     int lh[kMaxLevels + 1] = {0}, lw[kMaxLevels + 1] = {0};
     int64_t loff[kMaxLevels + 1] = {0};
@@ -251,7 +252,7 @@ void plan_cube(CubePlan& c, Layout& lay, int parts) {
             gpart_in_coef = (parts & P_IMG) && (size_t)c.r * rup(c.nc, 64) * 8 >= need;
             if (!gpart_in_coef) c.o_gpart = lay.add(need);
         } else {
-            c.gslots = (int)std::max<int64_t>(1, std::min<int64_t>(256, cdiv(c.n, 2048)));
+            c.gslots = (int)std::max<int64_t>(1, std::min<int64_t>(256, cdiv(c.n, c.gper)));
             c.o_gpart = lay.add((size_t)c.T * (c.T + 1) / 2 * 256 * 4 * c.gslots);
         }
         c.o_G = lay.add((size_t)c.p * c.p * 8);
@@ -1779,8 +1780,6 @@ struct ForpdnPlan {
     size_t total = 0;
 };
 
-uint32_t pmag_of(int p) { return (uint32_t)(0xffffffffu / (uint32_t)p) + 1u; }
-
 hyres_status plan_forpdn(ForpdnPlan& f, hyres_handle* h, int H, int W, int p, int L, int dtype, bool need_noise) {
     if (!valid_dtype(dtype)) return HYRES_E_DTYPE;
     if (p < 2 || p > kMaxBands) return HYRES_E_SHAPE;
@@ -1810,8 +1809,13 @@ hyres_status plan_forpdn(ForpdnPlan& f, hyres_handle* h, int H, int W, int p, in
     g.dtype = dtype;
     g.precision = HYRES_PREC_NATIVE;
     g.plan.resize(f.G);
+    // 256 slots over all groups, one per compute unit: the largest group's 244 of
+    // 2048 positions and the others' 82 took a second round of the chip
+    // (349 x 1905 x 144: 264 us, 184 now)
+    const int64_t per = std::max<int64_t>(2048, rup(cdiv(f.nc, 256 - f.G), 64));
     for (int j = 0; j < f.G; ++j) {
         CubePlan& c = g.plan[j];
+        c.gper = per;
         c.H = j < L ? 3 * f.lh[j + 1] : f.lh[L];
         c.W = j < L ? f.lw[j + 1] : f.lw[L];
         c.p = p; c.r = 1; c.L = 0; c.dtype = dtype; c.scope = 0; c.precision = HYRES_PREC_NATIVE;
@@ -1880,7 +1884,6 @@ HYRES_API hyres_status hyres_forpdn(hyres_handle* h, const void* Y, int H, int W
     }
     // F2: analysis, level by level (the first divides by sigma on load);
     // LL_l (l < L) in tmp[(l - 1) & 1], LL_L in the coefficients
-    const uint32_t pm = pmag_of(p);
     for (int l = 1; l <= levels; ++l) {
         VLevel a{};
         if (l == 1) {
@@ -1891,7 +1894,7 @@ HYRES_API hyres_status hyres_forpdn(hyres_handle* h, const void* Y, int H, int W
         a.scale = l == 1 ? sg : nullptr;
         a.ll = l == levels ? coef + (size_t)f.ll_off * p * es : tmp[(l - 1) & 1];
         a.det = coef + (size_t)f.loff[l] * p * es;
-        a.Hin = f.lh[l - 1]; a.Win = f.lw[l - 1]; a.h = f.lh[l]; a.w = f.lw[l]; a.p = p; a.pmag = pm;
+        a.Hin = f.lh[l - 1]; a.Win = f.lw[l - 1]; a.h = f.lh[l]; a.w = f.lw[l]; a.p = p;
         if (launch_vdwt_level(dtype, a, h->num_cu, s) != hipSuccess) return HYRES_E_HIP;
     }
     // F5: band Gram of every group, then the thresholds
@@ -1931,7 +1934,6 @@ HYRES_API hyres_status hyres_forpdn(hyres_handle* h, const void* Y, int H, int W
         ff.lambda = lambda;
         ff.p = p;
         ff.groups = f.G;
-        ff.pmag = pm;
         if (launch_forpdn_filter(dtype, ff, h->num_cu, s) != hipSuccess) return HYRES_E_HIP;
     }
     // F6: synthesis, coarsest level first; the last level writes X times sigma
@@ -1945,7 +1947,7 @@ HYRES_API hyres_status hyres_forpdn(hyres_handle* h, const void* Y, int H, int W
             a.out = tmp[(l - 2) & 1]; a.op = p; a.orow = (int64_t)f.lw[l - 1] * p;
         }
         a.scale = l == 1 ? sg : nullptr;
-        a.Hin = f.lh[l - 1]; a.Win = f.lw[l - 1]; a.h = f.lh[l]; a.w = f.lw[l]; a.p = p; a.pmag = pm;
+        a.Hin = f.lh[l - 1]; a.Win = f.lw[l - 1]; a.h = f.lh[l]; a.w = f.lw[l]; a.p = p;
         if (launch_vidwt_level(dtype, a, h->num_cu, s) != hipSuccess) return HYRES_E_HIP;
     }
     return HYRES_OK;

@@ -17,7 +17,6 @@ constexpr int kSureMaxChunks = 64;    // chunks per component of the threshold s
 constexpr int64_t kSureDirect = 65536;   // components of up to this many values: one block
 constexpr int64_t kSureRow16 = 65535;    // chunk size up to which its bin counts are stored in 16 bits
 constexpr int kGramThreads = 512;
-constexpr int kSmallThreads = 1024;
 constexpr int kPixTile = 64;          // pixels per projection / back-projection block
 constexpr int kRitzGroup = 128;       // projection tiles per first-level Rayleigh-Ritz sum
 
@@ -131,14 +130,12 @@ struct VLevel {
     void* ll;                               // LL output, h x w positions, dense
     void* det;                              // LH, HL, HH blocks of h x w positions each
     int Hin, Win, h, w, p;
-    uint32_t pmag;                          // floor(2^32 / p) + 1
 };
 struct VSyn {
     const void* ll; const void* det;        // this level's LL and detail blocks (dense)
     void* out; int64_t op, orow;            // the level below (element strides)
     const double* scale;                    // per-band factor on store (sigma at the last level) or null
     int Hin, Win, h, w, p;
-    uint32_t pmag;
 };
 struct FLambda {
     const double* G[kForpdnMaxGroups];      // p x p band Gram of each group's coefficient vectors
@@ -152,12 +149,10 @@ struct FFilter {
     int64_t goff[kForpdnMaxGroups + 1];     // first position of each group
     const double* lambda;
     int p, groups;
-    uint32_t pmag;
 };
 hipError_t launch_vdwt_level(int dtype, const VLevel& a, int num_cu, hipStream_t s);
 hipError_t launch_vidwt_level(int dtype, const VSyn& a, int num_cu, hipStream_t s);
 hipError_t launch_forpdn_lambda(const FLambda& a, int groups, hipStream_t s);
-size_t forpdn_filter_lds(int dtype, int p, int groups);
 hipError_t launch_forpdn_filter(int dtype, const FFilter& a, int num_cu, hipStream_t s);
 
 // Tile grid of a sliding-window solve (FP32), for the back-projection that
@@ -246,46 +241,6 @@ __device__ __forceinline__ void static_for(F&& f) {
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
-// DPP move of a double (both halves) with a row-level permutation (quad_perm,
-// row_half_mirror, row_mirror): every lane has a source, so no old value is
-// needed (no zero-initialised destination).
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
-    static_assert(CTRL <= 0xFF || CTRL == 0x140 || CTRL == 0x141, "permutation controls only");
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, false);
-    return __hiloint2double(hi, lo);
-}
-// DPP row shift of a double: lanes without a source read 0.
-template <int CTRL>
-__device__ __forceinline__ double dpp_shift_f64(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
-    return __hiloint2double(hi, lo);
-}
-// Sum over the 16 lanes of each DPP row, returned to every lane of the row:
-// quad_perm xor 1, quad_perm xor 2, row_half_mirror, row_mirror.
-__device__ __forceinline__ double row16_sum(double v) {
-    v += dpp_f64<0xB1>(v);    // quad_perm [1,0,3,2]
-    v += dpp_f64<0x4E>(v);    // quad_perm [2,3,0,1]
-    v += dpp_f64<0x141>(v);   // row_half_mirror
-    v += dpp_f64<0x140>(v);   // row_mirror
-    return v;
-}
-__device__ __forceinline__ double readlane_f64(double v, int l) {
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
-    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
-    return __hiloint2double(hi, lo);
-}
-// Sum over each half-wave (32 lanes), returned to every lane of the half: the
-// four row sums are read into scalar registers (no LDS round trip).  Call with
-// the whole wave active.
-__device__ __forceinline__ double half_sum(double v) {
-    v = row16_sum(v);
-    const double r0 = readlane_f64(v, 0), r1 = readlane_f64(v, 16);
-    const double r2 = readlane_f64(v, 32), r3 = readlane_f64(v, 48);
-    return (threadIdx.x & 32) ? r2 + r3 : r0 + r1;
-}
 // Sum over the wave, returned to every lane ((r0 + r1) + (r2 + r3) of the row sums).
 __device__ __forceinline__ double wave_sum(double v) {
     v = row16_sum(v);
