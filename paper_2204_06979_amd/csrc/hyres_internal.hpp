@@ -241,6 +241,37 @@ __device__ __forceinline__ void static_for(F&& f) {
     static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
+// DPP move of a double (both halves) with a row-level permutation (quad_perm,
+// row_half_mirror, row_mirror): every lane has a source, so no old value is
+// needed (no zero-initialised destination).
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+    static_assert(CTRL <= 0xFF || CTRL == 0x140 || CTRL == 0x141, "permutation controls only");
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+// DPP row shift of a double: lanes without a source read 0.
+template <int CTRL>
+__device__ __forceinline__ double dpp_shift_f64(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+// Sum over the 16 lanes of each DPP row, returned to every lane of the row:
+// quad_perm xor 1, quad_perm xor 2, row_half_mirror, row_mirror.
+__device__ __forceinline__ double row16_sum(double v) {
+    v += dpp_f64<0xB1>(v);    // quad_perm [1,0,3,2]
+    v += dpp_f64<0x4E>(v);    // quad_perm [2,3,0,1]
+    v += dpp_f64<0x141>(v);   // row_half_mirror
+    v += dpp_f64<0x140>(v);   // row_mirror
+    return v;
+}
+__device__ __forceinline__ double readlane_f64(double v, int l) {
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
+    const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
+    return __hiloint2double(hi, lo);
+}
 // Sum over the wave, returned to every lane ((r0 + r1) + (r2 + r3) of the row sums).
 __device__ __forceinline__ double wave_sum(double v) {
     v = row16_sum(v);
