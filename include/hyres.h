@@ -247,8 +247,8 @@ hyres_status hyres_denoise(hyres_handle* h, const void* Y, int H, int W, int p,
  * per device, resolved when a handle is created on that device and held until
  * the process ends.  The call allocates nothing (no hipMalloc, no library
  * allocation).  Solves whose hyres_denoise_workspace_size exceeds the array
- * return HYRES_E_WORKSPACE (the 349 x 1905 x 144 cube at rank 8 needs 61 MiB
- * in FP32 and 71 MiB in mixed precision).  Every call on a device shares that
+ * return HYRES_E_WORKSPACE (the 349 x 1905 x 144 cube at rank 8 needs 59 MiB
+ * in FP32 and 69 MiB in mixed precision).  Every call on a device shares that
  * device's array and leaves its last contents there (the solve rewrites
  * everything it reads before reading it): calls that overlap on one device,
  * on different streams or from different handles, race and must be ordered
