@@ -227,11 +227,11 @@ __device__ __forceinline__ uint32_t first_histogram(const HYRES_GLOBAL T* cf, in
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int64_t i = e + (int64_t)u * kSureThreads;
-            v[u] = i < e1 ? cf[i] : (T)0;
+            v[u] = cf[i < e1 ? i : e1 - 1];          // unconditional: see k_sure_gather
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const auto k = KT::key(v[u]);
+            const auto k = KT::key(e + (int64_t)u * kSureThreads < e1 ? v[u] : (T)0);
             if (k != 0) atomicAdd(&lc[first_bin<T>(k)], 1u);
             else if (e + (int64_t)u * kSureThreads < e1) ++nz;
         }
@@ -406,18 +406,35 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_gather(const CubeDesc* __
     const int nch = d.snch, local = blockIdx.x - items[cu], comp = local / nch, chunk = local - comp * nch;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t N = sure_count(d);
+    const int64_t e0 = (int64_t)chunk * d.schunk, e1 = min(e0 + d.schunk, N);
+    const HYRES_GLOBAL T* cf = gmem(static_cast<const T*>(d.coef)) + (int64_t)comp * d.ncs;
+    constexpr int U = kSureLoads;
+    T v[U];
+    // every load unconditional (clamped): loads under a condition wait for one another
+    auto fetch = [&](int64_t e) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = e + lane + (int64_t)u * kSureThreads;
+            v[u] = cf[i < e1 ? i : N - 1];
+        }
+    };
     uint32_t c[kBinsPer] = {0, 0, 0, 0};
     static_assert(kBinsPer == 4, "rows are read four bins at a time");
     const HYRES_GLOBAL uint32_t* rows = gmem(d.shist) + comp * d.shcs;
     if (d.schunk <= kSureRow16) {
-        const HYRES_GLOBAL uint2* r = (const HYRES_GLOBAL uint2*)rows + tid;
-#pragma unroll 8
-        for (int k = 0; k < nch; ++k) {
-            const uint32_t x = r[(int64_t)k * kSureThreads].x, y = r[(int64_t)k * kSureThreads].y;
-            c[0] += x & 0xffffu;
-            c[1] += x >> 16;
-            c[2] += y & 0xffffu;
-            c[3] += y >> 16;
+        const HYRES_GLOBAL uint64_t* r = (const HYRES_GLOBAL uint64_t*)rows + tid;
+        for (int k = 0; k < nch; k += 16) {
+            uint64_t x[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) x[q] = r[(int64_t)min(k + q, nch - 1) * kSureThreads];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                const uint64_t w = k + q < nch ? x[q] : 0;
+                c[0] += (uint32_t)w & 0xffffu;
+                c[1] += (uint32_t)w >> 16;
+                c[2] += (uint32_t)(w >> 32) & 0xffffu;
+                c[3] += (uint32_t)(w >> 48);
+            }
         }
     } else {
 #pragma unroll 4
@@ -434,6 +451,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_gather(const CubeDesc* __
     const uint32_t zeros = sh.zeros;
     int first, last;
     uint64_t c0;
+    fetch(e0 + tid - lane);                  // under the selection
     first_select<T>(c, zeros, (double)N, sh, &first, &last, &c0);
     uint64_t klo = 1, khi = 1;
     if (first >= 0) first_range<T>(first, last, &klo, &khi);
@@ -445,19 +463,12 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_gather(const CubeDesc* __
         s->zeros = zeros;
     }
     if (first < 0) return;
-    const int64_t e0 = (int64_t)chunk * d.schunk, e1 = min(e0 + d.schunk, N);
-    const HYRES_GLOBAL T* cf = gmem(static_cast<const T*>(d.coef)) + (int64_t)comp * d.ncs;
     HYRES_GLOBAL T* seg = gmem(static_cast<T*>(d.slist)) + comp * d.slcs + (int64_t)chunk * d.segcap;
     const uint32_t cap = (uint32_t)d.segcap;
-    constexpr int U = kSureLoads;
     double s0 = 0.0;
     for (int64_t e = e0 + tid - lane; e < e1; e += U * kSureThreads) {   // whole waves
-        T v[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int64_t i = e + lane + (int64_t)u * kSureThreads;
-            v[u] = i < e1 ? cf[i] : (T)0;
-        }
+        for (int u = 0; u < U; ++u) v[u] = e + lane + (int64_t)u * kSureThreads < e1 ? v[u] : (T)0;
         bool in[U];
         uint32_t n = 0;
 #pragma unroll
@@ -477,6 +488,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_gather(const CubeDesc* __
             if (in[u] && pos < cap) seg[pos] = v[u];
             at += (uint32_t)__popcll(m);
         }
+        if (e + U * kSureThreads < e1) fetch(e + U * kSureThreads);
     }
     s0 = wave_sum(s0);
     if (lane == 0) sh.ws[wave] = s0;
