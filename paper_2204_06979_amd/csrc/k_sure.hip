@@ -544,10 +544,10 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
 #pragma unroll
             for (int k = 0; k < U; ++k) {
                 const int64_t e = i + (int64_t)stride * k;
-                v[k] = e < b ? p[e] : (T)0;
+                v[k] = p[e < b ? e : b - 1];              // unconditional: see k_sure_gather
             }
 #pragma unroll
-            for (int k = 0; k < U; ++k) f(v[k]);          // zeros are in no range
+            for (int k = 0; k < U; ++k) f(i + (int64_t)stride * k < b ? v[k] : (T)0);   // zeros are in no range
         }
     };
     auto for_each = [&](auto f) {
@@ -591,8 +591,13 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
         zeros = s.zeros;
         const SureSeg* sg = d.sseg + (int64_t)comp * kSureMaxChunks;
         if (khi > klo) {
-            for (int k = tid; k < nch; k += kSureThreads) s_count[k] = sg[k].count;
-            for (int k = 0; k < nch; ++k) s0 += sg[k].s0;
+            for (int k = tid; k < nch; k += kSureThreads) {
+                s_count[k] = sg[k].count;
+                sum[k] = sg[k].s0;
+            }
+            __syncthreads();
+#pragma unroll 8
+            for (int k = 0; k < nch; ++k) s0 += sum[k];
         }
     }
     // candidate 0 and the smallest upper bound so far
