@@ -33,9 +33,9 @@
 // compared with the best one through the bins between the two.
 //
 // Bound by latency and LDS atomics: the three passes over the 21 MB of 349 x 1905
-// and 8 components take 13, 22 and 40 us, against 145 us for six passes with a
+// and 8 components take 10, 22 and 38 us, against 145 us for six passes with a
 // select in the last block of each; ten components of 145 x 217, one launch,
-// 44 us against 594; four FP64 ones of 64 x 64 25 us against 158.
+// 37 us against 594; four FP64 ones of 64 x 64 25 us against 158.
 #include "hyres_internal.hpp"
 
 namespace hyres {
@@ -217,10 +217,9 @@ __device__ __forceinline__ int waves_minmax(const int* w) {
 
 // First histogram of values e0..e1-1 into lc (kSureBins counts, zeroed by the
 // caller).  Each thread keeps its zeros; returns them.
-template <typename T>
-__device__ __forceinline__ uint32_t first_histogram(const HYRES_GLOBAL T* cf, int64_t e0, int64_t e1, uint32_t* lc) {
+template <typename T, int U>
+__device__ __forceinline__ uint32_t first_histogram_u(const HYRES_GLOBAL T* cf, int64_t e0, int64_t e1, uint32_t* lc) {
     typedef KeyTraits<T> KT;
-    constexpr int U = kSureLoads;
     uint32_t nz = 0;
     for (int64_t e = e0 + threadIdx.x; e < e1; e += U * kSureThreads) {
         T v[U];
@@ -237,6 +236,12 @@ __device__ __forceinline__ uint32_t first_histogram(const HYRES_GLOBAL T* cf, in
         }
     }
     return nz;
+}
+// Up to four values a thread are not read sixteen at a time: the clamped loads and
+// their zeros would cost more than the values.
+template <typename T>
+__device__ __forceinline__ uint32_t first_histogram(const HYRES_GLOBAL T* cf, int64_t e0, int64_t e1, uint32_t* lc) {
+    return e1 - e0 <= 4 * kSureThreads ? first_histogram_u<T, 4>(cf, e0, e1, lc) : first_histogram_u<T, kSureLoads>(cf, e0, e1, lc);
 }
 
 // Select on the first histogram: c[j] holds bin 4 tid + j (the zero slot's
@@ -544,10 +549,10 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
 #pragma unroll
             for (int k = 0; k < U; ++k) {
                 const int64_t e = i + (int64_t)stride * k;
-                v[k] = p[e < b ? e : b - 1];              // unconditional: see k_sure_gather
+                v[k] = e < b ? p[e] : (T)0;           // few of the U are in range: clamped loads are slower here (40.3 us, 38)
             }
 #pragma unroll
-            for (int k = 0; k < U; ++k) f(i + (int64_t)stride * k < b ? v[k] : (T)0);   // zeros are in no range
+            for (int k = 0; k < U; ++k) f(v[k]);          // zeros are in no range
         }
     };
     auto for_each = [&](auto f) {
