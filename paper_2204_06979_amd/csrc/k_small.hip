@@ -53,7 +53,8 @@ __device__ __forceinline__ double row_bcast(double v) {
 // d_i and e_{i-1}^2 of i = 16 b + c (entries past the matrix: d = 3, e = 0, no sign
 // change for x < 3); a step is two broadcasts, three FP64 operations and one that
 // shifts the sign into a word: 24 issue cycles, no LDS (broadcast 16-byte reads of
-// all waves were its bound before, 49 cycles a step).
+// all waves were its bound before, 49 cycles a step).  Call with all sixteen lanes
+// of a row active: a lane that is off broadcasts zeros.
 template <int T>
 __device__ __forceinline__ int sturm_count(const double (&dv)[T], const double (&ev)[T], double x) {
     double pm2 = 0.0, pm1 = 1.0;
@@ -649,8 +650,10 @@ __global__ __launch_bounds__(64 * Cols<T>::NW) void k_small(const CubeDesc* __re
             const int m = t % M;
             const int nslot = NTH / M;
             for (int g0 = 0; g0 < nev; g0 += nslot) {
-                const int g = g0 + t / M;
-                if (g < nev) {
+                // whole rows of 16 lanes: a group of a row beyond the last eigenvalue
+                // counts along on the last one
+                if (g0 + (t & ~15) / M < nev) {
+                    const int slot = g0 + t / M, g = min(slot, nev - 1);
                     const int midx = p - 1 - g;        // ascending index of the g-th largest
                     double lo = -1.0 - 1e-12, hi = 1.0 + 1e-12;
                     for (int it = 0; it < iters; ++it) {
@@ -665,7 +668,7 @@ __global__ __launch_bounds__(64 * Cols<T>::NW) void k_small(const CubeDesc* __re
                         lo = lo_c;
                         hi = hi_c;
                     }
-                    if (m == 0) {
+                    if (m == 0 && slot < nev) {
                         const double ev = 0.5 * (lo + hi) * gmax;
                         s_ev[g] = ev;
                         if (d.evals) d.evals[g] = ev;
