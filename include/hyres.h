@@ -84,8 +84,9 @@ typedef enum {
 #define HYRES_DEV_NONFINITE     2   /* NaN or Inf in the input cube */
 #define HYRES_DEV_EIGH_NOCONV   4   /* eigensolver produced a non-finite value */
 #define HYRES_DEV_DEGENERATE    8   /* warning: evals[r-1] / evals[r] < 1 + 1e-6 */
-#define HYRES_DEV_SURE_INEXACT 16   /* SURE search stopped before isolating the exact minimiser;
-                                       the threshold is the best exact candidate seen */
+#define HYRES_DEV_SURE_INEXACT 16   /* SURE search stopped before isolating the exact minimiser (a
+                                       risk that is flat over much of its range); the threshold
+                                       is the best one seen, with its risk */
 
 typedef struct hyres_handle hyres_handle;
 

@@ -22,8 +22,9 @@
 // 3. k_sure_finish, one block per component: histograms of counts and sums of
 //    squares over the list, each over the range that survived, until the
 //    surviving bins are small; their values, grouped by bin in LDS, are then
-//    evaluated one by one.  Smaller components do step 1 here, over the
-//    coefficients themselves.
+//    evaluated one by one.  Too many survivors all over a range are searched in
+//    windows of it.  Smaller components do step 1 here, over the coefficients
+//    themselves.
 //
 // The first histogram has 512 bins per octave of [1/16, 8), where thresholds
 // of unit-noise coefficients lie: 16 per octave (one key range for all numbers)
@@ -47,7 +48,14 @@ constexpr int kSureLoads = 16;       // values a thread reads at once
 constexpr int kZeroSlot = kSureBins - 1;              // first histogram: exact zeros
 constexpr int kSureLight = 64;      // largest bin evaluated without narrowing the range first
 constexpr int kSureHeavy = 256;     // a larger bin is searched as a range of its own
-constexpr int kSureStack = 256;     // ranges waiting (at most 128 heavy bins of one range)
+constexpr int kSureHeavies = 16;    // ... up to this many of them; more, or more values than fit in LDS: windows
+constexpr int kSureWindows = 16;
+constexpr int kSureStack = 256;     // ranges waiting
+// Values the finish reads in all, in passes over its list, before it gives the
+// smallest risk seen (1.5 ms of one block).  Only a risk that is flat over much of its
+// range gets there: of Rayleigh-distributed magnitudes, whose expected risk is the
+// same everywhere, a million are finished in 1.0-1.6 ms (bin by bin 1-55).
+constexpr int64_t kSureVisits = (int64_t)1 << 23;
 
 // Keys, and the bins of the first histogram: `lo_shift`-wide bins below 1/16
 // and from 8 on, 512 bins per octave between.  Word: the part of the key the
@@ -179,7 +187,7 @@ __device__ __forceinline__ int wave_minmax_i32(int v) {
 
 // Small per-block state.
 struct SureShared {
-    uint32_t wc[kSureWaves], wn[kSureWaves];
+    uint32_t wc[kSureWaves], wn[kSureWaves], wm[kSureWaves];
     double ws[kSureWaves], wt[kSureWaves], bs[kSureWaves], bt[kSureWaves];
     int wf[kSureWaves], wl[kSureWaves], wx[kSureWaves];
     uint32_t zeros, count;
@@ -507,6 +515,75 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_gather(const CubeDesc* __
     }
 }
 
+// Select on a histogram of counts c and sums of squares q (bins 4 tid + j, 2^shf keys
+// wide) of the range [klo, khi), with c0 values and squares s0 below it: the values
+// and squares before each thread's bins, the lower bounds of the bins and the
+// smallest upper bound with its threshold.
+template <typename T>
+__device__ __forceinline__ void range_select(const uint32_t (&c)[kBinsPer], const double (&q)[kBinsPer], double N,
+                                             uint64_t klo, uint64_t khi, int shf, uint64_t c0, double s0,
+                                             SureShared& sh, uint32_t* before, double* sbefore,
+                                             double (&lb)[kBinsPer], double* us, double* ut) {
+    typedef KeyTraits<T> KT;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t tc = 0;
+    double tq = 0.0;
+#pragma unroll
+    for (int j = 0; j < kBinsPer; ++j) {
+        tc += c[j];
+        tq += q[j];
+    }
+    const uint32_t ic = wave_incl_u32(tc);
+    const double iq = wave_incl_f64(tq), pq = __shfl_up(iq, 1, 64);
+    if (lane == 63) {
+        sh.wc[wave] = ic;
+        sh.ws[wave] = iq;
+    }
+    __syncthreads();
+    uint32_t total;
+    double all;
+    uint32_t pc = waves_before(sh.wc, wave, &total) + ic - tc;
+    double ps = waves_before(sh.ws, wave, &all);
+    if (lane) ps += pq;
+    *before = pc;
+    *sbefore = ps;
+    *us = __builtin_inf();
+    *ut = 0.0;
+#pragma unroll
+    for (int j = 0; j < kBinsPer; ++j) {
+        const int b = kBinsPer * tid + j;
+        lb[j] = __builtin_inf();
+        if (c[j]) {
+            const double C = (double)(c0 + pc), S = s0 + ps, cc = (double)c[j];
+            const uint64_t end = klo + ((uint64_t)(b + 1) << shf);
+            const double t0 = KT::val(klo + ((uint64_t)b << shf)), t1 = KT::val((end < khi ? end : khi) - 1);
+            lb[j] = N - 2.0 * (C + cc) + S + (N - C) * t0 * t0;
+            const double up = N - 2.0 * (C + cc) + (S + q[j]) + (N - C - cc) * t1 * t1;
+            if (up < *us || (up == *us && t1 < *ut)) {
+                *us = up;
+                *ut = t1;
+            }
+        }
+        pc += c[j];
+        ps += q[j];
+    }
+}
+
+// Argmin over the block of each thread's (s, t), smaller t on ties, to every thread.
+__device__ __forceinline__ void block_argmin(double& s, double& t, SureShared& sh) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    wave_argmin(s, t);
+    __syncthreads();
+    if (lane == 0) {
+        sh.bs[wave] = s;
+        sh.bt[wave] = t;
+    }
+    __syncthreads();
+    s = sh.bs[lane & 15];
+    t = sh.bt[lane & 15];
+    wave_argmin(s, t);
+}
+
 // A range of keys to search: values and squares below it, a lower bound.
 struct SureRange {
     uint64_t klo, khi, c0;
@@ -527,7 +604,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
     __shared__ uint32_t bits[kSureBins / 32];
     __shared__ SureRange stack[kSureStack];
     __shared__ SureShared sh;
-    __shared__ int s_sp, s_lo, s_hi, s_inexact;
+    __shared__ int s_sp, s_inexact, s_wlo[kSureWindows], s_whi[kSureWindows];
     __shared__ uint32_t s_count[kSureMaxChunks];
     const int cu = find_cube(items, ncubes, blockIdx.x);
     const CubeDesc& d = descs[cu];
@@ -572,6 +649,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
     uint32_t zeros = 0;
     uint64_t klo = 1, khi = 1, c0 = 0;
     double s0 = 0.0;
+    int64_t values = Ni, visits = 0;          // of a pass; read so far
     bool need_s0 = false;
     if (nch == 1) {
         for (int b = tid; b < kSureBins; b += kSureThreads) cnt[b] = 0;
@@ -601,12 +679,16 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
                 sum[k] = sg[k].s0;
             }
             __syncthreads();
+            values = 0;
 #pragma unroll 8
-            for (int k = 0; k < nch; ++k) s0 += sum[k];
+            for (int k = 0; k < nch; ++k) {
+                s0 += sum[k];
+                values += min(s_count[k], (uint32_t)d.schunk);
+            }
         }
     }
     // candidate 0 and the smallest upper bound so far
-    double best_s = N - 2.0 * (double)zeros, best_t = 0.0, U = best_s;
+    double best_s = N - 2.0 * (double)zeros, best_t = 0.0, U = best_s, Ut = 0.0;
     if (tid == 0) {
         s_sp = 0;
         s_inexact = 0;
@@ -620,19 +702,6 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
         }
     }
     __syncthreads();
-    // block-wide argmin of each thread's (s, t), smaller t on ties
-    auto block_argmin = [&](double& s, double& t) {
-        wave_argmin(s, t);
-        __syncthreads();
-        if (lane == 0) {
-            sh.bs[wave] = s;
-            sh.bt[wave] = t;
-        }
-        __syncthreads();
-        s = sh.bs[lane & 15];
-        t = sh.bt[lane & 15];
-        wave_argmin(s, t);
-    };
     while (true) {
         __syncthreads();
         const int sp = s_sp;
@@ -646,6 +715,14 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
         __syncthreads();
         if (tid == 0) s_sp = sp - 1;
         if (skip) continue;
+        if (visits + values > kSureVisits) {
+            if (tid == 0) {
+                s_inexact = 1;
+                s_sp = 0;
+            }
+            continue;
+        }
+        visits += values;
         const int shf = shift_for(khi - klo);
         for (int b = tid; b < kSureBins; b += kSureThreads) {
             cnt[b] = 0;
@@ -673,51 +750,26 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
             need_s0 = false;
             __syncthreads();
         }
-        // exclusive prefixes of the counts and sums
-        uint32_t c[PER], tc = 0;
-        double q[PER], tq = 0.0;
+        uint32_t c[PER], pc;
+        double q[PER], lb[PER], ps, us, ut;
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             c[j] = cnt[PER * tid + j];
             q[j] = sum[PER * tid + j];
-            tc += c[j];
-            tq += q[j];
         }
-        const uint32_t ic = wave_incl_u32(tc);
-        const double iq = wave_incl_f64(tq), pq = __shfl_up(iq, 1, 64);
-        if (lane == 63) {
-            sh.wc[wave] = ic;
-            sh.ws[wave] = iq;
-        }
-        __syncthreads();
-        uint32_t total;
-        double all;
-        uint32_t pc = waves_before(sh.wc, wave, &total) + ic - tc;
-        double ps = waves_before(sh.ws, wave, &all);
-        if (lane) ps += pq;
-        double lb[PER], us = __builtin_inf(), ut = 0.0;
+        range_select<T>(c, q, N, klo, khi, shf, c0, s0, sh, &pc, &ps, lb, &us, &ut);
 #pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int b = PER * tid + j;
-            pre[b] = pc;
-            sum[b] = ps;
-            lb[j] = __builtin_inf();
-            if (c[j]) {
-                const double C = (double)(c0 + pc), S = s0 + ps, cc = (double)c[j];
-                const uint64_t end = klo + ((uint64_t)(b + 1) << shf);
-                const double t0 = KT::val(klo + ((uint64_t)b << shf)), t1 = KT::val((end < khi ? end : khi) - 1);
-                lb[j] = N - 2.0 * (C + cc) + S + (N - C) * t0 * t0;
-                const double up = N - 2.0 * (C + cc) + (S + q[j]) + (N - C - cc) * t1 * t1;
-                if (up < us || (up == us && t1 < ut)) {
-                    us = up;
-                    ut = t1;
-                }
-            }
+        for (int j = 0; j < PER; ++j) {       // exclusive prefixes
+            pre[PER * tid + j] = pc;
+            sum[PER * tid + j] = ps;
             pc += c[j];
             ps += q[j];
         }
-        block_argmin(us, ut);
-        if (us < U) U = us;
+        block_argmin(us, ut, sh);
+        if (us < U) {
+            U = us;
+            Ut = ut;
+        }
         if (shf == 0) {                       // one value per bin: the bounds are exact
             if (us < best_s || (us == best_s && ut < best_t)) {
                 best_s = us;
@@ -727,7 +779,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
         }
         const double lim = U + 1e-12 * (fabs(U) + N);
         int f = 0x7fffffff, l = -1, mx = 0, nh = 0;
-        uint32_t m = 0;
+        uint32_t m = 0, ml = 0;
 #pragma unroll
         for (int j = 0; j < PER; ++j)
             if (lb[j] <= lim) {
@@ -737,9 +789,10 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
                 mx = n > mx ? n : mx;
                 nh += n > kSureHeavy ? 1 : 0;
                 m += c[j];
+                ml += n > kSureHeavy ? 0 : c[j];
             }
         const int wf = wave_minmax_i32<false>(f), wl = wave_minmax_i32<true>(l), wx = wave_minmax_i32<true>(mx);
-        const uint32_t wm = wave_incl_u32(m), wh = wave_incl_u32((uint32_t)nh);
+        const uint32_t wm = wave_incl_u32(m), wh = wave_incl_u32((uint32_t)nh), wlt = wave_incl_u32(ml);
         __syncthreads();
         if (lane == 63) {
             sh.wf[wave] = wf;
@@ -747,14 +800,16 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
             sh.wx[wave] = wx;
             sh.wc[wave] = wm;
             sh.wn[wave] = wh;
+            sh.wm[wave] = wlt;
         }
         __syncthreads();
         f = waves_minmax<false>(sh.wf);
         l = waves_minmax<true>(sh.wl);
         mx = waves_minmax<true>(sh.wx);
-        uint32_t heavies;
+        uint32_t total, heavies, light;
         (void)waves_before(sh.wc, wave, &total);
         (void)waves_before(sh.wn, wave, &heavies);
+        (void)waves_before(sh.wm, wave, &light);
         if (l < 0) continue;
         if ((total > (uint32_t)CAP || mx > kSureLight) && (l - f + 1) * 2 <= kSureBins) {
             // the surviving bins span at most half the range: search that
@@ -770,15 +825,50 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
             }
             continue;
         }
+        if (light > (uint32_t)CAP || heavies > (uint32_t)kSureHeavies) {
+            // flat over more than half the range: windows of it, each a range with bins as
+            // many times finer, down to about a sixteenth of the values
+            const int span = l - f + 1;
+            const int nw = (int)min((uint32_t)kSureWindows, total / (4u * CAP) + 2u);
+            if (tid < kSureWindows) {
+                s_wlo[tid] = kSureBins;
+                s_whi[tid] = -1;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < PER; ++j)
+                if (lb[j] <= lim) {
+                    const int b = PER * tid + j, w = (b - f) * nw / span;
+                    atomicMin(&s_wlo[w], b);
+                    atomicMax(&s_whi[w], b);
+                }
+            __syncthreads();
+            if (tid < nw && s_whi[tid] >= 0) {
+                const int at = atomicAdd(&s_sp, 1), b0 = s_wlo[tid], b1 = s_whi[tid];
+                if (at < kSureStack) {
+                    const uint64_t hi = klo + ((uint64_t)(b1 + 1) << shf);
+                    SureRange& r = stack[at];
+                    r.klo = klo + ((uint64_t)b0 << shf);
+                    r.khi = hi < khi ? hi : khi;
+                    r.c0 = c0 + pre[b0];
+                    r.s0 = s0 + sum[b0];
+                    r.lb = -__builtin_inf();
+                } else {
+                    s_inexact = 1;
+                }
+            }
+            __syncthreads();
+            if (tid == 0 && s_sp > kSureStack) s_sp = kSureStack;
+            continue;
+        }
         // bins too large to evaluate value by value become ranges of their own
-        const uint32_t heavy = heavies <= 128 ? (uint32_t)kSureHeavy : (uint32_t)(CAP / 2);
         uint32_t g[PER], tg = 0;
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             const int b = PER * tid + j;
             g[j] = 0;
             if (!(lb[j] <= lim)) continue;
-            if (c[j] > heavy) {
+            if (c[j] > (uint32_t)kSureHeavy) {
                 const int at = atomicAdd(&s_sp, 1);
                 if (at < kSureStack) {
                     const uint64_t hi = klo + ((uint64_t)(b + 1) << shf);
@@ -801,35 +891,21 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
         if (lane == 63) sh.wc[wave] = ig;
         if (tid == 0 && s_sp > kSureStack) s_sp = kSureStack;
         __syncthreads();
-        uint32_t light;
         const uint32_t og = waves_before(sh.wc, wave, &light) + ig - tg;
-        // groups of consecutive bins whose values fit in LDS (mostly one)
-        const uint32_t gc = light <= (uint32_t)CAP ? (uint32_t)CAP : (uint32_t)(CAP / 2);
-        for (uint32_t base = 0; base < light; base += gc) {
+        if (light) {                          // at most CAP values
             if (tid < kSureBins / 32) bits[tid] = 0;
-            if (tid == 0) {
-                s_lo = CAP;
-                s_hi = 0;
-            }
             __syncthreads();
             uint32_t o = og;
             uint32_t mine = 0;
-            int lo = CAP, hi = 0;
 #pragma unroll
             for (int j = 0; j < PER; ++j) {
-                if (g[j] && o >= base && o - base < gc) {
-                    off[PER * tid + j] = o - base;
+                if (g[j]) {
+                    off[PER * tid + j] = o;
                     mine |= 1u << j;
-                    lo = min(lo, (int)(o - base));
-                    hi = max(hi, (int)(o - base + g[j]));
                 }
                 o += g[j];
             }
-            if (mine) {
-                atomicOr(&bits[tid >> 3], mine << (4 * (tid & 7)));
-                atomicMin(&s_lo, lo);
-                atomicMax(&s_hi, hi);
-            }
+            if (mine) atomicOr(&bits[tid >> 3], mine << (4 * (tid & 7)));
             __syncthreads();
             for_each([&](T v) {
                 const uint64_t k = KT::key(v);
@@ -840,7 +916,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
             });
             __syncthreads();
             double es = __builtin_inf(), et = 0.0;
-            for (int i = s_lo + tid; i < s_hi; i += kSureThreads) {
+            for (int i = tid; i < (int)light; i += kSureThreads) {
                 const uint64_t key = keys[i];
                 const int b = (int)((key - klo) >> shf);
                 const int n = (int)cnt[b], j1 = (int)off[b];
@@ -865,7 +941,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
                     et = v;
                 }
             }
-            block_argmin(es, et);
+            block_argmin(es, et, sh);
             if (es < best_s || (es == best_s && et < best_t)) {
                 best_s = es;
                 best_t = et;
@@ -875,6 +951,10 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
         }
     }
     if (tid == 0) {
+        if (s_inexact && U < best_s) {        // the end of a bin: no value of the component
+            best_s = U;
+            best_t = Ut;
+        }
         d.lambda[comp] = best_t;
         if (d.sure) d.sure[comp] = best_s;
         if (s_inexact) set_status(d.status, HYRES_DEV_SURE_INEXACT);
