@@ -39,7 +39,9 @@ hipError_t launch_backproject_f64(const CubeDesc*, int, int64_t, hipStream_t);
 hipError_t launch_dwt_level1_rot(int tx, int ty, const CubeDesc*, const int*, int, int, int, hipStream_t);
 hipError_t launch_dwt_level(int dtype, int tx, int ty, bool inverse, const CubeDesc*, const int*, int, int,
                             int, hipStream_t);
-hipError_t launch_sure(int dtype, int step, const CubeDesc*, const int*, int, int, hipStream_t);
+hipError_t launch_sure(int dtype, int step, const CubeDesc*, const int*, int, int, int round, hipStream_t);
+int sure_rounds(int64_t N);
+int64_t sure_extra(int64_t N);
 int sure_chunks(int64_t N, int64_t total, int num_cu, int64_t room);
 int64_t sure_chunk(int64_t N, int nch);
 hipError_t launch_ritz(const CubeDesc*, const int*, const int*, int, int, int, hipStream_t);
@@ -297,15 +299,15 @@ void plan_cube(CubePlan& c, Layout& lay, int parts) {
             c.o_shist = c.o_tmp;
             c.shcs = c.tps * es / 4;
         } else {
-            const int nch = sure_chunks(c.nc, (int64_t)c.r * c.nc, 256, kSureMaxChunks);
+            const int nch = sure_chunks(c.nc, (int64_t)c.r * c.nc, 256, (int64_t)1 << 40);
             if (nch > 1) {
-                c.shcs = (int64_t)nch * kSureBins;
+                c.shcs = (int64_t)nch * kSureBins + sure_extra(c.nc);
                 c.slcs = c.nc / 4 + nch;
             }
             c.o_shist = lay.add(std::max<size_t>((size_t)c.r * c.shcs * 4, 16));
             c.o_slist = lay.add(std::max<size_t>((size_t)c.r * c.slcs * es, 16));
         }
-        c.o_ssel = lay.add((size_t)c.r * sizeof(SureSel));
+        c.o_ssel = lay.add((size_t)c.r * (kSureRefine + 1) * sizeof(SureSel));
         c.o_sseg = lay.add((size_t)c.r * kSureMaxChunks * sizeof(SureSeg));
         c.o_lambda = lay.add((size_t)c.r * 8);
         c.o_sure = lay.add((size_t)c.r * 8);
@@ -427,7 +429,7 @@ int small_class(int p) {
 // Upper bound on the tables of one program: per band-tile class (14) Gram,
 // projection items and the reduce list; back-projection items per class, or
 // per blend pass of a tile grid (whose tiles share one class); per small-solve
-// class a list; SURE component and histogram items; per level, direction and
+// class a list; SURE component, histogram and row items; per level, direction and
 // tile candidate the DWT items; the Rayleigh-Ritz slot and pixel items and
 // cube list; plus one scratch table for the tuner.
 // Cube groups (see Exec::group_of) repeat the SURE, transform and
@@ -435,7 +437,7 @@ int small_class(int p) {
 constexpr int kMaxColours = 8;    // blend colours per axis of a tile grid
 constexpr int kMaxGroups = 4;
 constexpr int kMaxTables = 3 * 14 + std::max(14, kMaxColours * kMaxColours) + kSmallClasses +
-                           kMaxGroups * (2 + 2 * kMaxLevels * kTileCands + 3) + 1;
+                           kMaxGroups * (3 + 2 * kMaxLevels * kTileCands + 3) + 1;
 size_t table_ints(int count) { return (size_t)kMaxTables * (count + 1); }
 
 struct Exec {
@@ -662,8 +664,9 @@ void build_group(Exec& x, int stages, int grp) {
     }
     if (stages & S_DWT) add_dwt(x, false, grp, x.precision == HYRES_PREC_MIXED && !f64 && (stages & S_PROJ));
     if (stages & S_SURE) {
-        std::vector<int64_t> comp(N, 0), hist(N, 0);
+        std::vector<int64_t> comp(N, 0), hist(N, 0), rows(N, 0);
         int64_t total_coef = 0;
+        int rounds = 0;
         auto values = [](const CubePlan& c) { return c.scope == HYRES_SCOPE_DETAIL ? c.ll_off : c.nc; };
         for (int i = 0; i < N; ++i) {
             const CubePlan& c = x.plan[i];
@@ -674,26 +677,40 @@ void build_group(Exec& x, int stages, int grp) {
             if (!in_group(x, i, grp) || c.has_lambda) continue;
             CubeDesc& d = x.desc[i];
             const int64_t ns = values(c);
-            d.snch = sure_chunks(ns, total_coef, x.h ? x.h->num_cu : 256, c.shcs / kSureBins);
+            d.snch = sure_chunks(ns, total_coef, x.h ? x.h->num_cu : 256, c.shcs);
             d.schunk = sure_chunk(ns, d.snch);
             d.snch = (int)cdiv(ns, d.schunk);
-            d.segcap = c.slcs / d.snch;
+            d.srounds = d.snch > 1 ? sure_rounds(ns) : 0;
+            d.segcap = c.slcs / (d.srounds ? 2 * d.snch : d.snch);
             comp[i] = c.r;
             hist[i] = d.snch > 1 ? (int64_t)c.r * d.snch : 0;
+            rows[i] = d.srounds ? (int64_t)c.r * kSureSplit : 0;
+            rounds = std::max(rounds, d.srounds);
         }
-        int64_t ncomp, nh;
+        int64_t ncomp, nh, nr = 0;
         const int tc = x.counts(comp, &ncomp);
         const int th = x.counts(hist, &nh);
-        for (int step = nh > 0 ? 0 : 2; step < 3 && ncomp > 0; ++step) {
+        const int tr = rounds ? x.counts(rows, &nr) : 0;
+        auto add = [&](int step, int table, int64_t grid, int round = 0) {
+            if (grid < 1) return;
             Launch R{};
             R.kind = K_SURE;
             R.stage = HYRES_STAGE_SURE;
             R.key = step;
-            R.a = step < 2 ? th : tc;
+            R.a = table;
             R.n = N;
-            R.grid = (int)(step < 2 ? nh : ncomp);
+            R.grid = (int)grid;
+            R.level = round;
             x.prog.push_back(R);
+        };
+        add(SURE_HIST, th, nh);
+        add(SURE_ROWS, tr, nr);
+        add(SURE_GATHER, th, nh);
+        for (int k = 0; k < rounds; ++k) {
+            add(SURE_REFINE, th, nh, k);
+            add(SURE_NARROW, th, nh, k);
         }
+        add(SURE_FINISH, tc, ncomp);
         for (int i = 0; i < N; ++i) {
             if (!in_group(x, i, grp) || !x.plan[i].has_lambda) continue;
             Launch C{};
@@ -767,7 +784,7 @@ hipError_t launch_one(const Exec& x, const Launch& L, hipStream_t s) {
         case K_IDWT:
             return launch_dwt_level(x.dtype, kTileTX[L.key], kTileTY[L.key], L.kind == K_IDWT, D, x.table(L.a),
                                     L.n, L.level, L.grid, s);
-        case K_SURE: return launch_sure(x.dtype, L.key, D, x.table(L.a), L.n, L.grid, s);
+        case K_SURE: return launch_sure(x.dtype, L.key, D, x.table(L.a), L.n, L.grid, L.level, s);
         case K_COPY:
             hipLaunchKernelGGL(k_copy_f64, dim3(1), dim3(64), 0, s, L.src, L.dst, L.n);
             return hipGetLastError();

@@ -13,7 +13,11 @@ constexpr int kMaxLevels = 8;
 constexpr int kMaxRank = 16;
 constexpr int kMaxBands = 224;        // FP64 small solver keeps a 224 x 224 matrix in registers
 constexpr int kSureBins = 4096;       // bins of a threshold-search histogram
-constexpr int kSureMaxChunks = 64;    // chunks per component of the threshold search
+constexpr int kSureChunks = 64;       // chunks per component of the threshold search
+constexpr int kSureMaxChunks = 256;   // ... of a large component
+constexpr int kSureSplit = 64;        // blocks per large component that add its count rows
+constexpr int kSureRefine = 3;        // refining rounds of the largest components
+constexpr int64_t kSureLarge = (int64_t)1 << 20;   // components beyond it are refined by all blocks before the finish
 constexpr int64_t kSureDirect = 65536;   // components of up to this many values: one block
 constexpr int64_t kSureRow16 = 65535;    // chunk size up to which its bin counts are stored in 16 bits
 constexpr int kGramThreads = 512;
@@ -27,17 +31,21 @@ constexpr double kH1 = 0.83651630373780794;
 constexpr double kH2 = 0.22414386804201339;
 constexpr double kH3 = -0.12940952255126037;
 
-// SURE threshold search: the key range [klo, khi) that survives the first
-// histogram, the values below it (exact zeros included) and the exact zeros.
+// SURE threshold search: the key range [klo, khi) that survives a histogram, the
+// values below it (exact zeros included), the smallest upper bound of the risk with
+// its threshold, and the exact zeros; after a refining round also the squares below
+// the range and the values in it.
 struct SureSel {
     uint64_t klo, khi, c0;
-    uint32_t zeros, pad;
+    double s0, U, Ut;
+    uint32_t zeros, count;
 };
-// ... and per chunk: squares of its values below the range, its values inside.
+// ... and per chunk: squares of its values below the first range, its values inside.
 struct SureSeg {
     double s0;
     uint32_t count, pad;
 };
+enum { SURE_HIST, SURE_ROWS, SURE_GATHER, SURE_REFINE, SURE_NARROW, SURE_FINISH };   // launches of the search
 
 // CubeDesc::mode bits
 constexpr int kModeSigma = 1;      // estimate the noise
@@ -85,9 +93,9 @@ struct CubeDesc {
     // segments of surviving values (component stride slcs, segcap each), results
     uint32_t* shist; int64_t shcs;
     void* slist; int64_t slcs, segcap;
-    SureSel* ssel;                          // r
+    SureSel* ssel;                          // r x (kSureRefine + 1)
     SureSeg* sseg;                          // r x kSureMaxChunks
-    int64_t schunk; int snch;               // coefficients per chunk, chunks (1: no list)
+    int64_t schunk; int snch, srounds;      // coefficients per chunk, chunks (1: no list), refining rounds
     double* lambda; double* sure;           // r
     const double* lambda_in;                // optional caller thresholds
     // sliding-window blend in the back-projection (bwy null: plain write).  A

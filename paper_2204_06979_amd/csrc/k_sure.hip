@@ -19,6 +19,8 @@
 // 2. k_sure_gather: every block adds its component's rows, finds the range of
 //    the surviving bins, and copies its chunk's values in that range into its
 //    segment of a list, with the sum of squares of those below.
+//    Beyond kSureLarge values k_sure_rows adds the rows up first, and rounds of
+//    k_sure_refine and k_sure_narrow shorten the list before step 3.
 // 3. k_sure_finish, one block per component: histograms of counts and sums of
 //    squares over the list, each over the range that survived, until the
 //    surviving bins are small; their values, grouped by bin in LDS, are then
@@ -409,6 +411,85 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_hist(const CubeDesc* __re
     }
 }
 
+// Appends the values of [klo, khi) among a wave's v (zeros are in no range) to a
+// list of `cap` values; *count counts those beyond it too.
+template <typename T, typename C>
+__device__ __forceinline__ void keep_range(const T (&v)[kSureLoads], uint64_t klo, uint64_t khi, HYRES_GLOBAL T* list,
+                                           uint32_t cap, C* count) {
+    typedef KeyTraits<T> KT;
+    const int lane = threadIdx.x & 63;
+    bool in[kSureLoads];
+    uint32_t n = 0;
+#pragma unroll
+    for (int u = 0; u < kSureLoads; ++u) {
+        const uint64_t k = KT::key(v[u]);
+        in[u] = k >= klo && k < khi;
+        n += (uint32_t)__popcll(__ballot(in[u]));
+    }
+    uint32_t at = 0;
+    if (!n) return;
+    if (lane == 0) at = atomicAdd(count, n);
+    at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
+#pragma unroll
+    for (int u = 0; u < kSureLoads; ++u) {
+        const unsigned long long m = __ballot(in[u]);
+        const uint32_t pos = at + (uint32_t)__popcll(m & ((1ull << lane) - 1));
+        if (in[u] && pos < cap) list[pos] = v[u];
+        at += (uint32_t)__popcll(m);
+    }
+}
+
+// Large components (d.srounds > 0): the chunks' count rows added into one, which the
+// gather reads, and the rows and list lengths of the refining rounds cleared.
+// kSureSplit blocks per component, each 64 bins: 16 threads of four bins
+// by 16 shares of the rows (256 rows in 5 us; one bin and all rows a thread took 30).
+template <typename T>
+__global__ __launch_bounds__(256) void k_sure_rows(const CubeDesc* __restrict__ descs, const int* __restrict__ items,
+                                                   int ncubes) {
+    __shared__ uint32_t part[16][64];
+    const int cu = find_cube(items, ncubes, blockIdx.x);
+    const CubeDesc& d = descs[cu];
+    const int local = blockIdx.x - items[cu], comp = local / kSureSplit, b0 = (local - comp * kSureSplit) * 64;
+    static_assert(kSureBins == kSureSplit * 64, "64 bins a block");
+    const int tid = threadIdx.x, bin = b0 + 4 * (tid & 15), share = tid >> 4;
+    HYRES_GLOBAL uint32_t* rows = gmem(d.shist) + comp * d.shcs;
+    uint32_t c[4] = {0, 0, 0, 0};
+    if (d.schunk <= kSureRow16) {
+        const HYRES_GLOBAL uint64_t* r = (const HYRES_GLOBAL uint64_t*)rows + bin / 4;
+#pragma unroll 16
+        for (int k = share; k < d.snch; k += 16) {
+            const uint64_t w = r[(int64_t)k * (kSureBins / 4)];
+            c[0] += (uint32_t)w & 0xffffu;
+            c[1] += (uint32_t)w >> 16;
+            c[2] += (uint32_t)(w >> 32) & 0xffffu;
+            c[3] += (uint32_t)(w >> 48);
+        }
+    } else {
+        typedef uint32_t U4 __attribute__((ext_vector_type(4)));
+        const HYRES_GLOBAL U4* r = (const HYRES_GLOBAL U4*)rows + bin / 4;
+#pragma unroll 16
+        for (int k = share; k < d.snch; k += 16) {
+            const U4 w = r[(int64_t)k * (kSureBins / 4)];
+            c[0] += w[0];
+            c[1] += w[1];
+            c[2] += w[2];
+            c[3] += w[3];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) part[share][4 * (tid & 15) + j] = c[j];
+    __syncthreads();
+    HYRES_GLOBAL uint32_t* out = rows + (int64_t)d.snch * kSureBins;
+    if (tid < 64) {
+        uint32_t t = 0;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) t += part[k][tid];
+        out[b0 + tid] = t;
+    }
+    for (int k = tid; k < 3 * kSureRefine * 64; k += 256) out[(1 + k / 64) * kSureBins + b0 + k % 64] = 0u;
+    if (b0 == 0 && tid <= kSureRefine) d.ssel[comp * (kSureRefine + 1) + tid].count = 0u;
+}
+
 template <typename T>
 __global__ __launch_bounds__(kSureThreads) void k_sure_gather(const CubeDesc* __restrict__ descs,
                                                               const int* __restrict__ items, int ncubes) {
@@ -434,7 +515,11 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_gather(const CubeDesc* __
     uint32_t c[kBinsPer] = {0, 0, 0, 0};
     static_assert(kBinsPer == 4, "rows are read four bins at a time");
     const HYRES_GLOBAL uint32_t* rows = gmem(d.shist) + comp * d.shcs;
-    if (d.schunk <= kSureRow16) {
+    if (d.srounds) {
+        const HYRES_GLOBAL uint32_t* r = rows + (int64_t)nch * kSureBins + kBinsPer * tid;
+#pragma unroll
+        for (int j = 0; j < kBinsPer; ++j) c[j] = r[j];
+    } else if (d.schunk <= kSureRow16) {
         const HYRES_GLOBAL uint64_t* r = (const HYRES_GLOBAL uint64_t*)rows + tid;
         for (int k = 0; k < nch; k += 16) {
             uint64_t x[16];
@@ -469,38 +554,24 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_gather(const CubeDesc* __
     uint64_t klo = 1, khi = 1;
     if (first >= 0) first_range<T>(first, last, &klo, &khi);
     if (chunk == 0 && tid == 0) {
-        SureSel* s = d.ssel + comp;
+        SureSel* s = d.ssel + comp * (kSureRefine + 1);
         s->klo = klo;
         s->khi = khi;
         s->c0 = c0;
+        s->U = __builtin_inf();
+        s->Ut = 0.0;
         s->zeros = zeros;
     }
     if (first < 0) return;
     HYRES_GLOBAL T* seg = gmem(static_cast<T*>(d.slist)) + comp * d.slcs + (int64_t)chunk * d.segcap;
-    const uint32_t cap = (uint32_t)d.segcap;
     double s0 = 0.0;
     for (int64_t e = e0 + tid - lane; e < e1; e += U * kSureThreads) {   // whole waves
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = e + lane + (int64_t)u * kSureThreads < e1 ? v[u] : (T)0;
-        bool in[U];
-        uint32_t n = 0;
-#pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint64_t k = KT::key(v[u]);
-            in[u] = k >= klo && k < khi;
-            n += (uint32_t)__popcll(__ballot(in[u]));
-            if (k < klo) s0 = fma((double)v[u], (double)v[u], s0);
+            v[u] = e + lane + (int64_t)u * kSureThreads < e1 ? v[u] : (T)0;
+            if (KT::key(v[u]) < klo) s0 = fma((double)v[u], (double)v[u], s0);
         }
-        uint32_t at = 0;
-        if (lane == 0 && n) at = atomicAdd(&sh.count, n);
-        at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const unsigned long long m = __ballot(in[u]);
-            const uint32_t pos = at + (uint32_t)__popcll(m & ((1ull << lane) - 1));
-            if (in[u] && pos < cap) seg[pos] = v[u];
-            at += (uint32_t)__popcll(m);
-        }
+        keep_range<T>(v, klo, khi, seg, (uint32_t)d.segcap, &sh.count);
         if (e + U * kSureThreads < e1) fetch(e + U * kSureThreads);
     }
     s0 = wave_sum(s0);
@@ -584,6 +655,209 @@ __device__ __forceinline__ void block_argmin(double& s, double& t, SureShared& s
     wave_argmin(s, t);
 }
 
+// ---- large components: the range narrowed by all blocks before the finish ----
+// (its list grows with the component, about 4 % of the values and an eighth of that a
+// round later, and the one block reads it several times: of 67 million values the
+// search took 2.8 ms, 2.35 of them the finish; 0.31 with two rounds)
+
+// Values of a list, of a segment or of a chunk.
+template <typename T>
+struct SurePart {
+    const HYRES_GLOBAL T* p;
+    int64_t m;
+};
+template <typename T>
+__device__ __forceinline__ SurePart<T> sure_chunk_part(const CubeDesc& d, int comp, int chunk) {
+    const int64_t e0 = (int64_t)chunk * d.schunk;
+    return {gmem(static_cast<const T*>(d.coef)) + (int64_t)comp * d.ncs + e0, min(d.schunk, sure_count(d) - e0)};
+}
+// The gather's: a chunk's segment, or the chunk itself where the segment overflowed.
+template <typename T>
+__device__ __forceinline__ SurePart<T> sure_segment(const CubeDesc& d, int comp, int chunk, uint32_t count) {
+    if (count > (uint32_t)d.segcap) return sure_chunk_part<T>(d, comp, chunk);
+    return {gmem(static_cast<const T*>(d.slist)) + comp * d.slcs + (int64_t)chunk * d.segcap, (int64_t)count};
+}
+// A round's: one list per component, in the halves of its space in turn (the
+// segments are in the first).
+template <typename T>
+__device__ __forceinline__ HYRES_GLOBAL T* sure_list(const CubeDesc& d, int comp, int round) {
+    return gmem(static_cast<T*>(d.slist)) + comp * d.slcs + (round & 1 ? d.segcap * d.snch : 0);
+}
+// Values that a block of round `round` takes.
+template <typename T>
+__device__ __forceinline__ SurePart<T> sure_share(const CubeDesc& d, int comp, int chunk, int round, uint32_t count) {
+    if (round == 0) return sure_segment<T>(d, comp, chunk, d.sseg[(int64_t)comp * kSureMaxChunks + chunk].count);
+    if ((int64_t)count > d.segcap * d.snch) return sure_chunk_part<T>(d, comp, chunk);
+    const int64_t per = ((int64_t)count + d.snch - 1) / d.snch, a = min(chunk * per, (int64_t)count);
+    return {sure_list<T>(d, comp, round) + a, min(per, (int64_t)count - a)};
+}
+// Row of counts and row of sums of squares of round `round`, behind the count rows.
+__device__ __forceinline__ HYRES_GLOBAL uint32_t* refine_counts(const CubeDesc& d, int comp, int round) {
+    return gmem(d.shist) + comp * d.shcs + (int64_t)(d.snch + 1 + 3 * round) * kSureBins;
+}
+__device__ __forceinline__ HYRES_GLOBAL double* refine_sums(const CubeDesc& d, int comp, int round) {
+    return (HYRES_GLOBAL double*)(refine_counts(d, comp, round) + kSureBins);
+}
+
+// Histogram of counts and sums of squares over the range, added to the component's rows.
+template <typename T>
+__global__ __launch_bounds__(kSureThreads) void k_sure_refine(const CubeDesc* __restrict__ descs,
+                                                              const int* __restrict__ items, int ncubes, int round) {
+    typedef KeyTraits<T> KT;
+    __shared__ uint32_t cnt[kSureBins];
+    __shared__ double sum[kSureBins];
+    const int cu = find_cube(items, ncubes, blockIdx.x);
+    const CubeDesc& d = descs[cu];
+    const int nch = d.snch, local = blockIdx.x - items[cu], comp = local / nch, chunk = local - comp * nch;
+    const int tid = threadIdx.x;
+    if (round >= d.srounds) return;
+    const SureSel s = d.ssel[comp * (kSureRefine + 1) + round];
+    if (s.khi <= s.klo) return;
+    for (int b = tid; b < kSureBins; b += kSureThreads) {
+        cnt[b] = 0;
+        sum[b] = 0.0;
+    }
+    __syncthreads();
+    const SurePart<T> a = sure_share<T>(d, comp, chunk, round, s.count);
+    const int shf = shift_for(s.khi - s.klo);
+    constexpr int U = kSureLoads;
+    for (int64_t e = tid; e < a.m; e += U * kSureThreads) {
+        T v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = e + (int64_t)u * kSureThreads;
+            v[u] = a.p[i < a.m ? i : a.m - 1];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint64_t k = KT::key(v[u]);
+            if (e + (int64_t)u * kSureThreads < a.m && k >= s.klo && k < s.khi) {
+                const int b = (int)((k - s.klo) >> shf);
+                atomicAdd(&cnt[b], 1u);
+                atomicAdd(&sum[b], (double)v[u] * (double)v[u]);
+            }
+        }
+    }
+    __syncthreads();
+    HYRES_GLOBAL uint32_t* gc = refine_counts(d, comp, round);
+    HYRES_GLOBAL double* gs = refine_sums(d, comp, round);
+    for (int b = tid; b < kSureBins; b += kSureThreads)
+        if (cnt[b]) {
+            atomicAdd(&gc[b], cnt[b]);
+            atomicAdd(&gs[b], sum[b]);
+        }
+}
+
+// Select on those rows by every block, then the chunk's values in the narrower range.
+template <typename T>
+__global__ __launch_bounds__(kSureThreads) void k_sure_narrow(const CubeDesc* __restrict__ descs,
+                                                              const int* __restrict__ items, int ncubes, int round) {
+    __shared__ SureShared sh;
+    const int cu = find_cube(items, ncubes, blockIdx.x);
+    const CubeDesc& d = descs[cu];
+    const int nch = d.snch, local = blockIdx.x - items[cu], comp = local / nch, chunk = local - comp * nch;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (round >= d.srounds) return;
+    const SureSel* s = d.ssel + comp * (kSureRefine + 1) + round;
+    const uint64_t klo = s->klo, khi = s->khi, c0 = s->c0;
+    SureSel* o = d.ssel + comp * (kSureRefine + 1) + round + 1;     // written by the first chunk's block, read by the next launch
+    if (khi <= klo) {
+        if (chunk == 0 && tid == 0) {
+            o->klo = o->khi = 1;
+            o->U = s->U;
+            o->Ut = s->Ut;
+            o->zeros = s->zeros;
+        }
+        return;
+    }
+    const double N = (double)sure_count(d);
+    const SureSeg* sg = d.sseg + (int64_t)comp * kSureMaxChunks;
+    double s0 = 0.0;
+    if (round == 0) {
+        // squares below the range: lane sums of every 64th chunk, the same in every wave
+        for (int k = lane; k < nch; k += 64) s0 += sg[k].s0;
+        s0 = wave_sum(s0);
+    } else {
+        s0 = s->s0;
+    }
+    uint32_t c[kBinsPer], pc;
+    double q[kBinsPer], lb[kBinsPer], ps, us, ut;
+    const HYRES_GLOBAL uint32_t* gc = refine_counts(d, comp, round) + kBinsPer * tid;
+    const HYRES_GLOBAL double* gs = refine_sums(d, comp, round) + kBinsPer * tid;
+#pragma unroll
+    for (int j = 0; j < kBinsPer; ++j) {
+        c[j] = gc[j];
+        q[j] = gs[j];
+    }
+    const int shf = shift_for(khi - klo);
+    range_select<T>(c, q, N, klo, khi, shf, c0, s0, sh, &pc, &ps, lb, &us, &ut);
+    block_argmin(us, ut, sh);
+    double U = s->U, Ut = s->Ut;
+    if (us < U) {
+        U = us;
+        Ut = ut;
+    }
+    const double U0 = fmin(U, N - 2.0 * (double)s->zeros), lim = U0 + 1e-12 * (fabs(U0) + N);
+    int f = 0x7fffffff, l = -1;
+#pragma unroll
+    for (int j = 0; j < kBinsPer; ++j)
+        if (lb[j] <= lim) {
+            const int b = kBinsPer * tid + j;
+            f = b < f ? b : f;
+            l = b;
+        }
+    const int wf = wave_minmax_i32<false>(f), wl = wave_minmax_i32<true>(l);
+    __syncthreads();
+    if (lane == 63) {
+        sh.wf[wave] = wf;
+        sh.wl[wave] = wl;
+    }
+    __syncthreads();
+    f = waves_minmax<false>(sh.wf);
+    l = waves_minmax<true>(sh.wl);
+    uint64_t nlo = 1, nhi = 1;
+    if (l >= 0) {
+        const uint64_t end = klo + ((uint64_t)(l + 1) << shf);
+        nlo = klo + ((uint64_t)f << shf);
+        nhi = end < khi ? end : khi;
+    }
+    if (chunk == 0) {
+        if (tid == (l >= 0 ? f / kBinsPer : 0)) {
+            uint64_t cf = c0 + pc;
+            double sf = s0 + ps;
+#pragma unroll
+            for (int j = 0; j < kBinsPer; ++j)
+                if (l >= 0 && kBinsPer * tid + j < f) {
+                    cf += c[j];
+                    sf += q[j];
+                }
+            o->klo = nlo;
+            o->khi = nhi;
+            o->c0 = cf;
+            o->s0 = sf;
+            o->U = U;
+            o->Ut = Ut;
+            o->zeros = s->zeros;
+        }
+    }
+    if (l < 0) return;
+    const SurePart<T> a = sure_share<T>(d, comp, chunk, round, s->count);
+    HYRES_GLOBAL T* list = sure_list<T>(d, comp, round + 1);
+    const uint32_t cap = (uint32_t)(d.segcap * nch);
+    constexpr int V = kSureLoads;
+    for (int64_t e = tid - lane; e < a.m; e += V * kSureThreads) {     // whole waves
+        T v[V];
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+            const int64_t i = e + lane + (int64_t)u * kSureThreads;
+            v[u] = a.p[i < a.m ? i : a.m - 1];
+        }
+#pragma unroll
+        for (int u = 0; u < V; ++u) v[u] = e + lane + (int64_t)u * kSureThreads < a.m ? v[u] : (T)0;
+        keep_range<T>(v, nlo, nhi, list, cap, &o->count);
+    }
+}
+
 // A range of keys to search: values and squares below it, a lower bound.
 struct SureRange {
     uint64_t klo, khi, c0;
@@ -605,7 +879,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
     __shared__ SureRange stack[kSureStack];
     __shared__ SureShared sh;
     __shared__ int s_sp, s_inexact, s_wlo[kSureWindows], s_whi[kSureWindows];
-    __shared__ uint32_t s_count[kSureMaxChunks];
+    __shared__ uint32_t s_count[kSureChunks];
     const int cu = find_cube(items, ncubes, blockIdx.x);
     const CubeDesc& d = descs[cu];
     const int comp = blockIdx.x - items[cu];
@@ -614,10 +888,10 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
     const double N = (double)Ni;
     const int nch = d.snch;
     const HYRES_GLOBAL T* coef = gmem(static_cast<const T*>(d.coef)) + (int64_t)comp * d.ncs;
-    const HYRES_GLOBAL T* list = gmem(static_cast<const T*>(d.slist)) + comp * d.slcs;
-    // f(value) for each of the values: the coefficients, taken by the whole block;
-    // or the chunks' segments (the chunk itself where its segment overflowed), in
-    // parts that the waves take in turn.
+    // f(value) for each of the values: the coefficients, or the list of the last
+    // round, taken by the whole block; or the chunks' segments, in parts that the
+    // waves take in turn.
+    SurePart<T> whole = {coef, Ni};
     const int parts = (kSureWaves + nch - 1) / nch;
     auto run = [&](const HYRES_GLOBAL T* p, int64_t a, int64_t b, int stride, auto f) {
         constexpr int U = kSureLoads;
@@ -633,23 +907,22 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
         }
     };
     auto for_each = [&](auto f) {
-        if (nch == 1) {
-            run(coef, tid, Ni, kSureThreads, f);
+        if (whole.p) {
+            run(whole.p, tid, whole.m, kSureThreads, f);
             return;
         }
         for (int u = wave; u < nch * parts; u += kSureWaves) {
             const int s = u / parts, part = u - s * parts;
-            const bool fits = s_count[s] <= (uint32_t)d.segcap;
-            const int64_t m = fits ? (int64_t)s_count[s] : min(d.schunk, Ni - (int64_t)s * d.schunk);
-            const int64_t step = (m + parts - 1) / parts, a = part * step, b = min(a + step, m);
-            run(fits ? list + (int64_t)s * d.segcap : coef + (int64_t)s * d.schunk, a + lane, b, 64, f);
+            const SurePart<T> q = sure_segment<T>(d, comp, s, s_count[s]);
+            const int64_t step = (q.m + parts - 1) / parts, a = part * step, b = min(a + step, q.m);
+            run(q.p, a + lane, b, 64, f);
         }
     };
 
     uint32_t zeros = 0;
     uint64_t klo = 1, khi = 1, c0 = 0;
-    double s0 = 0.0;
-    int64_t values = Ni, visits = 0;          // of a pass; read so far
+    double s0 = 0.0, U = __builtin_inf(), Ut = 0.0;
+    int64_t visits = 0;                       // values read so far
     bool need_s0 = false;
     if (nch == 1) {
         for (int b = tid; b < kSureBins; b += kSureThreads) cnt[b] = 0;
@@ -667,28 +940,40 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
         if (first >= 0) first_range<T>(first, last, &klo, &khi);
         need_s0 = true;
     } else {
-        const SureSel s = d.ssel[comp];
+        const SureSel s = d.ssel[comp * (kSureRefine + 1) + d.srounds];
         klo = s.klo;
         khi = s.khi;
         c0 = s.c0;
         zeros = s.zeros;
-        const SureSeg* sg = d.sseg + (int64_t)comp * kSureMaxChunks;
-        if (khi > klo) {
-            for (int k = tid; k < nch; k += kSureThreads) {
-                s_count[k] = sg[k].count;
-                sum[k] = sg[k].s0;
-            }
-            __syncthreads();
-            values = 0;
+        U = s.U;
+        Ut = s.Ut;
+        if (d.srounds) {
+            s0 = s.s0;
+            if ((int64_t)s.count <= d.segcap * nch) whole = {sure_list<T>(d, comp, d.srounds), (int64_t)s.count};
+        } else {
+            whole.p = nullptr;
+            const SureSeg* sg = d.sseg + (int64_t)comp * kSureMaxChunks;
+            if (khi > klo) {
+                for (int k = tid; k < nch; k += kSureThreads) {
+                    s_count[k] = sg[k].count;
+                    sum[k] = sg[k].s0;
+                }
+                __syncthreads();
+                whole.m = 0;
 #pragma unroll 8
-            for (int k = 0; k < nch; ++k) {
-                s0 += sum[k];
-                values += min(s_count[k], (uint32_t)d.schunk);
+                for (int k = 0; k < nch; ++k) {
+                    s0 += sum[k];
+                    whole.m += min(s_count[k], (uint32_t)d.schunk);
+                }
             }
         }
     }
     // candidate 0 and the smallest upper bound so far
-    double best_s = N - 2.0 * (double)zeros, best_t = 0.0, U = best_s, Ut = 0.0;
+    double best_s = N - 2.0 * (double)zeros, best_t = 0.0;
+    if (best_s <= U) {
+        U = best_s;
+        Ut = 0.0;
+    }
     if (tid == 0) {
         s_sp = 0;
         s_inexact = 0;
@@ -715,14 +1000,14 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
         __syncthreads();
         if (tid == 0) s_sp = sp - 1;
         if (skip) continue;
-        if (visits + values > kSureVisits) {
+        if (visits + whole.m > kSureVisits) {
             if (tid == 0) {
                 s_inexact = 1;
                 s_sp = 0;
             }
             continue;
         }
-        visits += values;
+        visits += whole.m;
         const int shf = shift_for(khi - klo);
         for (int b = tid; b < kSureBins; b += kSureThreads) {
             cnt[b] = 0;
@@ -962,31 +1247,51 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
 }
 
 // ---------------------------------------------------------------- launchers
-hipError_t launch_sure(int dtype, int step, const CubeDesc* descs, const int* items, int ncubes, int grid,
+hipError_t launch_sure(int dtype, int step, const CubeDesc* descs, const int* items, int ncubes, int grid, int round,
                        hipStream_t s) {
-#define HYRES_S(K)                                                                                                \
-    if (dtype == HYRES_F64) hipLaunchKernelGGL(K<double>, dim3(grid), dim3(kSureThreads), 0, s, descs, items, ncubes); \
-    else hipLaunchKernelGGL(K<float>, dim3(grid), dim3(kSureThreads), 0, s, descs, items, ncubes)
-    if (step == 0) HYRES_S(k_sure_hist);
-    else if (step == 1) HYRES_S(k_sure_gather);
-    else HYRES_S(k_sure_finish);
+#define HYRES_S(K, TH, ...)                                                                                   \
+    if (dtype == HYRES_F64) hipLaunchKernelGGL(K<double>, dim3(grid), dim3(TH), 0, s, descs, items, ncubes __VA_ARGS__); \
+    else hipLaunchKernelGGL(K<float>, dim3(grid), dim3(TH), 0, s, descs, items, ncubes __VA_ARGS__);           \
+    break
+    switch (step) {
+        case SURE_HIST: HYRES_S(k_sure_hist, kSureThreads);
+        case SURE_ROWS: HYRES_S(k_sure_rows, 256);
+        case SURE_GATHER: HYRES_S(k_sure_gather, kSureThreads);
+        case SURE_REFINE: HYRES_S(k_sure_refine, kSureThreads, , round);
+        case SURE_NARROW: HYRES_S(k_sure_narrow, kSureThreads, , round);
+        case SURE_FINISH: HYRES_S(k_sure_finish, kSureThreads);
+        default: return hipErrorInvalidValue;
+    }
 #undef HYRES_S
     return hipGetLastError();
 }
 
+// Refining rounds before the finish.  The line lies where a round costs what it saves:
+// one component of 2^20 values takes 75 us without and 65 with it, eight 82 and
+// 85; of 2^21 values 109 and 82, 153 and 129; of 2^24 569 and 159.
+int sure_rounds(int64_t N) {
+    if (N <= kSureLarge) return 0;
+    return N <= ((int64_t)1 << 24) ? 1 : N <= ((int64_t)1 << 28) ? 2 : kSureRefine;
+}
+// Words of the rows behind the count rows: the summed row and the refining rounds'.
+int64_t sure_extra(int64_t N) { return N > kSureLarge ? (1 + 3 * kSureRefine) * (int64_t)kSureBins : 0; }
+
 // Chunks of one component of N values in a program of `total` values: one per
-// compute unit over all components, of at least 16384 values, at most `room`
-// (rows that fit) and kSureMaxChunks.  Components of up to kSureDirect values
-// take one block for the whole search (two launches fewer; a block reads 65536
-// values in 2 us).  Up to 64 chunks of 16-bit counts before longer ones.
+// compute unit over all components, of at least 16384 values, at most those whose
+// rows fit in `room` words and kSureChunks (kSureMaxChunks of a large component, whose
+// rows a launch of their own adds up).  Components of up to kSureDirect values take one
+// block for the whole search (two launches fewer; a block reads 65536 values in 2 us).
+// Up to 64 chunks of 16-bit counts before longer ones.
 int sure_chunks(int64_t N, int64_t total, int num_cu, int64_t room) {
     if (N <= kSureDirect) return 1;
+    const int64_t most = N > kSureLarge ? kSureMaxChunks : kSureChunks;
     int64_t ch = (total + num_cu - 1) / num_cu;
     if (ch < 16384) ch = 16384;
     int64_t nch = (N + ch - 1) / ch;
     if (N <= 64 * kSureRow16 && (N + nch - 1) / nch > kSureRow16 - 1024) nch = (N + kSureRow16 - 1025) / (kSureRow16 - 1024);
-    if (nch > 64) nch = 64;
-    if (nch > room) nch = room;
+    if (nch > most) nch = most;
+    const int64_t rows = (room - sure_extra(N)) / kSureBins;
+    if (nch > rows) nch = rows;
     return nch < 1 ? 1 : (int)nch;
 }
 int64_t sure_chunk(int64_t N, int nch) {
