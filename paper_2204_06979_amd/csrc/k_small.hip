@@ -79,9 +79,13 @@ __device__ __forceinline__ int sturm_count(const double (&dv)[T], const double (
 }
 
 // 1 / d and sqrt(s) for normal s > 0: the hardware estimates (24 bits) and
-// Newton steps, to about one unit in the last place, without the scaling
-// steps of the general division and square root (their latency is on the
-// chain of every elimination step).
+// Newton steps, without the scaling steps of the general division and square
+// root (their latency is on the chain of every elimination step).  The last step
+// rounds once: against 1 / d and sqrt(s) over 2^20 arguments of every exponent,
+// 1 / d differs for 6 of the 256 fractions next to two and nowhere else (by one unit
+// in the last place, quotients below 2^-1022 included), the root only below 2^-970
+// (by one unit; its residual is subnormal there).
+constexpr double kTiny = 0x1p-1022;            // smallest normal number
 __device__ __forceinline__ double recip(double d) {
     double r = __builtin_amdgcn_rcp(d);
     r = fma(fma(-d, r, 1.0), r, r);
@@ -524,8 +528,9 @@ __global__ __launch_bounds__(64 * Cols<T>::NW) void k_small(const CubeDesc* __re
                             y[j] = (q[0] + q[1]) + (q[2] + q[3]);
                         }
                     });
-                    const bool some = ss > 1e-200;       // else the row is taken as tridiagonal already
-                    const double nr = root(fmax(ss, 1e-200)), nrm = some ? nr : 0.0;
+                    // a row whose squares vanish is taken as tridiagonal already
+                    const bool some = ss >= kTiny;
+                    const double nr = root(fmax(ss, kTiny)), nrm = some ? nr : 0.0;
                     alpha = x1 >= 0.0 ? -nrm : nrm;
                     const double b = recip(nr * (nr + fabs(x1)));     // 2 / v^T v
                     beta = some ? b : 0.0;
