@@ -51,17 +51,18 @@ __device__ __forceinline__ double row_bcast(double v) {
 // exactly zero counts as positive); both minors are rescaled by a power of two
 // every 8 steps so the recursion stays in range.  Lane c of a row of 16 holds
 // d_i and e_{i-1}^2 of i = 16 b + c (entries past the matrix: d = 3, e = 0, no sign
-// change for x < 3); a step is two broadcasts, three FP64 operations and one that
+// change for x < 3; whole groups of eight of them are left out); a step is two broadcasts, three FP64 operations and one that
 // shifts the sign into a word: 24 issue cycles, no LDS (broadcast 16-byte reads of
 // all waves were its bound before, 49 cycles a step).  Call with all sixteen lanes
 // of a row active: a lane that is off broadcasts zeros.
 template <int T>
-__device__ __forceinline__ int sturm_count(const double (&dv)[T], const double (&ev)[T], double x) {
+__device__ __forceinline__ int sturm_count(const double (&dv)[T], const double (&ev)[T], int p, double x) {
     double pm2 = 0.0, pm1 = 1.0;
     uint32_t bits = 0;                         // signs of the minors, the latest lowest
     int cnt = 0;
     static_for<2 * T>([&](auto h) {
         constexpr int b = decltype(h)::value / 2, c0 = 8 * (decltype(h)::value % 2);
+        if (8 * decltype(h)::value >= p) return;
         static_for<8>([&](auto u) {
             constexpr int c = c0 + decltype(u)::value;
             const double pi = fma(row_bcast<c>(dv[b]) - x, pm1, -row_bcast<c>(ev[b]) * pm2);
@@ -663,7 +664,7 @@ __global__ __launch_bounds__(64 * Cols<T>::NW) void k_small(const CubeDesc* __re
                     double lo = -1.0 - 1e-12, hi = 1.0 + 1e-12;
                     for (int it = 0; it < iters; ++it) {
                         const double x = lo + (hi - lo) * ((double)(m + 1) * inv_m1);
-                        const int cnt = sturm_count<T>(dv, ev2, x);
+                        const int cnt = sturm_count<T>(dv, ev2, p, x);
                         const bool below = cnt <= midx;   // x <= lambda
                         double lo_c = below ? x : lo;
                         double hi_c = below ? hi : x;
