@@ -418,7 +418,7 @@ struct Launch {
 
 // Small-solve kernel classes by band count (the kernel is specialised on the
 // register tiling of the p x p matrix).
-constexpr int kSmallClassMax[] = {32, 64, 96, 128, 144, 160, 176, 192, 224};
+constexpr int kSmallClassMax[] = {16, 32, 64, 96, 128, 144, 160, 176, 192, 224};
 constexpr int kSmallClasses = (int)(sizeof(kSmallClassMax) / sizeof(int));
 int small_class(int p) {
     for (int i = 0; i < kSmallClasses; ++i)
