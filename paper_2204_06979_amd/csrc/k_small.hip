@@ -9,8 +9,8 @@
 // squares 1/[G^-1]_ii (Schur complement), which is why the noise estimate only
 // needs the diagonal of the inverse Gram.
 //
-// The p x p matrix lives in registers by columns (T = ceil(p / 16) column
-// tiles): lane (g, c) = (lane / 16, lane mod 16) of the wave that owns column
+// The p x p matrix lives in registers by columns (T tiles of 16 columns, those of
+// the largest band count of its class, so that cubes of one class share a launch): lane (g, c) = (lane / 16, lane mod 16) of the wave that owns column
 // tile w holds, of column 16 w + c, the rows 4 e + g, e < 4 T.  A vector that
 // multiplies the rows is read from LDS as T / 4 registers, lane (g, c) holding its
 // entries of rows 4 (16 m + c) + g, and a product with row 4 (16 m + c') + g takes
@@ -101,7 +101,7 @@ __device__ __forceinline__ double root(double s) {
     return fma(fma(-w, w, s), h, w);
 }
 
-// In place: lo = max and hi = min over each aligned group of M lanes (M = 4, 16, 32 or 64).
+// In place: lo = max and hi = min over each aligned group of M lanes (M = 4, 16 or 64).
 __device__ __forceinline__ void group_maxmin(double& lo, double& hi, int M) {
     double a;
     a = dpp_f64<0xB1>(lo); lo = a > lo ? a : lo;      // quad_perm [1,0,3,2]
@@ -120,12 +120,6 @@ __device__ __forceinline__ void group_maxmin(double& lo, double& hi, int M) {
                  h3 = readlane_f64(hi, 48);
     const double la = l0 > l1 ? l0 : l1, lb = l2 > l3 ? l2 : l3;
     const double ha = h0 < h1 ? h0 : h1, hb = h2 < h3 ? h2 : h3;
-    if (M == 32) {
-        const bool upper = (threadIdx.x & 32) != 0;
-        lo = upper ? lb : la;
-        hi = upper ? hb : ha;
-        return;
-    }
     lo = la > lb ? la : lb;
     hi = ha < hb ? ha : hb;
 }
@@ -1328,13 +1322,13 @@ hipError_t launch_adj_sweep(const AdjDesc& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-// Kernel variant for p bands: T = ceil(p / 16) column tiles.
+// Kernel variant of the class of up to p bands: T = p / 16 column tiles.
 hipError_t launch_small(int p, const CubeDesc* descs, const int* cubes, int ncls, hipStream_t s) {
     switch ((p + 15) / 16) {
 #define HYRES_S(T) \
     case T: hipLaunchKernelGGL(k_small<T>, dim3(ncls), dim3(64 * Cols<T>::NW), 0, s, descs, cubes, ncls); break;
-        HYRES_S(1) HYRES_S(2) HYRES_S(3) HYRES_S(4) HYRES_S(5) HYRES_S(6) HYRES_S(7)
-        HYRES_S(8) HYRES_S(9) HYRES_S(10) HYRES_S(11) HYRES_S(12) HYRES_S(13) HYRES_S(14)
+        HYRES_S(1) HYRES_S(2) HYRES_S(4) HYRES_S(6) HYRES_S(8) HYRES_S(9) HYRES_S(10) HYRES_S(11) HYRES_S(12)
+        HYRES_S(14)
 #undef HYRES_S
         default: return hipErrorInvalidValue;
     }
