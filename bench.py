@@ -489,11 +489,11 @@ def run_tiled(args, api, synth, precs):
                              "scaled to the 25 tiles (blend not timed)"}
 
 
-# VALU lane-operations per band and sweep of the l1-l1 stage: forward
-# elimination with the fused shrinkage and Bregman updates (d: 1, its
-# difference to h: 1, clip: 1, a: 1, v: 2, clip: 1, c: 1, right-hand side: 2,
-# pivot: 1, carry: 1) and the back substitution (1).
-L1_OPS_PER_BAND_SWEEP = 13
+# VALU lane-operations per band and sweep of the l1-l1 stage at mu2 = 1: forward
+# elimination with the fused shrinkage and Bregman updates (t: 2, clip: 1,
+# a: 2, v: 2, clip: 1, c and its difference: 2, right-hand side: 1, pivot: 2)
+# and the back substitution (1).
+L1_OPS_PER_BAND_SWEEP = 14
 # FP32 vector peak without packed math: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz
 VALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 

@@ -9,7 +9,10 @@
 // segment of M bands of x, b1 and b2 in registers (indices resolved at compile
 // time) and its part of h in LDS.  The shrinkage and Bregman updates of sweep
 // k are fused into the forward elimination of sweep k+1 (they only need x of
-// sweep k), with the clipped Bregman variables as the state:
+// sweep k), with the clipped Bregman variables as the state, summed from the
+// differences h - x and D x at their own small size (x - b1 in place of them is an
+// operation less, but rounds b1 at the size of x, sweep after sweep: twice the error
+// at mu1 / mu2 = 0.02, seven times at 0.001):
 //   t = h - x + b1,  b1' = clip(t, 1/mu1),  h - s + b1' = h - t + 2 b1'
 //   v = x_{i+1} - x_i + b2_i,  b2_i' = clip(v, lam/mu2),  u_i - b2_i' = v - 2 b2_i'
 // The tridiagonal solve of a pixel runs as S local Thomas solves of the
@@ -49,14 +52,28 @@ __device__ __forceinline__ int opaque_zero() {
     return z;
 }
 
+// The back substitution reads its table again where a lane that holds it since the
+// elimination (x, b1, b2 and the table, and 20 + 4 S values more) has no room beside a
+// second wave, and one that does not has.  256 x 256 pixels, 50 sweeps: 128 bands in
+// FP32 355 us held, 235 read again; 224 697 and 508; 144 (two waves either way) 247
+// and 283.  A table of its own (mu2 not one) is read early by the compiler where
+// that rule does not stop it: 64 bands in FP64 273 and 207, in FP32 no difference.
+template <typename T, int M, int S, bool UNIT>
+constexpr bool kReread = (UNIT ? S > 1 && (int)sizeof(T) / 4 * (4 * M + 20 + 4 * S) > 256 : sizeof(T) == 8) &&
+                         (int)sizeof(T) / 4 * (3 * M + 20 + 4 * S) <= 256;
+
 }  // namespace
 
-template <typename T, int M, int S>
-__global__ __launch_bounds__(64) void k_l1l1(L1Args a, int64_t groups) {
+// UNIT: mu2 is one, and the products with it are left out (they are exact).
+// At most two waves per SIMD: for a third the compiler gives up loads in flight (36
+// bands in FP32 92 us, 77 with two; 144 bands and mu2 = 1.3 303 and 275).
+template <typename T, int M, int S, bool UNIT>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 2))) void k_l1l1(L1Args a, int64_t groups) {
     constexpr int PPB = 64 / S;                 // pixels per block
     constexpr int NI = 2 * (S - 1);             // interface unknowns
     __shared__ T s_h[M][64];                    // h, band-major (lane-private columns)
-    __shared__ __align__(16) T s_f[S][M];       // block Thomas: -e / beta_i = mu2 / beta_i (0 beyond the cube)
+    // block Thomas: 1 / beta_i (0 beyond the cube) and -e / beta_i = mu2 / beta_i
+    __shared__ __align__(16) T s_inv[S][M], s_f[UNIT ? 1 : S][UNIT ? 1 : M];
     __shared__ __align__(16) T s_wr[S][M], s_wl[S][M];   // spikes of the last / first row coupling
     __shared__ T s_r[NI > 0 ? NI : 1][NI > 0 ? NI : 1];   // inverse of the interface system
     __shared__ double s_tip[S][2][2];           // spike values at the ends of each block [s][wr/wl][first/last]
@@ -69,8 +86,7 @@ __global__ __launch_bounds__(64) void k_l1l1(L1Args a, int64_t groups) {
         const int l = p - seg * M;
         return l < 0 ? 0 : (l > M ? M : l);
     }();
-    // (a mu1 / mu2 beyond 1e30 changes no result: x = a then)
-    const double mu2 = a.mu2, mu1 = a.mu1 < 1e30 * mu2 ? a.mu1 : 1e30 * mu2;
+    const double mu1 = a.mu1, mu2 = a.mu2;
 
     // ---------------------------------------------------------- block tables
     // Factors of each diagonal block of M = mu1 I + mu2 D^T D and its spikes
@@ -87,7 +103,8 @@ __global__ __launch_bounds__(64) void k_l1l1(L1Args a, int64_t groups) {
             s_beta[s][i] = i == 0 ? dg : dg - e * e / s_beta[s][i - 1];
         }
         for (int i = 0; i < M; ++i) {
-            s_f[s][i] = i < L ? (T)(mu2 / s_beta[s][i]) : (T)0;
+            s_inv[s][i] = i < L ? (T)(1.0 / s_beta[s][i]) : (T)0;
+            if constexpr (!UNIT) s_f[s][i] = i < L ? (T)(mu2 / s_beta[s][i]) : (T)0;
             s_wr[s][i] = (T)0;
             s_wl[s][i] = (T)0;
         }
@@ -143,8 +160,8 @@ __global__ __launch_bounds__(64) void k_l1l1(L1Args a, int64_t groups) {
         __syncthreads();
     }
 
-    const T t1 = (T)(1.0 / a.mu1), t2 = (T)(a.lam / mu2);
-    const T rho = (T)(mu1 / mu2);
+    const T t1 = (T)(1.0 / mu1), t2 = (T)(a.lam / mu2);
+    const T m1 = (T)mu1, m2 = (T)mu2;
     // rows of D this lane owns: every band but the cube's last; the last band
     // of a block before a boundary uses the next block's first x
     const int vlen = seg < S - 1 ? M : lenS - 1;
@@ -178,7 +195,8 @@ __global__ __launch_bounds__(64) void k_l1l1(L1Args a, int64_t groups) {
             const int z0 = opaque_zero();
             const T* hcol = &s_h[0][lane + z0];
             // (rows of a multiple of four entries: four to a read)
-            const T* tf = static_cast<const T*>(__builtin_assume_aligned(&s_f[seg][z0], 16));
+            const T* tinv = static_cast<const T*>(__builtin_assume_aligned(&s_inv[seg][z0], 16));
+            const T* tf = UNIT ? tinv : static_cast<const T*>(__builtin_assume_aligned(&s_f[UNIT ? 0 : seg][z0], 16));
             const T* twr = static_cast<const T*>(__builtin_assume_aligned(&s_wr[seg][z0], 16));
             const T* twl = static_cast<const T*>(__builtin_assume_aligned(&s_wl[seg][z0], 16));
             T xn = (T)0, cprev = (T)0;
@@ -194,7 +212,7 @@ __global__ __launch_bounds__(64) void k_l1l1(L1Args a, int64_t groups) {
                     cprev = fma((T)-2, nb, v);
                 }
             }
-            T w = cprev;                         // z + c of the band before
+            T zprev = (T)0;
 #pragma unroll
             for (int i = 0; i < M; ++i) {
                 const T hi = hcol[i * 64];
@@ -203,9 +221,9 @@ __global__ __launch_bounds__(64) void k_l1l1(L1Args a, int64_t groups) {
                     a1 = hi;
                     c = (T)0;
                 } else {
-                    const T d = x[i] - b1[i];
-                    const T nb1 = clip(hi - d, t1);
-                    a1 = fma((T)2, nb1, d);
+                    const T t = (hi - x[i]) + b1[i];
+                    const T nb1 = clip(t, t1);
+                    a1 = fma((T)2, nb1, hi - t);
                     b1[i] = nb1;
                     const T xnext = i + 1 < M ? x[i + 1] : xn;
                     const T v = (xnext - x[i]) + b2[i];
@@ -216,12 +234,15 @@ __global__ __launch_bounds__(64) void k_l1l1(L1Args a, int64_t groups) {
                     // p / S rounded up to a multiple of four)
                     if (i >= M - 4 * S) c = i < vlen ? c : (T)0;
                 }
-                const T z = (fma(rho, a1, w) - c) * tf[i];
-                x[i] = z;
-                w = z + c;
+                if constexpr (UNIT) zprev = (zprev + fma(m1, a1, cprev - c)) * tinv[i];
+                else zprev = fma(m2, zprev, fma(m1, a1, m2 * (cprev - c))) * tinv[i];
+                x[i] = zprev;
+                cprev = c;
             }
+            const T* tb = tf;
+            if constexpr (kReread<T, M, S, UNIT>) tb = static_cast<const T*>(__builtin_assume_aligned(tf + opaque_zero(), 16));
 #pragma unroll
-            for (int i = M - 2; i >= 0; --i) x[i] = fma(tf[i], x[i + 1], x[i]);
+            for (int i = M - 2; i >= 0; --i) x[i] = fma(tb[i], x[i + 1], x[i]);
             if constexpr (S > 1) {
                 // tips of the block solutions, then the interface values this block needs
                 // (every block but the last is full: (S - 1) M < p)
@@ -285,12 +306,13 @@ bool l1l1_shape(int p, int dtype, int* S, int* M) {
     return true;
 }
 
-// k_l1l1<T, M, S> for the M of l1l1_shape, LO..HI in steps of four.
+// k_l1l1<T, M, S, mu2 is one> for the M of l1l1_shape, LO..HI in steps of four.
 template <typename T, int S, int LO, int HI>
 static hipError_t launch_l1l1_m(int M, const L1Args& a, int grid, int64_t groups, hipStream_t st) {
     if constexpr (LO <= HI) {
         if (M == LO) {
-            hipLaunchKernelGGL((k_l1l1<T, LO, S>), dim3(grid), dim3(64), 0, st, a, groups);
+            if (a.mu2 == 1.0) hipLaunchKernelGGL((k_l1l1<T, LO, S, true>), dim3(grid), dim3(64), 0, st, a, groups);
+            else hipLaunchKernelGGL((k_l1l1<T, LO, S, false>), dim3(grid), dim3(64), 0, st, a, groups);
             return hipGetLastError();
         }
         return launch_l1l1_m<T, S, LO + 4, HI>(M, a, grid, groups, st);
