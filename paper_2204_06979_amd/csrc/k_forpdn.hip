@@ -360,7 +360,11 @@ __global__ __launch_bounds__(1024) void k_forpdn_lambda(FLambda a) {
 // in LDS (formed in FP64 once per block), and writes the rows back the same way.
 // The floor is one read and one write of the coefficients.  Rows kept whole in
 // LDS left room for three waves on a compute unit, too few for the loads to
-// overlap the recurrences: 349 x 1905 x 144 took 371 us, 160 us now.
+// overlap the recurrences: 349 x 1905 x 144 took 371 us, 160 us now.  A row and an
+// address for each of its loads did not fit: 256 x 256 positions of 103 bands in
+// FP32 took 48 us with 146 registers spilled (23 now, 42 with rows in LDS), of
+// 191 97 (38, 121).  FP64 rows of more than 160 bands still spill (64 to 750
+// bytes a lane; 224 bands 100 us, 238 with rows in LDS).
 // The LDS rows of 16 bands are 20 (FP64 18) values apart: 16-byte accesses of 16
 // neighbouring lanes then fall on different banks, by row and by column.
 // NC chunks of 16 bands hold p; V bands per load (16 bytes if p allows, else one).
@@ -389,20 +393,23 @@ __global__ __launch_bounds__(64 * kFWaves, sizeof(T) == 4 && NC <= 12 ? 2 : 1) v
     const int64_t npos = a.npos, ntile = (npos + 63) / 64;
     const HYRES_GLOBAL T* coef = gmem(static_cast<const T*>(a.coef));
     const int lr = lane / LPR, lb = (lane % LPR) * V;       // row and band of a lane's global access
+    const int tail = min(16 * (NC - 1) + lb, p - V) - lb;   // last chunk: bands past p read others of the row
     T z[P16];
+    uint32_t at[K];                                         // this lane's place in its rows (those past the end: the last)
 
-    // raw values of the tile, in the layout of the global accesses
+    // raw values of the tile, in the layout of the global accesses: chunks at constant
+    // offsets from the places (an address each would not leave room for the rows)
     auto load = [&](int64_t tile) {
         const int64_t pos0 = tile * 64;
         const int last = npos - pos0 < 64 ? (int)(npos - pos0) - 1 : 63;
         const HYRES_GLOBAL T* src = coef + pos0 * p;
+#pragma unroll
+        for (int k = 0; k < K; ++k) at[k] = (uint32_t)(min(lr + k * RPS, last) * p + lb);
         static_for<NC>([&](auto cc) {
             constexpr int c = cc;
-            const int b = 16 * c + lb, bc = b < p ? b : p - V;
             static_for<K>([&](auto kc) {
                 constexpr int k = kc;
-                const int r = lr + k * RPS, rc = r < last ? r : last;
-                const GT v = *(const HYRES_GLOBAL GT*)(src + (uint32_t)(rc * p + bc));
+                const GT v = *(const HYRES_GLOBAL GT*)(src + at[k] + (c + 1 < NC ? 16 * c : tail));
 #pragma unroll
                 for (int i = 0; i < V; ++i) {
                     if constexpr (V == 1) z[16 * c + k] = v;
@@ -488,14 +495,13 @@ __global__ __launch_bounds__(64 * kFWaves, sizeof(T) == 4 && NC <= 12 ? 2 : 1) v
                 *(LT*)(s_row + lane * ST + i) = v;
             }
             wave_sync();
-            const int b = 16 * c + lb;
             static_for<K>([&](auto kc) {
                 constexpr int k = kc;
                 const int r = lr + k * RPS;
                 GT v;
 #pragma unroll
                 for (int i = 0; i < V; ++i) set_band<T, V>(v, i, turn_place(k)[i]);
-                if (r < cnt && b < p) *(HYRES_GLOBAL GT*)(dst + (uint32_t)(r * p + b)) = v;
+                if (r < cnt && (c + 1 < NC || 16 * c + lb < p)) *(HYRES_GLOBAL GT*)(dst + at[k] + 16 * c) = v;
             });
             wave_sync();
         });
