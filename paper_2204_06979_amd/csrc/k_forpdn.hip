@@ -58,7 +58,7 @@ __device__ __forceinline__ int64_t xcd_item(int64_t it, int64_t n) {
 // row within a strip: the rows that neighbouring windows share come again after
 // one strip's row (0.15 MB a row of four subbands at 144 bands), while they are
 // still in the XCD's L2, instead of after a whole row.
-constexpr int kStrip = 64;
+constexpr int kStrip = 32;      // (64 measures the same)
 struct Walk {
     int bh, bw, y, x, x0, sw;          // position (y, x0 + x) of the strip [x0, x0 + sw)
     __device__ __forceinline__ Walk(int bh_, int bw_, int64_t q) : bh(bh_), bw(bw_) {
