@@ -816,10 +816,13 @@ void group_by_small_class(Exec& x) {
 // Tile-grid groups: consecutive tiles in raster order, kMaxGroups of them, of
 // decreasing size (shares 10 : 8 : 5 : 2 of the tiles): the last group's small
 // solves end last, and the fewer tiles it holds, the sooner its remaining
-// stages (and then the blend) are done.  With the small solve of 224 bands at
-// 0.7 ms, 25 tiles of 512 x 512 x 224 take 5.41 ms mixed and 7.6 native (8 : 7 : 6 :
-// 4, right for a solve of 1.5 ms: 5.55 and 7.68; equal groups 5.58 and 7.9;
-// 9 : 9 : 5 : 2 5.34 and 7.84), 1100 x 1500 x 128 in tiles of 256 1.59 (1.67).
+// stages (and then the blend) are done.  The best shares move with the length of the
+// small solve and the tile count, a few percent either way; these, 8 : 7 : 6 : 4 and
+// 9 : 8 : 6 : 2 in ms:  2048 x 2048 x 224 in tiles of 512, mixed 5.41, 5.55, -, native
+// 7.6, 7.68, -;  2048 x 2048 x 144 mixed 3.48, 3.57, 3.60;  1500 x 1500 in tiles of
+// 512: 224 bands native 5.00, 5.33, 5.31, 160 mixed 2.72, 2.68, 2.62, 103 native
+// 2.21, 2.37, 2.33, 103 mixed 1.93, 1.90, 1.92, 48 native 1.15, 1.14, 1.16;  1100 x
+// 1500 x 128 in tiles of 256 native 1.72, 1.80, 1.72.
 void group_tiles(Exec& x) {
     x.ngroups = std::min(kMaxGroups, x.count);
     x.group_of.assign(x.count, 0);
