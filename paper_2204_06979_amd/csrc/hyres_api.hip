@@ -307,8 +307,8 @@ void plan_cube(CubePlan& c, Layout& lay, int parts) {
             c.o_shist = lay.add(std::max<size_t>((size_t)c.r * c.shcs * 4, 16));
             c.o_slist = lay.add(std::max<size_t>((size_t)c.r * c.slcs * es, 16));
         }
-        c.o_ssel = lay.add((size_t)c.r * (kSureRefine + 1) * sizeof(SureSel));
-        c.o_sseg = lay.add((size_t)c.r * kSureMaxChunks * sizeof(SureSeg));
+        c.o_ssel = lay.add((size_t)c.r * (sure_rounds(c.nc) + 1) * sizeof(SureSel));
+        c.o_sseg = lay.add((size_t)c.r * (c.nc > kSureLarge ? kSureMaxChunks : kSureChunks) * sizeof(SureSeg));
         c.o_lambda = lay.add((size_t)c.r * 8);
         c.o_sure = lay.add((size_t)c.r * 8);
     }

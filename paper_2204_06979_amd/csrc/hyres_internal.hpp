@@ -93,8 +93,8 @@ struct CubeDesc {
     // segments of surviving values (component stride slcs, segcap each), results
     uint32_t* shist; int64_t shcs;
     void* slist; int64_t slcs, segcap;
-    SureSel* ssel;                          // r x (kSureRefine + 1)
-    SureSeg* sseg;                          // r x kSureMaxChunks
+    SureSel* ssel;                          // r x (srounds + 1)
+    SureSeg* sseg;                          // r x snch
     int64_t schunk; int snch, srounds;      // coefficients per chunk, chunks (1: no list), refining rounds
     double* lambda; double* sure;           // r
     const double* lambda_in;                // optional caller thresholds

@@ -51,7 +51,8 @@ __device__ __forceinline__ double row_bcast(double v) {
 // exactly zero counts as positive); both minors are rescaled by a power of two
 // every 8 steps so the recursion stays in range.  Lane c of a row of 16 holds
 // d_i and e_{i-1}^2 of i = 16 b + c (entries past the matrix: d = 3, e = 0, no sign
-// change for x < 3; whole groups of eight of them are left out); a step is two broadcasts, three FP64 operations and one that
+// change for x < 3; whole groups of eight of them are left out where the class
+// may have them, which those of the class's smallest band count do not pay for); a step is two broadcasts, three FP64 operations and one that
 // shifts the sign into a word: 24 issue cycles, no LDS (broadcast 16-byte reads of
 // all waves were its bound before, 49 cycles a step).  Call with all sixteen lanes
 // of a row active: a lane that is off broadcasts zeros.
@@ -62,7 +63,8 @@ __device__ __forceinline__ int sturm_count(const double (&dv)[T], const double (
     int cnt = 0;
     static_for<2 * T>([&](auto h) {
         constexpr int b = decltype(h)::value / 2, c0 = 8 * (decltype(h)::value % 2);
-        if (8 * decltype(h)::value >= p) return;
+        constexpr int least = 16 * (T <= 2 || (T > 8 && T < 13) ? T - 1 : T - 2);   // bands of the class below
+        if (8 * decltype(h)::value > least && 8 * decltype(h)::value >= p) return;
         static_for<8>([&](auto u) {
             constexpr int c = c0 + decltype(u)::value;
             const double pi = fma(row_bcast<c>(dv[b]) - x, pm1, -row_bcast<c>(ev[b]) * pm2);

@@ -488,7 +488,7 @@ __global__ __launch_bounds__(256) void k_sure_rows(const CubeDesc* __restrict__ 
         out[b0 + tid] = t;
     }
     for (int k = tid; k < 3 * kSureRefine * 64; k += 256) out[(1 + k / 64) * kSureBins + b0 + k % 64] = 0u;
-    if (b0 == 0 && tid <= kSureRefine) d.ssel[comp * (kSureRefine + 1) + tid].count = 0u;
+    if (b0 == 0 && tid <= d.srounds) d.ssel[comp * (d.srounds + 1) + tid].count = 0u;
 }
 
 template <typename T>
@@ -555,7 +555,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_gather(const CubeDesc* __
     uint64_t klo = 1, khi = 1;
     if (first >= 0) first_range<T>(first, last, &klo, &khi);
     if (chunk == 0 && tid == 0) {
-        SureSel* s = d.ssel + comp * (kSureRefine + 1);
+        SureSel* s = d.ssel + comp * (d.srounds + 1);
         s->klo = klo;
         s->khi = khi;
         s->c0 = c0;
@@ -581,7 +581,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_gather(const CubeDesc* __
     if (tid == 0) {
         double s = 0.0;
         for (int w = 0; w < kSureWaves; ++w) s += sh.ws[w];
-        SureSeg* o = d.sseg + (int64_t)comp * kSureMaxChunks + chunk;
+        SureSeg* o = d.sseg + (int64_t)comp * d.snch + chunk;
         o->s0 = s;
         o->count = sh.count;
     }
@@ -687,7 +687,7 @@ __device__ __forceinline__ HYRES_GLOBAL T* sure_list(const CubeDesc& d, int comp
 // Values that a block of round `round` takes.
 template <typename T>
 __device__ __forceinline__ SurePart<T> sure_share(const CubeDesc& d, int comp, int chunk, int round, uint32_t count) {
-    if (round == 0) return sure_segment<T>(d, comp, chunk, d.sseg[(int64_t)comp * kSureMaxChunks + chunk].count);
+    if (round == 0) return sure_segment<T>(d, comp, chunk, d.sseg[(int64_t)comp * d.snch + chunk].count);
     if ((int64_t)count > d.segcap * d.snch) return sure_chunk_part<T>(d, comp, chunk);
     const int64_t per = ((int64_t)count + d.snch - 1) / d.snch, a = min(chunk * per, (int64_t)count);
     return {sure_list<T>(d, comp, round) + a, min(per, (int64_t)count - a)};
@@ -712,7 +712,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_refine(const CubeDesc* __
     const int nch = d.snch, local = blockIdx.x - items[cu], comp = local / nch, chunk = local - comp * nch;
     const int tid = threadIdx.x;
     if (round >= d.srounds) return;
-    const SureSel s = d.ssel[comp * (kSureRefine + 1) + round];
+    const SureSel s = d.ssel[comp * (d.srounds + 1) + round];
     if (s.khi <= s.klo) return;
     for (int b = tid; b < kSureBins; b += kSureThreads) {
         cnt[b] = 0;
@@ -759,9 +759,9 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_narrow(const CubeDesc* __
     const int nch = d.snch, local = blockIdx.x - items[cu], comp = local / nch, chunk = local - comp * nch;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (round >= d.srounds) return;
-    const SureSel* s = d.ssel + comp * (kSureRefine + 1) + round;
+    const SureSel* s = d.ssel + comp * (d.srounds + 1) + round;
     const uint64_t klo = s->klo, khi = s->khi, c0 = s->c0;
-    SureSel* o = d.ssel + comp * (kSureRefine + 1) + round + 1;     // written by the first chunk's block, read by the next launch
+    SureSel* o = d.ssel + comp * (d.srounds + 1) + round + 1;     // written by the first chunk's block, read by the next launch
     if (khi <= klo) {
         if (chunk == 0 && tid == 0) {
             o->klo = o->khi = 1;
@@ -772,7 +772,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_narrow(const CubeDesc* __
         return;
     }
     const double N = (double)sure_count(d);
-    const SureSeg* sg = d.sseg + (int64_t)comp * kSureMaxChunks;
+    const SureSeg* sg = d.sseg + (int64_t)comp * d.snch;
     double s0 = 0.0;
     if (round == 0) {
         // squares below the range: lane sums of every 64th chunk, the same in every wave
@@ -941,7 +941,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
         if (first >= 0) first_range<T>(first, last, &klo, &khi);
         need_s0 = true;
     } else {
-        const SureSel s = d.ssel[comp * (kSureRefine + 1) + d.srounds];
+        const SureSel s = d.ssel[comp * (d.srounds + 1) + d.srounds];
         klo = s.klo;
         khi = s.khi;
         c0 = s.c0;
@@ -953,7 +953,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
             if ((int64_t)s.count <= d.segcap * nch) whole = {sure_list<T>(d, comp, d.srounds), (int64_t)s.count};
         } else {
             whole.p = nullptr;
-            const SureSeg* sg = d.sseg + (int64_t)comp * kSureMaxChunks;
+            const SureSeg* sg = d.sseg + (int64_t)comp * d.snch;
             if (khi > klo) {
                 for (int k = tid; k < nch; k += kSureThreads) {
                     s_count[k] = sg[k].count;
