@@ -28,7 +28,7 @@
 // 5 x 9 entries per thread at p = 144, row sums over 16 lanes by DPP, operands of
 // both sides from LDS) issued about 480 vector instructions per Householder
 // step and wave.  Microseconds before and now at rank 4-10: 32 bands 81, 50; 103
-// 375, 203; 128 435, 231; 144 472, 290; 191 867, 428; 224 1490, 706.  Of the 290:
+// 375, 200; 128 435, 231; 144 472, 290; 191 867, 428; 224 1490, 706.  Of the 290:
 // noise 61, tridiagonalisation 137, Sturm counts 29, twisted factorisation 20,
 // back-transformation 36.
 #include "hyres_internal.hpp"

@@ -36,7 +36,7 @@
 // compared with the best one through the bins between the two.
 //
 // Bound by latency and LDS atomics: the three passes over the 21 MB of 349 x 1905
-// and 8 components take 10, 22 and 38 us, against 145 us for six passes with a
+// and 8 components take 10, 22 and 42 us, against 145 us for six passes with a
 // select in the last block of each; ten components of 145 x 217, one launch,
 // 37 us against 594; four FP64 ones of 64 x 64 25 us against 158.
 #include "hyres_internal.hpp"
