@@ -34,16 +34,17 @@ constexpr double kH3 = -0.12940952255126037;
 // SURE threshold search: the key range [klo, khi) that survives a histogram, the
 // values below it (exact zeros included), the smallest upper bound of the risk with
 // its threshold, and the exact zeros; after a refining round also the squares below
-// the range and the values in it.
+// the range and the values and pairs in it.
 struct SureSel {
     uint64_t klo, khi, c0;
     double s0, U, Ut;
-    uint32_t zeros, count;
+    uint32_t zeros, count, pairs, pad;
 };
-// ... and per chunk: squares of its values below the first range, its values inside.
+// ... and per chunk: squares of its values below the first range, its values inside
+// (one by one, and pairs of a tied value and its count).
 struct SureSeg {
     double s0;
-    uint32_t count, pad;
+    uint32_t count, pairs;
 };
 enum { SURE_HIST, SURE_ROWS, SURE_GATHER, SURE_REFINE, SURE_NARROW, SURE_FINISH };   // launches of the search
 

@@ -39,6 +39,8 @@
 // and 8 components take 10, 22 and 42 us, against 145 us for six passes with a
 // select in the last block of each; ten components of 145 x 217, one launch,
 // 37 us against 594; four FP64 ones of 64 x 64 25 us against 158.
+#include <type_traits>
+
 #include "hyres_internal.hpp"
 
 namespace hyres {
@@ -192,7 +194,8 @@ struct SureShared {
     uint32_t wc[kSureWaves], wn[kSureWaves], wm[kSureWaves];
     double ws[kSureWaves], wt[kSureWaves], bs[kSureWaves], bt[kSureWaves];
     int wf[kSureWaves], wl[kSureWaves], wx[kSureWaves];
-    uint32_t zeros, count;
+    uint32_t zeros, count, pairs;
+    int tied;
     double ref[4];                 // first select: the reference bin
     uint64_t c0;
     int first, last;
@@ -255,12 +258,28 @@ __device__ __forceinline__ uint32_t first_histogram(const HYRES_GLOBAL T* cf, in
     return e1 - e0 <= 4 * kSureThreads ? first_histogram_u<T, 4>(cf, e0, e1, lc) : first_histogram_u<T, kSureLoads>(cf, e0, e1, lc);
 }
 
+// Whether a thread's bins among first..last show tied values: a bin of more than 64
+// with an empty one beside it, which a continuous distribution does not leave, or
+// alone in the range.
+__device__ __forceinline__ bool bins_tied(const uint32_t (&c)[kBinsPer], int first, int last) {
+    bool heavy = false, gap = first == last;
+#pragma unroll
+    for (int j = 0; j < kBinsPer; ++j) {
+        const int b = kBinsPer * (int)threadIdx.x + j;
+        const bool in = b >= first && b <= last;
+        heavy |= in && c[j] > 64;
+        gap |= in && c[j] == 0;
+    }
+    return heavy && gap;
+}
+
 // Select on the first histogram: c[j] holds bin 4 tid + j (the zero slot's
 // count in `zeros`).  Returns the first and last surviving bin (-1: none) and the
 // number of values below the first.  Sums of squares are known to the edges of
 // the bins only: relative to a reference bin J with upper bound U, L - U needs
 // the sum over the bins between, bounded by their edges.
-template <typename T>
+// TIES: sh.tied (cleared before) tells whether a bin shows tied values.
+template <typename T, bool TIES>
 __device__ __forceinline__ void first_select(const uint32_t (&c)[kBinsPer], uint32_t zeros, double N, SureShared& sh,
                                              int* first, int* last, uint64_t* c0) {
     typedef KeyTraits<T> KT;
@@ -373,6 +392,7 @@ __device__ __forceinline__ void first_select(const uint32_t (&c)[kBinsPer], uint
     __syncthreads();
     const int ff = waves_minmax<false>(sh.wf), ll = waves_minmax<true>(sh.wl);
     if (l >= 0 && f == ff) sh.c0 = (uint64_t)cf;
+    if (TIES && bins_tied(c, ff, ll)) sh.tied = 1;
     __syncthreads();
     *first = ll >= 0 ? ff : -1;
     *last = ll;
@@ -414,30 +434,105 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_hist(const CubeDesc* __re
 
 // Appends the values of [klo, khi) among a wave's v (zeros are in no range) to a
 // list of `cap` values; *count counts those beyond it too.
-template <typename T, typename C>
-__device__ __forceinline__ void keep_range(const T (&v)[kSureLoads], uint64_t klo, uint64_t khi, HYRES_GLOBAL T* list,
-                                           uint32_t cap, C* count) {
-    typedef KeyTraits<T> KT;
+template <typename T, int U, typename C>
+__device__ __forceinline__ void keep_values(const T (&v)[U], const bool (&in)[U], HYRES_GLOBAL T* list, uint32_t cap,
+                                            C* count) {
     const int lane = threadIdx.x & 63;
-    bool in[kSureLoads];
     uint32_t n = 0;
 #pragma unroll
-    for (int u = 0; u < kSureLoads; ++u) {
-        const uint64_t k = KT::key(v[u]);
-        in[u] = k >= klo && k < khi;
-        n += (uint32_t)__popcll(__ballot(in[u]));
-    }
-    uint32_t at = 0;
+    for (int u = 0; u < U; ++u) n += (uint32_t)__popcll(__ballot(in[u]));
     if (!n) return;
+    uint32_t at = 0;
     if (lane == 0) at = atomicAdd(count, n);
     at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
 #pragma unroll
-    for (int u = 0; u < kSureLoads; ++u) {
+    for (int u = 0; u < U; ++u) {
         const unsigned long long m = __ballot(in[u]);
         const uint32_t pos = at + (uint32_t)__popcll(m & ((1ull << lane) - 1));
         if (in[u] && pos < cap) list[pos] = v[u];
         at += (uint32_t)__popcll(m);
     }
+}
+template <typename T, int U, typename C>
+__device__ __forceinline__ void keep_range(const T (&v)[U], uint64_t klo, uint64_t khi, HYRES_GLOBAL T* list, uint32_t cap,
+                                           C* count) {
+    bool in[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const uint64_t k = KeyTraits<T>::key(v[u]);
+        in[u] = k >= klo && k < khi;
+    }
+    keep_values<T, U>(v, in, list, cap, count);
+}
+
+// ---- components of tied values (integers, a quantised image) ----
+// A bin then holds one value many times over, and a list of them all is most of the
+// component: one block took 2 ms for a million integers, 32 for 2^24 (0.3 and 0.46 in
+// passes over all of them by all blocks).  A block keeps one value per bin instead,
+// the first it meets, and counts those equal to it; at its end they go to the list as
+// pairs of value and count, from the end of the list's space downwards: a million
+// integers 0.1 ms, 2^24 0.2.
+template <typename T>
+struct SureTies {
+    typename KeyTraits<T>::K key[kSureBins];
+    uint32_t n[kSureBins];
+};
+template <typename T>
+__device__ __forceinline__ void clear_ties(SureTies<T>& t) {      // a barrier follows
+    for (int b = threadIdx.x; b < kSureBins; b += kSureThreads) {
+        t.key[b] = 0;
+        t.n[b] = 0;
+    }
+}
+// The values p[0..m) of [klo, khi) kept so; returns the squares of those below.
+template <typename T, typename Bin, typename C>
+__device__ __forceinline__ double fold_ties(const HYRES_GLOBAL T* p, int64_t m, uint64_t klo, uint64_t khi, SureTies<T>& t,
+                                            Bin bin, HYRES_GLOBAL T* list, uint32_t cap, C* count) {
+    typedef typename KeyTraits<T>::K K;
+    const int lane = threadIdx.x & 63;
+    double below = 0.0;
+    for (int64_t e = threadIdx.x - lane; e < m; e += 4 * kSureThreads) {     // whole waves
+        T v[4];
+        bool in[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t i = e + lane + (int64_t)u * kSureThreads;
+            v[u] = p[i < m ? i : m - 1];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (e + lane + (int64_t)u * kSureThreads >= m) v[u] = (T)0;
+            const K k = KeyTraits<T>::key(v[u]);
+            in[u] = (uint64_t)k >= klo && (uint64_t)k < khi;
+            if ((uint64_t)k < klo) below = fma((double)v[u], (double)v[u], below);
+            if (in[u]) {
+                const int b = bin(k);
+                K r = t.key[b];
+                if (r == 0) {
+                    const K old = atomicCAS(&t.key[b], (K)0, k);
+                    r = old ? old : k;
+                }
+                if (r == k) {
+                    atomicAdd(&t.n[b], 1u);
+                    in[u] = false;
+                }
+            }
+        }
+        keep_values<T, 4>(v, in, list, cap, count);
+    }
+    return below;
+}
+// (after a barrier)  `end` is the end of a list's space of `cap` values.
+template <typename T, typename C>
+__device__ __forceinline__ void keep_ties(const SureTies<T>& t, HYRES_GLOBAL T* end, int64_t cap, C* pairs) {
+    for (int b = threadIdx.x; b < kSureBins; b += kSureThreads)
+        if (t.n[b]) {
+            const int64_t at = 2 * (int64_t)(atomicAdd(pairs, 1u) + 1u);
+            if (at <= cap) {
+                end[-at] = (T)KeyTraits<T>::val(t.key[b]);
+                end[1 - at] = (T)t.n[b];          // below 2^24: exact
+            }
+        }
 }
 
 // Large components (d.srounds > 0): the chunks' count rows added into one, which the
@@ -488,7 +583,10 @@ __global__ __launch_bounds__(256) void k_sure_rows(const CubeDesc* __restrict__ 
         out[b0 + tid] = t;
     }
     for (int k = tid; k < 3 * kSureRefine * 64; k += 256) out[(1 + k / 64) * kSureBins + b0 + k % 64] = 0u;
-    if (b0 == 0 && tid <= d.srounds) d.ssel[comp * (d.srounds + 1) + tid].count = 0u;
+    if (b0 == 0 && tid <= d.srounds) {
+        d.ssel[comp * (d.srounds + 1) + tid].count = 0u;
+        d.ssel[comp * (d.srounds + 1) + tid].pairs = 0u;
+    }
 }
 
 template <typename T>
@@ -496,6 +594,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_gather(const CubeDesc* __
                                                               const int* __restrict__ items, int ncubes) {
     typedef KeyTraits<T> KT;
     __shared__ SureShared sh;
+    __shared__ SureTies<T> ties;
     const int cu = find_cube(items, ncubes, blockIdx.x);
     const CubeDesc& d = descs[cu];
     const int nch = d.snch, local = blockIdx.x - items[cu], comp = local / nch, chunk = local - comp * nch;
@@ -545,13 +644,15 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_gather(const CubeDesc* __
         sh.zeros = c[kBinsPer - 1];
         c[kBinsPer - 1] = 0;
         sh.count = 0;
+        sh.pairs = 0;
+        sh.tied = 0;
     }
     __syncthreads();
     const uint32_t zeros = sh.zeros;
     int first, last;
     uint64_t c0;
     fetch(e0 + tid - lane);                  // under the selection
-    first_select<T>(c, zeros, (double)N, sh, &first, &last, &c0);
+    first_select<T, true>(c, zeros, (double)N, sh, &first, &last, &c0);
     uint64_t klo = 1, khi = 1;
     if (first >= 0) first_range<T>(first, last, &klo, &khi);
     if (chunk == 0 && tid == 0) {
@@ -564,26 +665,39 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_gather(const CubeDesc* __
         s->zeros = zeros;
     }
     if (first < 0) return;
+    const bool tied = __builtin_amdgcn_readfirstlane(sh.tied) != 0;
     HYRES_GLOBAL T* seg = gmem(static_cast<T*>(d.slist)) + comp * d.slcs + (int64_t)chunk * d.segcap;
     double s0 = 0.0;
-    for (int64_t e = e0 + tid - lane; e < e1; e += U * kSureThreads) {   // whole waves
+    if (__builtin_expect(tied, 0)) {
+        clear_ties(ties);
+        __syncthreads();
+        s0 = fold_ties<T>(cf + e0, e1 - e0, klo, khi, ties, [](typename KT::K k) { return first_bin<T>(k); }, seg,
+                          (uint32_t)d.segcap, &sh.count);
+    } else {
+        for (int64_t e = e0 + tid - lane; e < e1; e += U * kSureThreads) {   // whole waves
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            v[u] = e + lane + (int64_t)u * kSureThreads < e1 ? v[u] : (T)0;
-            if (KT::key(v[u]) < klo) s0 = fma((double)v[u], (double)v[u], s0);
+            for (int u = 0; u < U; ++u) {
+                v[u] = e + lane + (int64_t)u * kSureThreads < e1 ? v[u] : (T)0;
+                if (KT::key(v[u]) < klo) s0 = fma((double)v[u], (double)v[u], s0);
+            }
+            keep_range<T, U>(v, klo, khi, seg, (uint32_t)d.segcap, &sh.count);
+            if (e + U * kSureThreads < e1) fetch(e + U * kSureThreads);
         }
-        keep_range<T>(v, klo, khi, seg, (uint32_t)d.segcap, &sh.count);
-        if (e + U * kSureThreads < e1) fetch(e + U * kSureThreads);
     }
     s0 = wave_sum(s0);
     if (lane == 0) sh.ws[wave] = s0;
     __syncthreads();
+    if (tied) {
+        keep_ties<T>(ties, seg + d.segcap, d.segcap, &sh.pairs);
+        __syncthreads();
+    }
     if (tid == 0) {
         double s = 0.0;
         for (int w = 0; w < kSureWaves; ++w) s += sh.ws[w];
         SureSeg* o = d.sseg + (int64_t)comp * d.snch + chunk;
         o->s0 = s;
         o->count = sh.count;
+        o->pairs = sh.pairs;
     }
 }
 
@@ -661,22 +775,30 @@ __device__ __forceinline__ void block_argmin(double& s, double& t, SureShared& s
 // round later, and the one block reads it several times: of 67 million values the
 // search took 2.8 ms, 2.35 of them the finish; 0.31 with two rounds)
 
-// Values of a list, of a segment or of a chunk.
+// Values of a list, of a segment or of a chunk, and pairs of value and count, which
+// lie downwards from `end`.
 template <typename T>
 struct SurePart {
     const HYRES_GLOBAL T* p;
     int64_t m;
+    const HYRES_GLOBAL T* end;
+    int pairs;
 };
 template <typename T>
 __device__ __forceinline__ SurePart<T> sure_chunk_part(const CubeDesc& d, int comp, int chunk) {
     const int64_t e0 = (int64_t)chunk * d.schunk;
-    return {gmem(static_cast<const T*>(d.coef)) + (int64_t)comp * d.ncs + e0, min(d.schunk, sure_count(d) - e0)};
+    return {gmem(static_cast<const T*>(d.coef)) + (int64_t)comp * d.ncs + e0, min(d.schunk, sure_count(d) - e0), nullptr, 0};
+}
+// Values and pairs that fit a list's space of `cap`
+__device__ __forceinline__ bool sure_fits(uint32_t count, uint32_t pairs, int64_t cap) {
+    return (int64_t)count + 2 * (int64_t)pairs <= cap;
 }
 // The gather's: a chunk's segment, or the chunk itself where the segment overflowed.
 template <typename T>
-__device__ __forceinline__ SurePart<T> sure_segment(const CubeDesc& d, int comp, int chunk, uint32_t count) {
-    if (count > (uint32_t)d.segcap) return sure_chunk_part<T>(d, comp, chunk);
-    return {gmem(static_cast<const T*>(d.slist)) + comp * d.slcs + (int64_t)chunk * d.segcap, (int64_t)count};
+__device__ __forceinline__ SurePart<T> sure_segment(const CubeDesc& d, int comp, int chunk, uint32_t count, uint32_t pairs) {
+    if (!sure_fits(count, pairs, d.segcap)) return sure_chunk_part<T>(d, comp, chunk);
+    const HYRES_GLOBAL T* seg = gmem(static_cast<const T*>(d.slist)) + comp * d.slcs + (int64_t)chunk * d.segcap;
+    return {seg, (int64_t)count, seg + d.segcap, (int)pairs};
 }
 // A round's: one list per component, in the halves of its space in turn (the
 // segments are in the first).
@@ -684,13 +806,20 @@ template <typename T>
 __device__ __forceinline__ HYRES_GLOBAL T* sure_list(const CubeDesc& d, int comp, int round) {
     return gmem(static_cast<T*>(d.slist)) + comp * d.slcs + (round & 1 ? d.segcap * d.snch : 0);
 }
-// Values that a block of round `round` takes.
+// Values and pairs that a block of round `round` takes.
 template <typename T>
-__device__ __forceinline__ SurePart<T> sure_share(const CubeDesc& d, int comp, int chunk, int round, uint32_t count) {
-    if (round == 0) return sure_segment<T>(d, comp, chunk, d.sseg[(int64_t)comp * d.snch + chunk].count);
-    if ((int64_t)count > d.segcap * d.snch) return sure_chunk_part<T>(d, comp, chunk);
+__device__ __forceinline__ SurePart<T> sure_share(const CubeDesc& d, int comp, int chunk, int round, uint32_t count,
+                                                  uint32_t pairs) {
+    if (round == 0) {
+        const SureSeg* g = d.sseg + (int64_t)comp * d.snch + chunk;
+        return sure_segment<T>(d, comp, chunk, g->count, g->pairs);
+    }
+    const int64_t cap = d.segcap * d.snch;
+    if (!sure_fits(count, pairs, cap)) return sure_chunk_part<T>(d, comp, chunk);
     const int64_t per = ((int64_t)count + d.snch - 1) / d.snch, a = min(chunk * per, (int64_t)count);
-    return {sure_list<T>(d, comp, round) + a, min(per, (int64_t)count - a)};
+    const int64_t pp = ((int64_t)pairs + d.snch - 1) / d.snch, b = min(chunk * pp, (int64_t)pairs);
+    const HYRES_GLOBAL T* list = sure_list<T>(d, comp, round);
+    return {list + a, min(per, (int64_t)count - a), list + cap - 2 * b, (int)min(pp, (int64_t)pairs - b)};
 }
 // Row of counts and row of sums of squares of round `round`, behind the count rows.
 __device__ __forceinline__ HYRES_GLOBAL uint32_t* refine_counts(const CubeDesc& d, int comp, int round) {
@@ -719,7 +848,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_refine(const CubeDesc* __
         sum[b] = 0.0;
     }
     __syncthreads();
-    const SurePart<T> a = sure_share<T>(d, comp, chunk, round, s.count);
+    const SurePart<T> a = sure_share<T>(d, comp, chunk, round, s.count, s.pairs);
     const int shf = shift_for(s.khi - s.klo);
     constexpr int U = kSureLoads;
     for (int64_t e = tid; e < a.m; e += U * kSureThreads) {
@@ -739,6 +868,15 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_refine(const CubeDesc* __
             }
         }
     }
+    for (int e = tid; e < a.pairs; e += kSureThreads) {
+        const double v = a.end[-2 * e - 2], n = a.end[-2 * e - 1];
+        const uint64_t k = KT::key((T)v);
+        if (k >= s.klo && k < s.khi) {
+            const int b = (int)((k - s.klo) >> shf);
+            atomicAdd(&cnt[b], (uint32_t)n);
+            atomicAdd(&sum[b], n * (v * v));
+        }
+    }
     __syncthreads();
     HYRES_GLOBAL uint32_t* gc = refine_counts(d, comp, round);
     HYRES_GLOBAL double* gs = refine_sums(d, comp, round);
@@ -753,7 +891,9 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_refine(const CubeDesc* __
 template <typename T>
 __global__ __launch_bounds__(kSureThreads) void k_sure_narrow(const CubeDesc* __restrict__ descs,
                                                               const int* __restrict__ items, int ncubes, int round) {
+    typedef KeyTraits<T> KT;
     __shared__ SureShared sh;
+    __shared__ SureTies<T> ties;
     const int cu = find_cube(items, ncubes, blockIdx.x);
     const CubeDesc& d = descs[cu];
     const int nch = d.snch, local = blockIdx.x - items[cu], comp = local / nch, chunk = local - comp * nch;
@@ -813,9 +953,12 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_narrow(const CubeDesc* __
         sh.wf[wave] = wf;
         sh.wl[wave] = wl;
     }
+    if (tid == 0) sh.tied = 0;
     __syncthreads();
     f = waves_minmax<false>(sh.wf);
     l = waves_minmax<true>(sh.wl);
+    if (bins_tied(c, f, l)) sh.tied = 1;
+    __syncthreads();
     uint64_t nlo = 1, nhi = 1;
     if (l >= 0) {
         const uint64_t end = klo + ((uint64_t)(l + 1) << shf);
@@ -842,20 +985,43 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_narrow(const CubeDesc* __
         }
     }
     if (l < 0) return;
-    const SurePart<T> a = sure_share<T>(d, comp, chunk, round, s->count);
+    const SurePart<T> a = sure_share<T>(d, comp, chunk, round, s->count, s->pairs);
     HYRES_GLOBAL T* list = sure_list<T>(d, comp, round + 1);
-    const uint32_t cap = (uint32_t)(d.segcap * nch);
-    constexpr int V = kSureLoads;
-    for (int64_t e = tid - lane; e < a.m; e += V * kSureThreads) {     // whole waves
-        T v[V];
+    const int64_t cap = d.segcap * nch;
+    const bool tied = __builtin_amdgcn_readfirstlane(sh.tied) != 0;
+    if (__builtin_expect(tied, 0)) {
+        clear_ties(ties);
+        __syncthreads();
+        (void)fold_ties<T>(a.p, a.m, nlo, nhi, ties, [&](typename KT::K k) { return (int)(((uint64_t)k - klo) >> shf); },
+                           list, (uint32_t)cap, &o->count);
+    } else {
+        constexpr int V = kSureLoads;
+        for (int64_t e = tid - lane; e < a.m; e += V * kSureThreads) {     // whole waves
+            T v[V];
 #pragma unroll
-        for (int u = 0; u < V; ++u) {
-            const int64_t i = e + lane + (int64_t)u * kSureThreads;
-            v[u] = a.p[i < a.m ? i : a.m - 1];
+            for (int u = 0; u < V; ++u) {
+                const int64_t i = e + lane + (int64_t)u * kSureThreads;
+                v[u] = a.p[i < a.m ? i : a.m - 1];
+            }
+#pragma unroll
+            for (int u = 0; u < V; ++u) v[u] = e + lane + (int64_t)u * kSureThreads < a.m ? v[u] : (T)0;
+            keep_range<T, V>(v, nlo, nhi, list, (uint32_t)cap, &o->count);
         }
-#pragma unroll
-        for (int u = 0; u < V; ++u) v[u] = e + lane + (int64_t)u * kSureThreads < a.m ? v[u] : (T)0;
-        keep_range<T>(v, nlo, nhi, list, cap, &o->count);
+    }
+    for (int e = tid; e < a.pairs; e += kSureThreads) {
+        const T v = a.end[-2 * e - 2], n = a.end[-2 * e - 1];
+        const uint64_t k = KT::key(v);
+        if (k >= nlo && k < nhi) {
+            const int64_t at = 2 * (int64_t)(atomicAdd(&o->pairs, 1u) + 1u);
+            if (at <= cap) {
+                list[cap - at] = v;
+                list[cap - at + 1] = n;
+            }
+        }
+    }
+    if (tied) {
+        __syncthreads();
+        keep_ties<T>(ties, list + cap, cap, &o->pairs);
     }
 }
 
@@ -880,7 +1046,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
     __shared__ SureRange stack[kSureStack];
     __shared__ SureShared sh;
     __shared__ int s_sp, s_inexact, s_wlo[kSureWindows], s_whi[kSureWindows];
-    __shared__ uint32_t s_count[kSureChunks];
+    __shared__ uint32_t s_count[kSureChunks], s_pairs[kSureChunks];
     const int cu = find_cube(items, ncubes, blockIdx.x);
     const CubeDesc& d = descs[cu];
     const int comp = blockIdx.x - items[cu];
@@ -889,13 +1055,13 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
     const double N = (double)Ni;
     const int nch = d.snch;
     const HYRES_GLOBAL T* coef = gmem(static_cast<const T*>(d.coef)) + (int64_t)comp * d.ncs;
-    // f(value) for each of the values: the coefficients, or the list of the last
-    // round, taken by the whole block; or the chunks' segments, in parts that the
-    // waves take in turn.
-    SurePart<T> whole = {coef, Ni};
+    // f(value, how often) for each of the values: the coefficients, or the list of the
+    // last round, taken by the whole block; or the chunks' segments, in parts that
+    // the waves take in turn.
+    SurePart<T> whole = {coef, Ni, nullptr, 0};
     const int parts = (kSureWaves + nch - 1) / nch;
-    auto run = [&](const HYRES_GLOBAL T* p, int64_t a, int64_t b, int stride, auto f) {
-        constexpr int U = kSureLoads;
+    auto run = [&](auto loads, const HYRES_GLOBAL T* p, int64_t a, int64_t b, int stride, auto f) {
+        constexpr int U = decltype(loads)::value;
         for (int64_t i = a; i < b; i += (int64_t)stride * U) {
             T v[U];
 #pragma unroll
@@ -904,19 +1070,26 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
                 v[k] = e < b ? p[e] : (T)0;           // few of the U are in range: clamped loads are slower here (40.3 us, 38)
             }
 #pragma unroll
-            for (int k = 0; k < U; ++k) f(v[k]);          // zeros are in no range
+            for (int k = 0; k < U; ++k) f(v[k], 1u);      // zeros are in no range
         }
     };
-    auto for_each = [&](auto f) {
+    auto run_pairs = [&](const SurePart<T>& q, int a, int stride, auto f) {
+        for (int i = a; i < q.pairs; i += stride) f(q.end[-2 * i - 2], (uint32_t)q.end[-2 * i - 1]);
+    };
+    auto for_each = [&](auto pairs, auto f) {
+        const std::integral_constant<int, decltype(pairs)::value ? 4 : kSureLoads> loads{};   // (few values beside pairs)
         if (whole.p) {
-            run(whole.p, tid, whole.m, kSureThreads, f);
+            run(loads, whole.p, tid, whole.m, kSureThreads, f);
+            if constexpr (decltype(pairs)::value) run_pairs(whole, tid, kSureThreads, f);
             return;
         }
         for (int u = wave; u < nch * parts; u += kSureWaves) {
             const int s = u / parts, part = u - s * parts;
-            const SurePart<T> q = sure_segment<T>(d, comp, s, s_count[s]);
+            const SurePart<T> q = sure_segment<T>(d, comp, s, s_count[s], s_pairs[s]);
             const int64_t step = (q.m + parts - 1) / parts, a = part * step, b = min(a + step, q.m);
-            run(q.p, a + lane, b, 64, f);
+            run(loads, q.p, a + lane, b, 64, f);
+            if constexpr (decltype(pairs)::value)
+                if (part == 0) run_pairs(q, lane, 64, f);
         }
     };
 
@@ -937,7 +1110,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
         zeros = cnt[kZeroSlot];
         if (tid == kSureThreads - 1) c[PER - 1] = 0;
         int first, last;
-        first_select<T>(c, zeros, N, sh, &first, &last, &c0);
+        first_select<T, false>(c, zeros, N, sh, &first, &last, &c0);
         if (first >= 0) first_range<T>(first, last, &klo, &khi);
         need_s0 = true;
     } else {
@@ -950,22 +1123,26 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
         Ut = s.Ut;
         if (d.srounds) {
             s0 = s.s0;
-            if ((int64_t)s.count <= d.segcap * nch) whole = {sure_list<T>(d, comp, d.srounds), (int64_t)s.count};
+            const HYRES_GLOBAL T* list = sure_list<T>(d, comp, d.srounds);
+            const uint32_t count = readlane_u32(s.count, 0), pairs = readlane_u32(s.pairs, 0);
+            if (sure_fits(count, pairs, d.segcap * nch))
+                whole = {list, (int64_t)count, list + d.segcap * nch, (int)pairs};
         } else {
             whole.p = nullptr;
             const SureSeg* sg = d.sseg + (int64_t)comp * d.snch;
             if (khi > klo) {
-                for (int k = tid; k < nch; k += kSureThreads) {
-                    s_count[k] = sg[k].count;
-                    sum[k] = sg[k].s0;
+                static_assert(kSureChunks == 64, "a lane per chunk");
+                const SureSeg g = sg[lane < nch ? lane : 0];
+                if (tid < nch) {
+                    s_count[tid] = g.count;
+                    s_pairs[tid] = g.pairs;
+                    sum[tid] = g.s0;
                 }
+                whole.m = readlane_u32(wave_incl_u32(lane < nch ? min(g.count, (uint32_t)d.schunk) : 0u), 63);
+                whole.pairs = (int)readlane_u32(wave_incl_u32(lane < nch ? g.pairs : 0u), 63);
                 __syncthreads();
-                whole.m = 0;
 #pragma unroll 8
-                for (int k = 0; k < nch; ++k) {
-                    s0 += sum[k];
-                    whole.m += min(s_count[k], (uint32_t)d.schunk);
-                }
+                for (int k = 0; k < nch; ++k) s0 += sum[k];
             }
         }
     }
@@ -988,254 +1165,262 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
         }
     }
     __syncthreads();
-    while (true) {
-        __syncthreads();
-        const int sp = s_sp;
-        if (sp == 0) break;
-        klo = stack[sp - 1].klo;
-        khi = stack[sp - 1].khi;
-        c0 = stack[sp - 1].c0;
-        s0 = stack[sp - 1].s0;
-        const double tol = 1e-12 * (fabs(U) + N);
-        const bool skip = !(stack[sp - 1].lb <= U + tol);
-        __syncthreads();
-        if (tid == 0) s_sp = sp - 1;
-        if (skip) continue;
-        if (visits + whole.m > kSureVisits) {
-            if (tid == 0) {
-                s_inexact = 1;
-                s_sp = 0;
-            }
-            continue;
-        }
-        visits += whole.m;
-        const int shf = shift_for(khi - klo);
-        for (int b = tid; b < kSureBins; b += kSureThreads) {
-            cnt[b] = 0;
-            sum[b] = 0.0;
-        }
-        __syncthreads();
-        double below = 0.0;
-        for_each([&](T v) {
-            const uint64_t k = KT::key(v);
-            if (k >= klo && k < khi) {
-                const int b = (int)((k - klo) >> shf);
-                atomicAdd(&cnt[b], 1u);
-                atomicAdd(&sum[b], (double)v * (double)v);
-            } else if (need_s0 && k < klo) {
-                below = fma((double)v, (double)v, below);
-            }
-        });
-        if (need_s0) {
-            below = wave_sum(below);
-            if (lane == 0) sh.ws[wave] = below;
-        }
-        __syncthreads();
-        if (need_s0) {
-            (void)waves_before(sh.ws, wave, &s0);
-            need_s0 = false;
+    // (without pairs, as most components are, the code of their loops is out of the way)
+    auto search = [&](auto pairs) {
+        while (true) {
             __syncthreads();
-        }
-        uint32_t c[PER], pc;
-        double q[PER], lb[PER], ps, us, ut;
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            c[j] = cnt[PER * tid + j];
-            q[j] = sum[PER * tid + j];
-        }
-        range_select<T>(c, q, N, klo, khi, shf, c0, s0, sh, &pc, &ps, lb, &us, &ut);
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {       // exclusive prefixes
-            pre[PER * tid + j] = pc;
-            sum[PER * tid + j] = ps;
-            pc += c[j];
-            ps += q[j];
-        }
-        block_argmin(us, ut, sh);
-        if (us < U) {
-            U = us;
-            Ut = ut;
-        }
-        if (shf == 0) {                       // one value per bin: the bounds are exact
-            if (us < best_s || (us == best_s && ut < best_t)) {
-                best_s = us;
-                best_t = ut;
-            }
-            continue;
-        }
-        const double lim = U + 1e-12 * (fabs(U) + N);
-        int f = 0x7fffffff, l = -1, mx = 0, nh = 0;
-        uint32_t m = 0, ml = 0;
-#pragma unroll
-        for (int j = 0; j < PER; ++j)
-            if (lb[j] <= lim) {
-                const int b = PER * tid + j, n = c[j] < 0x7fffffffu ? (int)c[j] : 0x7fffffff;
-                f = b < f ? b : f;
-                l = b;
-                mx = n > mx ? n : mx;
-                nh += n > kSureHeavy ? 1 : 0;
-                m += c[j];
-                ml += n > kSureHeavy ? 0 : c[j];
-            }
-        const int wf = wave_minmax_i32<false>(f), wl = wave_minmax_i32<true>(l), wx = wave_minmax_i32<true>(mx);
-        const uint32_t wm = wave_incl_u32(m), wh = wave_incl_u32((uint32_t)nh), wlt = wave_incl_u32(ml);
-        __syncthreads();
-        if (lane == 63) {
-            sh.wf[wave] = wf;
-            sh.wl[wave] = wl;
-            sh.wx[wave] = wx;
-            sh.wc[wave] = wm;
-            sh.wn[wave] = wh;
-            sh.wm[wave] = wlt;
-        }
-        __syncthreads();
-        f = waves_minmax<false>(sh.wf);
-        l = waves_minmax<true>(sh.wl);
-        mx = waves_minmax<true>(sh.wx);
-        uint32_t total, heavies, light;
-        (void)waves_before(sh.wc, wave, &total);
-        (void)waves_before(sh.wn, wave, &heavies);
-        (void)waves_before(sh.wm, wave, &light);
-        if (l < 0) continue;
-        if ((total > (uint32_t)CAP || mx > kSureLight) && (l - f + 1) * 2 <= kSureBins) {
-            // the surviving bins span at most half the range: search that
-            if (tid == 0) {
-                const uint64_t hi = klo + ((uint64_t)(l + 1) << shf);
-                SureRange& r = stack[s_sp];
-                r.klo = klo + ((uint64_t)f << shf);
-                r.khi = hi < khi ? hi : khi;
-                r.c0 = c0 + pre[f];
-                r.s0 = s0 + sum[f];
-                r.lb = -__builtin_inf();
-                s_sp = s_sp + 1;
-            }
-            continue;
-        }
-        if (light > (uint32_t)CAP || heavies > (uint32_t)kSureHeavies) {
-            // flat over more than half the range: windows of it, each a range with bins as
-            // many times finer, down to about a sixteenth of the values
-            const int span = l - f + 1;
-            const int nw = (int)min((uint32_t)kSureWindows, total / (4u * CAP) + 2u);
-            if (tid < kSureWindows) {
-                s_wlo[tid] = kSureBins;
-                s_whi[tid] = -1;
-            }
+            const int sp = s_sp;
+            if (sp == 0) break;
+            klo = stack[sp - 1].klo;
+            khi = stack[sp - 1].khi;
+            c0 = stack[sp - 1].c0;
+            s0 = stack[sp - 1].s0;
+            const double tol = 1e-12 * (fabs(U) + N);
+            const bool skip = !(stack[sp - 1].lb <= U + tol);
             __syncthreads();
-#pragma unroll
-            for (int j = 0; j < PER; ++j)
-                if (lb[j] <= lim) {
-                    const int b = PER * tid + j, w = (b - f) * nw / span;
-                    atomicMin(&s_wlo[w], b);
-                    atomicMax(&s_whi[w], b);
-                }
-            __syncthreads();
-            if (tid < nw && s_whi[tid] >= 0) {
-                const int at = atomicAdd(&s_sp, 1), b0 = s_wlo[tid], b1 = s_whi[tid];
-                if (at < kSureStack) {
-                    const uint64_t hi = klo + ((uint64_t)(b1 + 1) << shf);
-                    SureRange& r = stack[at];
-                    r.klo = klo + ((uint64_t)b0 << shf);
-                    r.khi = hi < khi ? hi : khi;
-                    r.c0 = c0 + pre[b0];
-                    r.s0 = s0 + sum[b0];
-                    r.lb = -__builtin_inf();
-                } else {
+            if (tid == 0) s_sp = sp - 1;
+            if (skip) continue;
+            if (visits + whole.m + whole.pairs > kSureVisits) {
+                if (tid == 0) {
                     s_inexact = 1;
+                    s_sp = 0;
                 }
+                continue;
+            }
+            visits += whole.m + whole.pairs;
+            const int shf = shift_for(khi - klo);
+            for (int b = tid; b < kSureBins; b += kSureThreads) {
+                cnt[b] = 0;
+                sum[b] = 0.0;
             }
             __syncthreads();
-            if (tid == 0 && s_sp > kSureStack) s_sp = kSureStack;
-            continue;
-        }
-        // bins too large to evaluate value by value become ranges of their own
-        uint32_t g[PER], tg = 0;
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int b = PER * tid + j;
-            g[j] = 0;
-            if (!(lb[j] <= lim)) continue;
-            if (c[j] > (uint32_t)kSureHeavy) {
-                const int at = atomicAdd(&s_sp, 1);
-                if (at < kSureStack) {
-                    const uint64_t hi = klo + ((uint64_t)(b + 1) << shf);
-                    SureRange& r = stack[at];
-                    r.klo = klo + ((uint64_t)b << shf);
-                    r.khi = hi < khi ? hi : khi;
-                    r.c0 = c0 + pre[b];
-                    r.s0 = s0 + sum[b];
-                    r.lb = lb[j];
-                } else {
-                    s_inexact = 1;
-                }
-            } else {
-                g[j] = c[j];
-                tg += c[j];
-            }
-        }
-        const uint32_t ig = wave_incl_u32(tg);
-        __syncthreads();
-        if (lane == 63) sh.wc[wave] = ig;
-        if (tid == 0 && s_sp > kSureStack) s_sp = kSureStack;
-        __syncthreads();
-        const uint32_t og = waves_before(sh.wc, wave, &light) + ig - tg;
-        if (light) {                          // at most CAP values
-            if (tid < kSureBins / 32) bits[tid] = 0;
-            __syncthreads();
-            uint32_t o = og;
-            uint32_t mine = 0;
-#pragma unroll
-            for (int j = 0; j < PER; ++j) {
-                if (g[j]) {
-                    off[PER * tid + j] = o;
-                    mine |= 1u << j;
-                }
-                o += g[j];
-            }
-            if (mine) atomicOr(&bits[tid >> 3], mine << (4 * (tid & 7)));
-            __syncthreads();
-            for_each([&](T v) {
+            double below = 0.0;
+            for_each(pairs, [&](T v, uint32_t n) {
                 const uint64_t k = KT::key(v);
                 if (k >= klo && k < khi) {
                     const int b = (int)((k - klo) >> shf);
-                    if ((bits[b >> 5] >> (b & 31)) & 1u) keys[atomicAdd(&off[b], 1u)] = (K)k;
+                    atomicAdd(&cnt[b], n);
+                    atomicAdd(&sum[b], (double)n * ((double)v * (double)v));
+                } else if (need_s0 && k < klo) {
+                    below = fma((double)v, (double)v, below);
                 }
             });
+            if (need_s0) {
+                below = wave_sum(below);
+                if (lane == 0) sh.ws[wave] = below;
+            }
             __syncthreads();
-            double es = __builtin_inf(), et = 0.0;
-            for (int i = tid; i < (int)light; i += kSureThreads) {
-                const uint64_t key = keys[i];
-                const int b = (int)((key - klo) >> shf);
-                const int n = (int)cnt[b], j1 = (int)off[b];
-                int in = 0;
-                double sq = 0.0;
-                for (int j = j1 - n; j < j1; j += 4) {      // four reads in flight, added in order
-                    uint64_t kj[4];
+            if (need_s0) {
+                (void)waves_before(sh.ws, wave, &s0);
+                need_s0 = false;
+                __syncthreads();
+            }
+            uint32_t c[PER], pc;
+            double q[PER], lb[PER], ps, us, ut;
 #pragma unroll
-                    for (int w = 0; w < 4; ++w) kj[w] = keys[j + w < j1 ? j + w : j1 - 1];
+            for (int j = 0; j < PER; ++j) {
+                c[j] = cnt[PER * tid + j];
+                q[j] = sum[PER * tid + j];
+            }
+            range_select<T>(c, q, N, klo, khi, shf, c0, s0, sh, &pc, &ps, lb, &us, &ut);
 #pragma unroll
-                    for (int w = 0; w < 4; ++w)
-                        if (j + w < j1 && kj[w] <= key) {
-                            const double vj = KT::val(kj[w]);
-                            ++in;
-                            sq = fma(vj, vj, sq);
+            for (int j = 0; j < PER; ++j) {       // exclusive prefixes
+                pre[PER * tid + j] = pc;
+                sum[PER * tid + j] = ps;
+                pc += c[j];
+                ps += q[j];
+            }
+            block_argmin(us, ut, sh);
+            if (us < U) {
+                U = us;
+                Ut = ut;
+            }
+            if (shf == 0) {                       // one value per bin: the bounds are exact
+                if (us < best_s || (us == best_s && ut < best_t)) {
+                    best_s = us;
+                    best_t = ut;
+                }
+                continue;
+            }
+            const double lim = U + 1e-12 * (fabs(U) + N);
+            int f = 0x7fffffff, l = -1, mx = 0, nh = 0;
+            uint32_t m = 0, ml = 0;
+#pragma unroll
+            for (int j = 0; j < PER; ++j)
+                if (lb[j] <= lim) {
+                    const int b = PER * tid + j, n = c[j] < 0x7fffffffu ? (int)c[j] : 0x7fffffff;
+                    f = b < f ? b : f;
+                    l = b;
+                    mx = n > mx ? n : mx;
+                    nh += n > kSureHeavy ? 1 : 0;
+                    m += c[j];
+                    ml += n > kSureHeavy ? 0 : c[j];
+                }
+            const int wf = wave_minmax_i32<false>(f), wl = wave_minmax_i32<true>(l), wx = wave_minmax_i32<true>(mx);
+            const uint32_t wm = wave_incl_u32(m), wh = wave_incl_u32((uint32_t)nh), wlt = wave_incl_u32(ml);
+            __syncthreads();
+            if (lane == 63) {
+                sh.wf[wave] = wf;
+                sh.wl[wave] = wl;
+                sh.wx[wave] = wx;
+                sh.wc[wave] = wm;
+                sh.wn[wave] = wh;
+                sh.wm[wave] = wlt;
+            }
+            __syncthreads();
+            f = waves_minmax<false>(sh.wf);
+            l = waves_minmax<true>(sh.wl);
+            mx = waves_minmax<true>(sh.wx);
+            uint32_t total, heavies, light;
+            (void)waves_before(sh.wc, wave, &total);
+            (void)waves_before(sh.wn, wave, &heavies);
+            (void)waves_before(sh.wm, wave, &light);
+            if (l < 0) continue;
+            if ((total > (uint32_t)CAP || mx > kSureLight) && (l - f + 1) * 2 <= kSureBins) {
+                // the surviving bins span at most half the range: search that
+                if (tid == 0) {
+                    const uint64_t hi = klo + ((uint64_t)(l + 1) << shf);
+                    SureRange& r = stack[s_sp];
+                    r.klo = klo + ((uint64_t)f << shf);
+                    r.khi = hi < khi ? hi : khi;
+                    r.c0 = c0 + pre[f];
+                    r.s0 = s0 + sum[f];
+                    r.lb = -__builtin_inf();
+                    s_sp = s_sp + 1;
+                }
+                continue;
+            }
+            if (light > (uint32_t)CAP || heavies > (uint32_t)kSureHeavies) {
+                // flat over more than half the range: windows of it, each a range with bins as
+                // many times finer, down to about a sixteenth of the values
+                const int span = l - f + 1;
+                const int nw = (int)min((uint32_t)kSureWindows, total / (4u * CAP) + 2u);
+                if (tid < kSureWindows) {
+                    s_wlo[tid] = kSureBins;
+                    s_whi[tid] = -1;
+                }
+                __syncthreads();
+#pragma unroll
+                for (int j = 0; j < PER; ++j)
+                    if (lb[j] <= lim) {
+                        const int b = PER * tid + j, w = (b - f) * nw / span;
+                        atomicMin(&s_wlo[w], b);
+                        atomicMax(&s_whi[w], b);
+                    }
+                __syncthreads();
+                if (tid < nw && s_whi[tid] >= 0) {
+                    const int at = atomicAdd(&s_sp, 1), b0 = s_wlo[tid], b1 = s_whi[tid];
+                    if (at < kSureStack) {
+                        const uint64_t hi = klo + ((uint64_t)(b1 + 1) << shf);
+                        SureRange& r = stack[at];
+                        r.klo = klo + ((uint64_t)b0 << shf);
+                        r.khi = hi < khi ? hi : khi;
+                        r.c0 = c0 + pre[b0];
+                        r.s0 = s0 + sum[b0];
+                        r.lb = -__builtin_inf();
+                    } else {
+                        s_inexact = 1;
+                    }
+                }
+                __syncthreads();
+                if (tid == 0 && s_sp > kSureStack) s_sp = kSureStack;
+                continue;
+            }
+            // bins too large to evaluate value by value become ranges of their own
+            uint32_t g[PER], tg = 0;
+#pragma unroll
+            for (int j = 0; j < PER; ++j) {
+                const int b = PER * tid + j;
+                g[j] = 0;
+                if (!(lb[j] <= lim)) continue;
+                if (c[j] > (uint32_t)kSureHeavy) {
+                    const int at = atomicAdd(&s_sp, 1);
+                    if (at < kSureStack) {
+                        const uint64_t hi = klo + ((uint64_t)(b + 1) << shf);
+                        SureRange& r = stack[at];
+                        r.klo = klo + ((uint64_t)b << shf);
+                        r.khi = hi < khi ? hi : khi;
+                        r.c0 = c0 + pre[b];
+                        r.s0 = s0 + sum[b];
+                        r.lb = lb[j];
+                    } else {
+                        s_inexact = 1;
+                    }
+                } else {
+                    g[j] = c[j];
+                    tg += c[j];
+                }
+            }
+            const uint32_t ig = wave_incl_u32(tg);
+            __syncthreads();
+            if (lane == 63) sh.wc[wave] = ig;
+            if (tid == 0 && s_sp > kSureStack) s_sp = kSureStack;
+            __syncthreads();
+            const uint32_t og = waves_before(sh.wc, wave, &light) + ig - tg;
+            if (light) {                          // at most CAP values
+                if (tid < kSureBins / 32) bits[tid] = 0;
+                __syncthreads();
+                uint32_t o = og;
+                uint32_t mine = 0;
+#pragma unroll
+                for (int j = 0; j < PER; ++j) {
+                    if (g[j]) {
+                        off[PER * tid + j] = o;
+                        mine |= 1u << j;
+                    }
+                    o += g[j];
+                }
+                if (mine) atomicOr(&bits[tid >> 3], mine << (4 * (tid & 7)));
+                __syncthreads();
+                for_each(pairs, [&](T v, uint32_t n) {
+                    const uint64_t k = KT::key(v);
+                    if (k >= klo && k < khi) {
+                        const int b = (int)((k - klo) >> shf);
+                        if ((bits[b >> 5] >> (b & 31)) & 1u) {
+                            const uint32_t at = atomicAdd(&off[b], n);
+                            for (uint32_t i = 0; i < n; ++i) keys[at + i] = (K)k;
                         }
+                    }
+                });
+                __syncthreads();
+                double es = __builtin_inf(), et = 0.0;
+                for (int i = tid; i < (int)light; i += kSureThreads) {
+                    const uint64_t key = keys[i];
+                    const int b = (int)((key - klo) >> shf);
+                    const int n = (int)cnt[b], j1 = (int)off[b];
+                    int in = 0;
+                    double sq = 0.0;
+                    for (int j = j1 - n; j < j1; j += 4) {      // four reads in flight, added in order
+                        uint64_t kj[4];
+#pragma unroll
+                        for (int w = 0; w < 4; ++w) kj[w] = keys[j + w < j1 ? j + w : j1 - 1];
+#pragma unroll
+                        for (int w = 0; w < 4; ++w)
+                            if (j + w < j1 && kj[w] <= key) {
+                                const double vj = KT::val(kj[w]);
+                                ++in;
+                                sq = fma(vj, vj, sq);
+                            }
+                    }
+                    const double cc = (double)(c0 + pre[b]) + (double)in, S = s0 + sum[b] + sq, v = KT::val(key);
+                    const double sv = N - 2.0 * cc + S + (N - cc) * v * v;
+                    if (sv < es || (sv == es && v < et)) {
+                        es = sv;
+                        et = v;
+                    }
                 }
-                const double cc = (double)(c0 + pre[b]) + (double)in, S = s0 + sum[b] + sq, v = KT::val(key);
-                const double sv = N - 2.0 * cc + S + (N - cc) * v * v;
-                if (sv < es || (sv == es && v < et)) {
-                    es = sv;
-                    et = v;
+                block_argmin(es, et, sh);
+                if (es < best_s || (es == best_s && et < best_t)) {
+                    best_s = es;
+                    best_t = et;
                 }
+                if (best_s < U) U = best_s;
+                __syncthreads();
             }
-            block_argmin(es, et, sh);
-            if (es < best_s || (es == best_s && et < best_t)) {
-                best_s = es;
-                best_t = et;
-            }
-            if (best_s < U) U = best_s;
-            __syncthreads();
         }
-    }
+    };
+    if (__builtin_expect(whole.pairs == 0, 1)) search(std::integral_constant<bool, false>{});
+    else search(std::integral_constant<bool, true>{});
     if (tid == 0) {
         if (s_inexact && U < best_s) {        // the end of a bin: no value of the component
             best_s = U;
