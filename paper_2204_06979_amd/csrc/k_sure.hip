@@ -18,7 +18,8 @@
 //    of each chunk, one LDS atomic per value, into a row of its own.
 // 2. k_sure_gather: every block adds its component's rows, finds the range of
 //    the surviving bins, and copies its chunk's values in that range into its
-//    segment of a list, with the sum of squares of those below.
+//    segment of a list, with the sum of squares of those below; tied values go
+//    there as pairs of value and count.
 //    Beyond kSureLarge values k_sure_rows adds the rows up first, and rounds of
 //    k_sure_refine and k_sure_narrow shorten the list before step 3.
 // 3. k_sure_finish, one block per component: histograms of counts and sums of
@@ -36,7 +37,7 @@
 // compared with the best one through the bins between the two.
 //
 // Bound by latency and LDS atomics: the three passes over the 21 MB of 349 x 1905
-// and 8 components take 10, 22 and 42 us, against 145 us for six passes with a
+// and 8 components take 10, 23 and 43 us, against 145 us for six passes with a
 // select in the last block of each; ten components of 145 x 217, one launch,
 // 37 us against 594; four FP64 ones of 64 x 64 25 us against 158.
 #include <type_traits>
