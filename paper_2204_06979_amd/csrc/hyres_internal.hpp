@@ -33,12 +33,13 @@ constexpr double kH3 = -0.12940952255126037;
 
 // SURE threshold search: the key range [klo, khi) that survives a histogram, the
 // values below it (exact zeros included), the smallest upper bound of the risk with
-// its threshold, and the exact zeros; after a refining round also the squares below
-// the range and the values and pairs in it.
+// its threshold, the exact zeros, and where the bins of the first histogram are
+// narrowest; after a refining round also the squares below the range and the values
+// and pairs in it.
 struct SureSel {
     uint64_t klo, khi, c0;
     double s0, U, Ut;
-    uint32_t zeros, count, pairs, pad;
+    uint32_t zeros, count, pairs, fine;
 };
 // ... and per chunk: squares of its values below the first range, its values inside
 // (one by one, and pairs of a tied value and its count).

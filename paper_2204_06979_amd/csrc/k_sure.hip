@@ -30,7 +30,7 @@
 //    themselves.
 //
 // The first histogram has 512 bins per octave of [1/16, 8), where thresholds
-// of unit-noise coefficients lie: 16 per octave (one key range for all numbers)
+// of unit-noise coefficients lie (lower for components of smaller values): 16 per octave (one key range for all numbers)
 // put most values of a block into some fifty bins, whose LDS atomics queued,
 // and left most of the values to a second full histogram.  Its sums are not
 // needed: the squares of a bin lie between those of its edges, and a bin is
@@ -62,17 +62,16 @@ constexpr int kSureStack = 256;     // ranges waiting
 // same everywhere, a million are finished in 1.0-1.6 ms (bin by bin 1-55).
 constexpr int64_t kSureVisits = (int64_t)1 << 23;
 
-// Keys, and the bins of the first histogram: `lo_shift`-wide bins below 1/16
-// and from 8 on, 512 bins per octave between.  Word: the part of the key the
+// Keys, and the bins of the first histogram: 512 per octave in the seven octaves
+// from `fine` on, kSureOuter bits wide below and above.  Word: the part of the key the
 // bins are formed from (its high word for FP64).
 template <typename T> struct KeyTraits;
 template <> struct KeyTraits<float> {
     typedef uint32_t K;
     static constexpr int kCap = 16384;       // values evaluated at once (LDS)
     static constexpr int kWordShift = 0;
-    static constexpr uint32_t kC0 = 0x3D800000u, kC1 = 0x41000000u;
-    static constexpr int kMid = 14;          // bits below 512 bins per octave
-    static constexpr int kLow = 246, kHigh = kLow + 3584;
+    static constexpr int kOctave = 23;       // bits of an octave in a word
+    static constexpr uint32_t kFine = 0x3D800000u;       // 1/16
     __device__ static K key(float v) { return __float_as_uint(v) & 0x7fffffffu; }
     __device__ static double val(uint64_t k) { return (double)__uint_as_float((uint32_t)k); }
 };
@@ -80,33 +79,37 @@ template <> struct KeyTraits<double> {
     typedef unsigned long long K;
     static constexpr int kCap = 8192;
     static constexpr int kWordShift = 32;
-    static constexpr uint32_t kC0 = 0x3FB00000u, kC1 = 0x40200000u;
-    static constexpr int kMid = 11;
-    static constexpr int kLow = 255, kHigh = kLow + 3584;
+    static constexpr int kOctave = 20;
+    static constexpr uint32_t kFine = 0x3FB00000u;
     __device__ static K key(double v) {
         return (unsigned long long)__double_as_longlong(v) & 0x7fffffffffffffffull;
     }
     __device__ static double val(uint64_t k) { return __longlong_as_double((long long)k); }
 };
 constexpr int kSureOuter = 22;               // bits of an outer bin
+constexpr int kSureOctaves = 7;              // ... of 512 bins
+// Words of those octaves, and the first bin of them
+template <typename T> constexpr uint32_t kFineSpan = (uint32_t)kSureOctaves << KeyTraits<T>::kOctave;
+__device__ __forceinline__ int fine_bin(uint32_t fine) { return (int)((fine + (1u << kSureOuter) - 1) >> kSureOuter); }
 template <typename T>
-__device__ __forceinline__ int first_bin(typename KeyTraits<T>::K k) {
+__device__ __forceinline__ int first_bin(typename KeyTraits<T>::K k, uint32_t fine) {
     typedef KeyTraits<T> KT;
     const uint32_t w = (uint32_t)((uint64_t)k >> KT::kWordShift);
-    if (w < KT::kC0) return (int)(w >> kSureOuter);
-    if (w < KT::kC1) return KT::kLow + (int)((w - KT::kC0) >> KT::kMid);
-    return KT::kHigh + (int)((w - KT::kC1) >> kSureOuter);
+    if (w < fine) return (int)(w >> kSureOuter);
+    const int low = fine_bin(fine);
+    if (w - fine < kFineSpan<T>) return low + (int)((w - fine) >> (KT::kOctave - 9));
+    return low + kSureOctaves * 512 + (int)((w - fine - kFineSpan<T>) >> kSureOuter);
 }
 // Smallest key of bin b (the end of the keys beyond the last bin).
 template <typename T>
-__device__ __forceinline__ uint64_t first_edge(int b) {
+__device__ __forceinline__ uint64_t first_edge(int b, uint32_t fine) {
     typedef KeyTraits<T> KT;
+    const int low = fine_bin(fine), high = low + kSureOctaves * 512;
     uint64_t w;
-    if (b < KT::kLow) w = (uint64_t)b << kSureOuter;
-    else if (b < KT::kHigh) w = KT::kC0 + ((uint64_t)(b - KT::kLow) << KT::kMid);
-    else w = KT::kC1 + ((uint64_t)(b - KT::kHigh) << kSureOuter);
+    if (b < low) w = (uint64_t)b << kSureOuter;
+    else if (b < high) w = fine + ((uint64_t)(b - low) << (KT::kOctave - 9));
+    else w = (uint64_t)fine + kFineSpan<T> + ((uint64_t)(b - high) << kSureOuter);
     if (w > 0x80000000ull) w = 0x80000000ull;
-    if (b < KT::kLow && w > KT::kC0) w = KT::kC0;
     return w << KT::kWordShift;
 }
 
@@ -232,7 +235,7 @@ __device__ __forceinline__ int waves_minmax(const int* w) {
 // First histogram of values e0..e1-1 into lc (kSureBins counts, zeroed by the
 // caller).  Each thread keeps its zeros; returns them.
 template <typename T, int U>
-__device__ __forceinline__ uint32_t first_histogram_u(const HYRES_GLOBAL T* cf, int64_t e0, int64_t e1, uint32_t* lc) {
+__device__ __forceinline__ uint32_t first_histogram_u(const HYRES_GLOBAL T* cf, int64_t e0, int64_t e1, uint32_t fine, uint32_t* lc) {
     typedef KeyTraits<T> KT;
     uint32_t nz = 0;
     for (int64_t e = e0 + threadIdx.x; e < e1; e += U * kSureThreads) {
@@ -245,7 +248,7 @@ __device__ __forceinline__ uint32_t first_histogram_u(const HYRES_GLOBAL T* cf, 
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const auto k = KT::key(e + (int64_t)u * kSureThreads < e1 ? v[u] : (T)0);
-            if (k != 0) atomicAdd(&lc[first_bin<T>(k)], 1u);
+            if (k != 0) atomicAdd(&lc[first_bin<T>(k, fine)], 1u);
             else if (e + (int64_t)u * kSureThreads < e1) ++nz;
         }
     }
@@ -255,8 +258,9 @@ __device__ __forceinline__ uint32_t first_histogram_u(const HYRES_GLOBAL T* cf, 
 // zeros take 1.3 us more (27.5 and 28.9 us for four components of 4096; eight at a
 // time up to 8192 would save 0.9 there, and cost FP64 searches of any size 0.3).
 template <typename T>
-__device__ __forceinline__ uint32_t first_histogram(const HYRES_GLOBAL T* cf, int64_t e0, int64_t e1, uint32_t* lc) {
-    return e1 - e0 <= 4 * kSureThreads ? first_histogram_u<T, 4>(cf, e0, e1, lc) : first_histogram_u<T, kSureLoads>(cf, e0, e1, lc);
+__device__ __forceinline__ uint32_t first_histogram(const HYRES_GLOBAL T* cf, int64_t e0, int64_t e1, uint32_t fine, uint32_t* lc) {
+    return e1 - e0 <= 4 * kSureThreads ? first_histogram_u<T, 4>(cf, e0, e1, fine, lc)
+                                       : first_histogram_u<T, kSureLoads>(cf, e0, e1, fine, lc);
 }
 
 // Whether a thread's bins among first..last show tied values: a bin of more than 64
@@ -281,8 +285,8 @@ __device__ __forceinline__ bool bins_tied(const uint32_t (&c)[kBinsPer], int fir
 // the sum over the bins between, bounded by their edges.
 // TIES: sh.tied (cleared before) tells whether a bin shows tied values.
 template <typename T, bool TIES>
-__device__ __forceinline__ void first_select(const uint32_t (&c)[kBinsPer], uint32_t zeros, double N, SureShared& sh,
-                                             int* first, int* last, uint64_t* c0) {
+__device__ __forceinline__ void first_select(const uint32_t (&c)[kBinsPer], uint32_t zeros, double N, uint32_t fine,
+                                             SureShared& sh, int* first, int* last, uint64_t* c0) {
     typedef KeyTraits<T> KT;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     double a[kBinsPer], b[kBinsPer];
@@ -291,7 +295,7 @@ __device__ __forceinline__ void first_select(const uint32_t (&c)[kBinsPer], uint
 #pragma unroll
     for (int j = 0; j < kBinsPer; ++j) {
         const int bin = kBinsPer * tid + j;
-        const double lo = KT::val(first_edge<T>(bin)), hi = KT::val(first_edge<T>(bin + 1) - 1);
+        const double lo = KT::val(first_edge<T>(bin, fine)), hi = KT::val(first_edge<T>(bin + 1, fine) - 1);
         a[j] = lo * lo;
         b[j] = hi * hi;
         if (c[j]) {
@@ -402,10 +406,25 @@ __device__ __forceinline__ void first_select(const uint32_t (&c)[kBinsPer], uint
 
 // Keys of the bins first..last, zeros left out.
 template <typename T>
-__device__ __forceinline__ void first_range(int first, int last, uint64_t* klo, uint64_t* khi) {
-    const uint64_t k = first_edge<T>(first);
+__device__ __forceinline__ void first_range(int first, int last, uint32_t fine, uint64_t* klo, uint64_t* khi) {
+    const uint64_t k = first_edge<T>(first, fine);
     *klo = k ? k : 1;
-    *khi = first_edge<T>(last + 1);
+    *khi = first_edge<T>(last + 1, fine);
+}
+
+// First word of the octaves of 512 bins for a component of N > kSureDirect values, from
+// 64 of them, the same for every wave: 1/16, but where the largest of the 64 is below
+// that (and not zero), 1/32 to 1/64 of it.  The risk of values far below the noise
+// falls up to the largest of them, and with 1/16 a million FP64 ones of standard
+// deviation 0.001 share a few bins: the search took 0.6 ms, of equally spaced values
+// 2.1, most of it the one finishing block (0.06, 0.07).  Values far above it leave the
+// first few: nothing to gain.
+template <typename T>
+__device__ __forceinline__ uint32_t sure_fine(T v) {
+    typedef KeyTraits<T> KT;
+    const uint32_t w = (uint32_t)wave_minmax_i32<true>((int)(uint32_t)((uint64_t)KT::key(v) >> KT::kWordShift));
+    const uint32_t octave = w >> KT::kOctave << KT::kOctave, below = 5u << KT::kOctave;
+    return w >= KT::kFine || w == 0 ? KT::kFine : octave > below ? octave - below : 0u;
 }
 
 template <typename T>
@@ -416,11 +435,15 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_hist(const CubeDesc* __re
     const CubeDesc& d = descs[c];
     const int nch = d.snch, local = blockIdx.x - items[c], comp = local / nch, chunk = local - comp * nch;
     const int tid = threadIdx.x;
+    const int64_t N = sure_count(d), e0 = (int64_t)chunk * d.schunk, e1 = min(e0 + d.schunk, N);
+    const HYRES_GLOBAL T* cf = gmem(static_cast<const T*>(d.coef)) + (int64_t)comp * d.ncs;
+    static_assert(kSureDirect >= 64 * 64, "the sample's last is below N");
+    const T sample = cf[(tid & 63) * (N / 64) + (29 * tid & 63)];
     for (int b = tid; b < kSureBins; b += kSureThreads) lc[b] = 0;
     __syncthreads();
-    const int64_t N = sure_count(d), e0 = (int64_t)chunk * d.schunk, e1 = min(e0 + d.schunk, N);
-    const uint32_t nz =
-        first_histogram<T>(gmem(static_cast<const T*>(d.coef)) + (int64_t)comp * d.ncs, e0, e1, lc);
+    const uint32_t fine = sure_fine<T>(sample);
+    if (chunk == 0 && tid == 0) d.ssel[comp * (d.srounds + 1)].fine = fine;
+    const uint32_t nz = first_histogram<T>(cf, e0, e1, fine, lc);
     if (nz) atomicAdd(&lc[kZeroSlot], nz);
     __syncthreads();
     HYRES_GLOBAL uint32_t* row = gmem(d.shist) + comp * d.shcs;
@@ -613,6 +636,8 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_gather(const CubeDesc* __
             v[u] = cf[i < e1 ? i : N - 1];
         }
     };
+    SureSel* s = d.ssel + comp * (d.srounds + 1);
+    const uint32_t fine = s->fine;
     uint32_t c[kBinsPer] = {0, 0, 0, 0};
     static_assert(kBinsPer == 4, "rows are read four bins at a time");
     const HYRES_GLOBAL uint32_t* rows = gmem(d.shist) + comp * d.shcs;
@@ -653,11 +678,10 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_gather(const CubeDesc* __
     int first, last;
     uint64_t c0;
     fetch(e0 + tid - lane);                  // under the selection
-    first_select<T, true>(c, zeros, (double)N, sh, &first, &last, &c0);
+    first_select<T, true>(c, zeros, (double)N, fine, sh, &first, &last, &c0);
     uint64_t klo = 1, khi = 1;
-    if (first >= 0) first_range<T>(first, last, &klo, &khi);
+    if (first >= 0) first_range<T>(first, last, fine, &klo, &khi);
     if (chunk == 0 && tid == 0) {
-        SureSel* s = d.ssel + comp * (d.srounds + 1);
         s->klo = klo;
         s->khi = khi;
         s->c0 = c0;
@@ -672,8 +696,8 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_gather(const CubeDesc* __
     if (__builtin_expect(tied, 0)) {
         clear_ties(ties);
         __syncthreads();
-        s0 = fold_ties<T>(cf + e0, e1 - e0, klo, khi, ties, [](typename KT::K k) { return first_bin<T>(k); }, seg,
-                          (uint32_t)d.segcap, &sh.count);
+        s0 = fold_ties<T>(cf + e0, e1 - e0, klo, khi, ties, [fine](typename KT::K k) { return first_bin<T>(k, fine); },
+                          seg, (uint32_t)d.segcap, &sh.count);
     } else {
         for (int64_t e = e0 + tid - lane; e < e1; e += U * kSureThreads) {   // whole waves
 #pragma unroll
@@ -1102,7 +1126,7 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
     if (nch == 1) {
         for (int b = tid; b < kSureBins; b += kSureThreads) cnt[b] = 0;
         __syncthreads();
-        const uint32_t nz = first_histogram<T>(coef, 0, Ni, cnt);
+        const uint32_t nz = first_histogram<T>(coef, 0, Ni, KT::kFine, cnt);
         if (nz) atomicAdd(&cnt[kZeroSlot], nz);
         __syncthreads();
         uint32_t c[PER];
@@ -1111,8 +1135,8 @@ __global__ __launch_bounds__(kSureThreads) void k_sure_finish(const CubeDesc* __
         zeros = cnt[kZeroSlot];
         if (tid == kSureThreads - 1) c[PER - 1] = 0;
         int first, last;
-        first_select<T, false>(c, zeros, N, sh, &first, &last, &c0);
-        if (first >= 0) first_range<T>(first, last, &klo, &khi);
+        first_select<T, false>(c, zeros, N, KT::kFine, sh, &first, &last, &c0);
+        if (first >= 0) first_range<T>(first, last, KT::kFine, &klo, &khi);
         need_s0 = true;
     } else {
         const SureSel s = d.ssel[comp * (d.srounds + 1) + d.srounds];
